@@ -27,8 +27,8 @@
 // Backward: the data gradient of a layer is the same convolution with the
 // weights transposed in the channels and flipped in the taps, masked by the
 // ReLU pattern of the forward activation; weight gradients are contractions
-// over voxels on v_mfma_f32_16x16x4f32 (FP32 operands, split over voxel
-// ranges, reduced in a fixed order).
+// over voxels on the same BF16 instruction (k_wgrad16, k_wgrad_few; split over
+// tiles, reduced in a fixed order).
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -485,10 +485,27 @@ __global__ __launch_bounds__(256) void k_conv_out1(const uint16_t* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // weight gradients: dW[t][ca][cg] = sum over samples and voxels of
-// a[v + tap_t][ca] g[v][cg]; one partial row per wave (a voxel range of one sample)
+// a[v + tap_t][ca] g[v][cg], on v_mfma_f32_16x16x32_bf16 with 32 voxels along x
+// as the contraction.  Both operands are stored in BF16, so the products are
+// exact and only the FP32 sums round, as with FP32 operands.
+//
+// The fields hold a voxel's channels together, the operands want one channel
+// of eight consecutive voxels per lane: a work-group stages x-rows channel by
+// channel in LDS (two voxels per 32-bit write; row strides of 28 and 20 words
+// spread the 16 channels of a 16-byte read over all banks), which reads every
+// element of a field once per tile instead of once per tap.
+// A work item is a tile of 32 x 8 voxels of one sample marched over ZC planes,
+// wave w taking rows 2 w and 2 w + 1 of every plane; the planes of the shifted
+// operand pass through a ring of four LDS planes and the next plane's loads are
+// in flight while the current one is multiplied (one barrier per plane).
+// The 16 -> 16 layers hold their 27 taps in 108 accumulator registers: one row
+// of a and its two x-shifted forms (made in registers) multiply the nine rows
+// of g around it, which the two rows of a wave share.
+// Bound by LDS reads and the matrix cores (two work-groups per compute unit at
+// 243 registers).  Measured at 64^3, 16 samples, against FP32 matrix cores fed
+// with 2-byte loads from global memory: 16 -> 16 channels 4424 -> 118 us (492
+// TFLOP/s), 2 -> 16 1085 -> 43 us, 16 -> 1 670 -> 35 us.
 // ---------------------------------------------------------------------------
-enum { WGR_16 = 0, WGR_W4 = 1, WGR_W1 = 2 };
-
 struct Vox {
   int x, y, z;
 };
@@ -500,93 +517,267 @@ __device__ __forceinline__ Vox vox_of(uint32_t v, uint32_t m0, uint32_t m1) {
   r.z = (int)(v / m1);
   return r;
 }
-__device__ __forceinline__ bool inside(int x, int y, int z, uint32_t m0, uint32_t m1, uint32_t m2) {
-  return x >= 0 && x < (int)m0 && y >= 0 && y < (int)m1 && z >= 0 && z < (int)m2;
+
+constexpr int GX = 32, GY = 8;                  // x-y tile of a work item
+constexpr int GRX = 20, GAX = 28;               // words of a staged channel row: 32 voxels; 8 + 32 + 8 (with x halo)
+constexpr int GG_PLANE = (GY + 2) * 16 * GRX;   // words of one staged plane of g (rows y0 - 1 .. y0 + 8)
+constexpr int GA_PLANE = GY * 16 * GAX;         // words of one staged plane of a
+
+// Work items (sample, z range, tile) of a weight-gradient pass; work-group w
+// takes items w, w + G, ...
+struct WgTiles {
+  uint32_t m0, m1, m2, ntx, nty, nzc, ZC, total;
+};
+
+__device__ __forceinline__ void wg_item(const WgTiles& w, uint32_t it, uint32_t& b, int& x0, int& y0, int& z0,
+                                        int& z1) {
+  x0 = (int)(it % w.ntx) * GX;
+  it /= w.ntx;
+  y0 = (int)(it % w.nty) * GY;
+  it /= w.nty;
+  z0 = (int)((it % w.nzc) * w.ZC);
+  b = it / w.nzc;
+  z1 = z0 + (int)w.ZC < (int)w.m2 ? z0 + (int)w.ZC : (int)w.m2;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ a, const uint16_t* __restrict__ g,
-                                               float* __restrict__ part, uint32_t part_ld, uint32_t part_off,
-                                               uint32_t rows, uint32_t rows_per_sample, uint32_t vox_per_row,
-                                               uint32_t m0, uint32_t m1, uint32_t m2) {
-  constexpr int NACC = MODE == WGR_16 ? 27 : (MODE == WGR_W4 ? 2 : 4);
-  constexpr int CA = MODE == WGR_W1 ? 2 : 16;
-  constexpr int CG = MODE == WGR_W4 ? 1 : 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t row = blockIdx.x * 4 + wave;
-  if (row >= rows) return;
-  const uint32_t b = row / rows_per_sample, ch = row - b * rows_per_sample;
-  const uint64_t n = (uint64_t)m0 * m1 * m2;
-  const uint32_t v0 = ch * vox_per_row;
-  const uint32_t v1 = (uint32_t)min<uint64_t>(n, (uint64_t)v0 + vox_per_row);
-  const uint16_t* as = a + (uint64_t)b * n * CA;
-  const uint16_t* gs = g + (uint64_t)b * n * CG;
+// Eight channels (half h) of the two voxels x, x + 1 of a row of a 16-channel
+// field (zero outside the grid; row < 0: the row is outside).
+struct VoxPair {
+  v4u a, b;
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ f, int64_t row, int x, int m0, int h) {
+    a = v4u{0u, 0u, 0u, 0u};
+    b = a;
+    if (row >= 0) {
+      if (x >= 0 && x < m0) a = *reinterpret_cast<const v4u*>(f + (row + x) * 16 + 8 * h);
+      if (x + 1 >= 0 && x + 1 < m0) b = *reinterpret_cast<const v4u*>(f + (row + x + 1) * 16 + 8 * h);
+    }
+  }
+  // channel by channel: word c * stride holds (voxel x, voxel x + 1) of channel c
+  __device__ __forceinline__ void store(uint32_t* dst, int stride) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      dst[(2 * i) * stride] = (a[i] & 0xffffu) | (b[i] << 16);
+      dst[(2 * i + 1) * stride] = (a[i] >> 16) | (b[i] & 0xffff0000u);
+    }
+  }
+};
+
+// Sums the four waves' accumulators in wave order (FP64, in LDS) and writes the
+// work-group's partial row: value q * 256 + dr * 16 + j < count.
+template <int NACC>
+__device__ __forceinline__ void wgrad_out(double* red, const v4f (&acc)[NACC], int wave, int lane, uint32_t count,
+                                          float* __restrict__ out) {
   const int j = lane & 15, kq = lane >> 4;
-  v4f acc[NACC];
+  for (int w = 0; w < 4; ++w) {
+    __syncthreads();                            // the staged planes, or the previous wave's sums, are read
+    if (wave != w) continue;
 #pragma unroll
-  for (int q = 0; q < NACC; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < NACC; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double* d = red + q * 256 + (4 * kq + r) * 16 + j;
+        *d = (w ? *d : 0.0) + (double)acc[q][r];
+      }
+  }
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < count; e += 256) out[e] = (float)red[e];
+}
 
-  for (uint32_t vb = v0; vb < v1; vb += 4) {
-    const uint32_t v = vb + kq;
-    const bool ok = v < v1;
-    const Vox p = vox_of(ok ? v : v0, m0, m1);
-    if constexpr (MODE == WGR_16) {
-      // A[ca = j][k] = a[v_k + tap][j], B[k][cg = j] = g[v_k][j]
-      const float gv = ok ? from_bf16(gs[(uint64_t)v * 16 + j]) : 0.f;
+// 16 -> 16 channel layers
+__global__ __launch_bounds__(256, 2) void k_wgrad16(const uint16_t* __restrict__ a, const uint16_t* __restrict__ g,
+                                                    float* __restrict__ part, uint32_t part_ld, uint32_t part_off,
+                                                    WgTiles wt) {
+  __shared__ __align__(16) uint32_t sm[2 * GA_PLANE + 4 * GG_PLANE];
+  static_assert(sizeof(sm) >= 27 * 256 * sizeof(double), "the staged planes are reused for the waves' sums");
+  uint32_t* const sa = sm;                      // a: two planes
+  uint32_t* const sg = sm + 2 * GA_PLANE;       // g: ring of four planes
+  const int m0 = (int)wt.m0, m1 = (int)wt.m1, m2 = (int)wt.m2;
+  const uint64_t n = (uint64_t)m0 * m1 * m2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 15, kq = lane >> 4;
+  constexpr int IA = GY * 18 * 2, IG = (GY + 2) * 16 * 2;      // voxel-pair halves of a plane of a and of g
+  constexpr int IPT = (IA + IG + 255) / 256;
+  v4f acc[27];
 #pragma unroll
-      for (int t = 0; t < 27; ++t) {
-        const int x = p.x + t % 3 - 1, y = p.y + (t / 3) % 3 - 1, z = p.z + t / 9 - 1;
-        float av = 0.f;
-        if (ok && inside(x, y, z, m0, m1, m2)) av = from_bf16(as[(((uint64_t)z * m1 + y) * m0 + x) * 16 + j]);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv, acc[t], 0, 0, 0);
-      }
-    } else if constexpr (MODE == WGR_W4) {
-      // A[ca = j][k] = a[v_k][j], B[k][col] = g[v_k - tap_col], col = 16 cb + j
-      const float av = ok ? from_bf16(as[(uint64_t)v * 16 + j]) : 0.f;
+  for (int q = 0; q < 27; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (uint32_t it = blockIdx.x; it < wt.total; it += gridDim.x) {
+    uint32_t b;
+    int x0, y0, z0, z1;
+    wg_item(wt, it, b, x0, y0, z0, z1);
+    const uint16_t* as = a + (uint64_t)b * n * 16;
+    const uint16_t* gs = g + (uint64_t)b * n * 16;
+    VoxPair vp[IPT];
+    // a's plane za (skipped when za < z0) and g's plane zg
+    auto load = [&](int za, int zg) {
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        const int t = 16 * cb + j;
-        float gv = 0.f;
-        if (ok && t < 27) {
-          const int x = p.x - (t % 3 - 1), y = p.y - ((t / 3) % 3 - 1), z = p.z - (t / 9 - 1);
-          if (inside(x, y, z, m0, m1, m2)) gv = from_bf16(gs[((uint64_t)z * m1 + y) * m0 + x]);
+      for (int u = 0; u < IPT; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
+        if (e < IA) {
+          const int h = e & 1, p = (e >> 1) % 18, r = (e >> 1) / 18;
+          const int y = y0 + r;
+          const bool in = za >= z0 && za < m2 && y < m1;
+          vp[u].load(as, in ? ((int64_t)za * m1 + y) * m0 : -1, x0 + 2 * p - 2, m0, h);
+        } else if (e < IA + IG) {
+          const int f = e - IA, h = f & 1, p = (f >> 1) & 15, r = f >> 5;
+          const int y = y0 + r - 1;
+          const bool in = zg >= 0 && zg < m2 && y >= 0 && y < m1;
+          vp[u].load(gs, in ? ((int64_t)zg * m1 + y) * m0 : -1, x0 + 2 * p, m0, h);
         }
-        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv, acc[cb], 0, 0, 0);
       }
-    } else {
-      // A[row][k] = x[v_k + tap_t][ci], row = 16 rb + j = 2 t + ci; B[k][co = j] = g[v_k][j]
-      const float gv = ok ? from_bf16(gs[(uint64_t)v * 16 + j]) : 0.f;
+    };
+    auto store = [&](int za, int zg) {
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        const int r = 16 * rb + j, t = r >> 1, ci = r & 1;
-        float av = 0.f;
-        if (ok && t < 27) {
-          const int x = p.x + t % 3 - 1, y = p.y + (t / 3) % 3 - 1, z = p.z + t / 9 - 1;
-          if (inside(x, y, z, m0, m1, m2)) av = from_bf16(as[(((uint64_t)z * m1 + y) * m0 + x) * 2 + ci]);
+      for (int u = 0; u < IPT; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
+        if (e < IA) {
+          const int h = e & 1, p = (e >> 1) % 18, r = (e >> 1) / 18;
+          // word 4 + p' of a channel row holds voxels 2 p', 2 p' + 1 of the tile (p' = p - 1)
+          vp[u].store(sa + (za & 1) * GA_PLANE + (r * 16 + 8 * h) * GAX + 3 + p, GAX);
+        } else if (e < IA + IG) {
+          const int f = e - IA, h = f & 1, p = (f >> 1) & 15, r = f >> 5;
+          vp[u].store(sg + ((zg + 4) & 3) * GG_PLANE + (r * 16 + 8 * h) * GRX + p, GRX);
         }
-        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv, acc[rb], 0, 0, 0);
+      }
+    };
+    __syncthreads();                            // the previous item's planes are read
+    load(z0 - 1, z0 - 1);
+    store(z0 - 1, z0 - 1);
+    load(z0 - 1, z0);
+    store(z0 - 1, z0);
+    load(z0, z0 + 1);
+    for (int z = z0; z < z1; ++z) {
+      // writes: a's buffer z & 1 and ring slot z + 1; the waves still in plane
+      // z - 1 read the other buffer and slots z - 2 .. z
+      store(z, z + 1);
+      __syncthreads();
+      if (z + 1 < z1) load(z + 1, z + 2);
+      v8bf gf[3][4];                            // g at plane z - 1 + q, rows 2 wave - 1 .. 2 wave + 2 of the tile
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          gf[q][r] = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4u*>(
+              sg + ((z + 3 + q) & 3) * GG_PLANE + ((2 * wave + r) * 16 + j) * GRX + 4 * kq));
+#pragma unroll
+      for (int yr = 0; yr < 2; ++yr) {
+        const uint32_t* row = sa + (z & 1) * GA_PLANE + ((2 * wave + yr) * 16 + j) * GAX + 4 + 4 * kq;
+        const v4u c = *reinterpret_cast<const v4u*>(row);
+        const uint32_t wl = row[-1], wr = row[4];
+        v4u lo, hi;                             // voxels one to the left (dx = -1) and to the right (dx = 1)
+        lo[0] = (wl >> 16) | (c[0] << 16);
+        hi[3] = (c[3] >> 16) | (wr << 16);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          lo[i + 1] = (c[i] >> 16) | (c[i + 1] << 16);
+          hi[i] = lo[i + 1];
+        }
+        const v8bf av[3] = {__builtin_bit_cast(v8bf, lo), __builtin_bit_cast(v8bf, c), __builtin_bit_cast(v8bf, hi)};
+        // tap (dz, dy, dx): a at v + tap, so g's plane z - dz (index 1 - dz) and row y - dy (index 1 - dy)
+#pragma unroll
+        for (int t = 0; t < 27; ++t) {
+          const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1;
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t % 3], gf[1 - dz][yr + 1 - dy], acc[t], 0, 0, 0);
+        }
       }
     }
   }
+  wgrad_out<27>(reinterpret_cast<double*>(sm), acc, wave, lane, 27 * 256,
+                part + (uint64_t)blockIdx.x * part_ld + part_off);
+}
 
-  // lane holds D[4 kq + r][j]
-  float* out = part + (uint64_t)row * part_ld + part_off;
+// Layers with few channels on one side: out[t C + ci][j] = sum_v q[v + S tap_t][ci] p[v][j]
+// for a C-channel field q and a 16-channel field p: the first layer (C = 2, S = 1,
+// q its input pair) and the last (C = 1, S = -1, q the output's gradient).  The
+// rows (t, ci) fill 16-row operand blocks; q is staged once per x offset, so
+// that every lane reads its own tap's row with one 16-byte read.
+template <int C, int S>
+__global__ __launch_bounds__(256) void k_wgrad_few(const uint16_t* __restrict__ q, const uint16_t* __restrict__ p,
+                                                   float* __restrict__ part, uint32_t part_ld, uint32_t part_off,
+                                                   WgTiles wt) {
+  constexpr int NB = (27 * C + 15) / 16;                       // 16-row blocks
+  constexpr int PP = GY * 16 * GRX, QP = (GY + 2) * C * 3 * GRX;   // words of a staged plane of p and of q
+  constexpr int SM = (2 * PP + 4 * QP) * 4 > NB * 2048 ? 2 * PP + 4 * QP : NB * 512;
+  __shared__ __align__(16) uint32_t sm[SM];
+  uint32_t* const sp = sm;
+  uint32_t* const sq = sm + 2 * PP;
+  const int m0 = (int)wt.m0, m1 = (int)wt.m1, m2 = (int)wt.m2;
+  const uint64_t n = (uint64_t)m0 * m1 * m2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 15, kq = lane >> 4;
+  static_assert(GY * 16 * 2 == 256 && (GY + 2) * 16 <= 256, "one voxel-pair half of p and one pair of q per thread");
+  v4f acc[NB];
 #pragma unroll
-  for (int q = 0; q < NACC; ++q) {
+  for (int k = 0; k < NB; ++k) acc[k] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (uint32_t it = blockIdx.x; it < wt.total; it += gridDim.x) {
+    uint32_t b;
+    int x0, y0, z0, z1;
+    wg_item(wt, it, b, x0, y0, z0, z1);
+    const uint16_t* ps = p + (uint64_t)b * n * 16;
+    const uint16_t* qs = q + (uint64_t)b * n * C;
+    VoxPair vp;
+    uint32_t qv[4];                                            // voxels x - 1 .. x + 2 of q (C channels each)
+    const int ph = threadIdx.x & 1, pp = (threadIdx.x >> 1) & 15, pr = threadIdx.x >> 5;
+    const int qp = threadIdx.x & 15, qr = threadIdx.x >> 4;    // q: pair and row (rows y0 - 1 .. y0 + 8)
+    auto load = [&](int zp, int zq) {
+      const bool in = zp >= z0 && zp < m2 && y0 + pr < m1;
+      vp.load(ps, in ? ((int64_t)zp * m1 + y0 + pr) * m0 : -1, x0 + 2 * pp, m0, ph);
+      const int y = y0 + qr - 1;
+      const bool qin = qr < GY + 2 && zq >= 0 && zq < m2 && y >= 0 && y < m1;
+      const int64_t row = ((int64_t)zq * m1 + y) * m0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int dr = 4 * kq + r;
-      if constexpr (MODE == WGR_16) {
-        out[q * 256 + dr * 16 + j] = acc[q][r];                 // dW[t = q][ca = dr][cg = j]
-      } else if constexpr (MODE == WGR_W4) {
-        const int t = 16 * q + j;                               // dW4[t][ca = dr]
-        if (t < 27) out[t * 16 + dr] = acc[q][r];
-      } else {
-        const int rr = 16 * q + dr;                             // dW1[t][ci][co = j], rr = 2 t + ci
-        if (rr < 54) out[rr * 16 + j] = acc[q][r];
+      for (int i = 0; i < 4; ++i) {
+        const int x = x0 + 2 * qp - 1 + i;
+        qv[i] = 0u;
+        if (qin && x >= 0 && x < m0) {
+          if constexpr (C == 2) qv[i] = *reinterpret_cast<const uint32_t*>(qs + (row + x) * 2);
+          else qv[i] = qs[row + x];
+        }
+      }
+    };
+    auto store = [&](int zp, int zq) {
+      vp.store(sp + (zp & 1) * PP + (pr * 16 + 8 * ph) * GRX + pp, GRX);
+      if (qr < GY + 2) {
+        uint32_t* d = sq + ((zq + 4) & 3) * QP + qr * (C * 3) * GRX + qp;
+#pragma unroll
+        for (int ci = 0; ci < C; ++ci)
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {                        // voxels x + s - 1, x + s
+            const uint32_t l = (qv[s] >> (16 * ci)) & 0xffffu, h = (qv[s + 1] >> (16 * ci)) & 0xffffu;
+            d[(ci * 3 + s) * GRX] = l | (h << 16);
+          }
+      }
+    };
+    __syncthreads();
+    load(z0 - 1, z0 - 1);
+    store(z0 - 1, z0 - 1);
+    load(z0 - 1, z0);
+    store(z0 - 1, z0);
+    load(z0, z0 + 1);
+    for (int z = z0; z < z1; ++z) {
+      store(z, z + 1);
+      __syncthreads();
+      if (z + 1 < z1) load(z + 1, z + 2);
+#pragma unroll
+      for (int yr = 0; yr < 2; ++yr) {
+        const int y = 2 * wave + yr;
+        const v8bf pv = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4u*>(
+            sp + (z & 1) * PP + (y * 16 + j) * GRX + 4 * kq));
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+          const int r = 16 * k + j, t = r / C, ci = r - t * C;
+          v4u w = {0u, 0u, 0u, 0u};
+          if (t < 27) {
+            const int dz = S * (t / 9 - 1), dy = S * ((t / 3) % 3 - 1), dx = S * (t % 3 - 1);
+            w = *reinterpret_cast<const v4u*>(sq + ((z + dz + 4) & 3) * QP +
+                                              ((y + 1 + dy) * (C * 3) + ci * 3 + dx + 1) * GRX + 4 * kq);
+          }
+          acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, w), pv, acc[k], 0, 0, 0);
+        }
       }
     }
   }
+  wgrad_out<NB>(reinterpret_cast<double*>(sm), acc, wave, lane, 27 * C * 16,
+                part + (uint64_t)blockIdx.x * part_ld + part_off);
 }
 
 // fixed-order sum of partial rows: stage[grp][p] over the rows of group grp
@@ -934,7 +1125,7 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ w, float* __re
 
 namespace {
 
-constexpr int WGRAD_ROWS = 2048;      // partial rows of the weight gradients (about 2 waves per SIMD)
+constexpr int WGRAD_ROWS = 2048;      // partial rows of the weight gradients (at most)
 constexpr int WGRAD_GROUPS = 32;      // first-stage groups of their fixed-order reduction
 
 void free_net(ope_net* t) {
@@ -1000,12 +1191,36 @@ hipError_t pack_x(ope_net* t, const float* X, const float* v2, uint32_t B) {
   return hipGetLastError();
 }
 
-template <int MODE>
-hipError_t wgrad(ope_net* t, const uint16_t* a, const uint16_t* g, uint32_t off, uint32_t B, uint32_t rps,
-                 uint32_t vpr) {
-  const uint32_t rows = B * rps;
-  hipLaunchKernelGGL(k_wgrad<MODE>, dim3((rows + 3) / 4), dim3(256), 0, t->ctx->stream, a, g, t->part,
-                     (uint32_t)OPE_NET_PARAMS, off, rows, rps, vpr, t->m0, t->m1, t->m2);
+// Work items of the weight gradients: z ranges so that about 512 work-groups
+// (two per compute unit) have one each; at most WGRAD_ROWS work-groups, each
+// writing one partial row.
+WgTiles wgrad_tiles(const ope_net* t, uint32_t B, uint32_t& rows) {
+  WgTiles w;
+  w.m0 = t->m0;
+  w.m1 = t->m1;
+  w.m2 = t->m2;
+  w.ntx = (t->m0 + GX - 1) / GX;
+  w.nty = (t->m1 + GY - 1) / GY;
+  const uint64_t cols = (uint64_t)w.ntx * w.nty * B;
+  uint64_t nzc = (512 + cols - 1) / cols;
+  if (nzc > t->m2) nzc = t->m2;
+  w.ZC = (uint32_t)((t->m2 + nzc - 1) / nzc);
+  w.nzc = (t->m2 + w.ZC - 1) / w.ZC;
+  w.total = (uint32_t)(cols * w.nzc);
+  rows = (uint32_t)std::min<uint64_t>(w.total, WGRAD_ROWS);
+  return w;
+}
+
+hipError_t wgrad16(ope_net* t, const uint16_t* a, const uint16_t* g, uint32_t off, const WgTiles& w, uint32_t rows) {
+  hipLaunchKernelGGL(k_wgrad16, dim3(rows), dim3(256), 0, t->ctx->stream, a, g, t->part, (uint32_t)OPE_NET_PARAMS, off,
+                     w);
+  return hipGetLastError();
+}
+
+template <int C, int S>
+hipError_t wgrad_few(ope_net* t, const uint16_t* q, const uint16_t* p, uint32_t off, const WgTiles& w, uint32_t rows) {
+  hipLaunchKernelGGL((k_wgrad_few<C, S>), dim3(rows), dim3(256), 0, t->ctx->stream, q, p, t->part,
+                     (uint32_t)OPE_NET_PARAMS, off, w);
   return hipGetLastError();
 }
 
@@ -1047,23 +1262,19 @@ ope_status grad_pass(ope_net* t, const float* X, const float* v2, const float* T
                        t->coef, t->coef + t->max_batch, t->g4);
   }
   HIPCHK(hipGetLastError());
-  // voxel ranges of the weight-gradient partials
-  uint32_t rps = (uint32_t)std::max<int64_t>(1, std::min<int64_t>((int64_t)((n + 1023) / 1024), WGRAD_ROWS / B));
-  uint32_t vpr = (uint32_t)((n + rps - 1) / rps);
-  vpr = (vpr + 3) & ~3u;
-  rps = (uint32_t)((n + vpr - 1) / vpr);
-  const uint32_t rows = B * rps;
+  uint32_t rows = 0;                              // partial rows of the weight gradients
+  const WgTiles wt = wgrad_tiles(t, B, rows);
   // layer 4: g3 = conv^T(g4) masked by a3 > 0; dW4 from (a3, g4)
   HIPCHK((conv<1, 16, EPI_MASK>(t, t->g4, PK_B4, t->a3, t->g3, B)));
-  HIPCHK(wgrad<WGR_W4>(t, t->a3, t->g4, W4_OFF, B, rps, vpr));
+  HIPCHK((wgrad_few<1, -1>(t, t->g4, t->a3, W4_OFF, wt, rows)));
   // layer 3: dW3 from (a2, g3); g2 (into a3) = conv^T(g3) masked by a2
-  HIPCHK(wgrad<WGR_16>(t, t->a2, t->g3, W3_OFF, B, rps, vpr));
+  HIPCHK(wgrad16(t, t->a2, t->g3, W3_OFF, wt, rows));
   HIPCHK((conv<16, 16, EPI_MASK>(t, t->g3, PK_B3, t->a2, t->a3, B)));
   // layer 2: dW2 from (a1, g2); g1 (into g3) = conv^T(g2) masked by a1
-  HIPCHK(wgrad<WGR_16>(t, t->a1, t->a3, W2_OFF, B, rps, vpr));
+  HIPCHK(wgrad16(t, t->a1, t->a3, W2_OFF, wt, rows));
   HIPCHK((conv<16, 16, EPI_MASK>(t, t->a3, PK_B2, t->a1, t->g3, B)));
   // layer 1: dW1 from (x, g1)
-  HIPCHK(wgrad<WGR_W1>(t, t->x, t->g3, W1_OFF, B, rps, vpr));
+  HIPCHK((wgrad_few<2, 1>(t, t->x, t->g3, W1_OFF, wt, rows)));
   // fixed-order reduction of the partial rows
   const uint32_t rpg = (rows + WGRAD_GROUPS - 1) / WGRAD_GROUPS;
   const uint32_t groups = (rows + rpg - 1) / rpg;

@@ -182,6 +182,37 @@ def test_gradients_exact_on_integer_data():
         assert np.array_equal(got[L].astype(np.float64), grads[L]), L
 
 
+@pytest.mark.parametrize("m,B", [((33, 9, 3), 1), ((64, 8, 5), 1), ((31, 17, 2), 1), ((3, 2, 41), 1),
+                                 ((33, 9, 2), 1024)])
+def test_gradients_exact_across_the_weight_gradient_tiles(m, B):
+    """The integer case above on grids that cross the 32 x 8 voxel tiles of the
+    weight gradients in x and y and split z into ranges, and as a batch of 1024
+    equal samples (several tiles per work-group): every sum is exact in float32
+    (the batch's mean scales by a power of two), so any tiling gives the
+    oracle's gradient bit for bit."""
+    from paper_2511_06788_amd import ope
+    g = _grid(m)
+    p = W.Problem("net", g, np.zeros(g.n), 3, 1.0)
+    for seed in range(200):
+        X, v2, Ws = _integer_case(m, 300 + seed, 1, xr=(-1, 1), vr=(0, 0))
+        T = np.zeros_like(X)
+        T[tuple(np.argwhere(X == 1.0)[0])] = 2.0   # x . t = 2
+        grads, mags, fields = NN.storage_grad(np.stack([X, v2], axis=-1), T, v2, Ws, 1.0, 1.0, kind="energy")
+        if (all(_exact_in_bf16(np.maximum(fields[k], 0.0)) for k in ("z1", "z2", "z3"))
+                and all(_exact_in_bf16(fields[k]) for k in ("f", "g4_raw", "g3_raw", "g2_raw", "g1_raw"))
+                and all(B * np.max(mm) < 2 ** 24 for mm in mags) and all(np.count_nonzero(gr) > 0 for gr in grads)):
+            break
+    else:
+        raise AssertionError("no exact case found")
+    say(f"net gradients exact m={m} B={B}")
+    with _ctx(p) as ctx, ope.Net(ctx, B, ope.net_layers_to_weights(Ws)) as net:
+        ope.ope_net_set_loss(net.handle, ope.OPE_NET_LOSS_ENERGY)
+        _, grad = ope.ope_net_grad(net.handle, _dev32(np.tile(X.reshape(1, -1), (B, 1))), _dev32(v2.reshape(-1)),
+                                   _dev32(np.tile(T.reshape(1, -1), (B, 1))), B)
+    for L, got in enumerate(ope.net_weights_to_layers(grad)):
+        assert np.array_equal(got.astype(np.float64), grads[L]), L
+
+
 def _grad_case(m, B, seed):
     g = _grid(m)
     V = W.gaussian_wells(g, seed)
