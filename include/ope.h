@@ -234,7 +234,8 @@ ope_status ope_energy(ope_ctx* ctx, const void* U, double* energy);
 
 /* FP64 checks of an iterate (host outputs, each nullable):
  *   *residual = |H U - U Lam|_F / |Lam|_F with Lam = U^T H U,
- *   ritz[0..N) = eigenvalues of Lam, ascending (device Jacobi, FP64),
+ *   ritz[0..N) = eigenvalues of Lam, ascending (device tridiagonalisation and
+ *     bisection, FP64),
  *   *drift = |U^T U - I|_F.  Synchronises. */
 ope_status ope_residual(ope_ctx* ctx, const void* U, double* residual, double* ritz, double* drift);
 

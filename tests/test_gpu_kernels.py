@@ -228,6 +228,33 @@ def test_energy_residual_ritz_match_oracle():
     assert abs(drift - O.ortho_error(U)) <= 1e-14 * p.N
 
 
+@pytest.mark.parametrize("N", [1, 2, 3, 63, 64, 65, 127, 128, 129, 193, 256, 512])
+@pytest.mark.parametrize("start", ["random", "modes"])
+def test_ritz_values_at_the_edges_of_the_reduction(N, start):
+    """Ritz values of a random block and of exact sine modes (Lam diagonal up to
+    rounding, with the cube's repeated eigenvalues) at the widths where the
+    tridiagonalisation changes its layout or ends early.  A backward-stable
+    method is within a small multiple of N eps |Lam|, the Gram and the stencil
+    within that of n eps |H|: 1e-12 of the largest value covers both."""
+    from paper_2511_06788_amd import ope
+    m = 9
+    g = W.unit_box_grid((m, m, m))
+    if start == "modes":
+        i = np.arange(1, m + 1)
+        S = np.sqrt(2.0 / (m + 1)) * np.sin(np.pi * np.outer(i, i) / (m + 1))
+        U = np.ascontiguousarray(np.kron(S, np.kron(S, S))[:, :N])
+    else:
+        U = W.initial_block(g.n, N, N)
+    op = O.Operator(g.m, g.h, np.zeros(g.n))
+    Lam = U.T @ O.apply_H(op, U)
+    ref = np.linalg.eigvalsh(0.5 * (Lam + Lam.T))
+    say(f"ritz N={N} {start}")
+    with ope.Context(g, np.zeros(g.n), N) as ctx:
+        _, ritz, _ = ope.ope_residual(ctx.handle, to_dev(U), N)
+    assert np.all(np.diff(ritz) >= 0.0)
+    assert np.max(np.abs(ritz - ref)) <= 1e-12 * ref[-1]
+
+
 def test_autotune_single_context_keeps_results():
     """ope_autotune picks the fastest sweep shape by timing; H X and the CG
     solution then still match the oracle (a shape changes only the summation
