@@ -482,15 +482,15 @@ ope_status ope_batch_solve(ope_batch* batch, void* const* U, double tau, double 
                            ope_solve_info* info);
 /* shared = 1: Step 1's CG sweeps and column reductions of all
  * problems whose column sums fit one work-group (at most 128 columns and
- * 2^15 partial values) run as one launch per phase and class of problems
+ * 2^15 partial values), except those on grids of at most 16384 points (their
+ * CG is one launch each in any mode), run as one launch per phase and class of problems
  * (storage type, vector width, passes per plane, split x lines, line tiles)
  * on a batch stream, each launch's work-groups spread over (problem, tile)
  * work items of every problem's own sweep shape, each problem over all XCDs; same kernels and summation order as the per-problem launches,
  * so the results are identical.  shared = 0 (default): every problem's CG
  * runs on its own stream.  Measured: on the 64-problem workload (grid edges
- * 24..48, N 16..128) per-problem launches are 4-8% faster; on a batch of
- * small problems alone shared launches are faster (2.2x for sixteen 24^3,
- * N = 16 problems), on a batch of large ones slightly slower. */
+ * 24..48, N 16..128) per-problem launches are 4-8% faster, on a batch of large
+ * problems alone slightly faster. */
 ope_status ope_batch_set_shared(ope_batch* batch, int32_t shared);
 /* Graph-captured batched step: one HIP graph holding a whole step of every
  * problem (residual and warm start on the problems' streams, then exactly
@@ -533,7 +533,9 @@ ope_status ope_batch_autotune(ope_batch* batch, int32_t* tuned);
  * temporary n x N block (an FP32 one its own CG buffers). */
 ope_status ope_autotune(ope_ctx* ctx);
 
-/* Step 1's CG runs in chunks of 4 iterations between host convergence checks
+/* On grids of at most 16384 points the unpreconditioned CG is one launch (one
+ * work-group per column), with no host check and no graph; elsewhere
+ * Step 1's CG runs in chunks of 4 iterations between host convergence checks
  * (preconditioned: 1, or 2 with graphs on);
  * with graphs on each chunk is one replay of a HIP graph captured once per
  * context (on a private stream, replayed on the context's stream), with the
@@ -600,7 +602,9 @@ typedef struct {
 } ope_kernel_time;
 
 /* Start timing every launch of `kernel` on the context's stream with a pair of
- * HIP events (until ope_profile_end).  Adds two event records per launch. */
+ * HIP events (until ope_profile_end).  Adds two event records per launch.  While
+ * a kernel of the CG sweeps is timed, small grids run the sweeps too instead of
+ * their one-launch CG. */
 ope_status ope_profile_begin(ope_ctx* ctx, int32_t kernel);
 
 /* Stop timing; synchronises the stream and writes the totals to *out (host). */

@@ -455,33 +455,6 @@ __global__ void k_to_f64(const float* __restrict__ src, double* __restrict__ dst
 // N = 512 on 32^3 28 ms, where the Jacobi iteration alone took 1300 ms.
 // ---------------------------------------------------------------------------
 
-// The value of another lane of the same 16, by a DPP control.
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// The value held by lane `l` (uniform).
-__device__ __forceinline__ double lane_value(double v, uint32_t l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, (int)l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), (int)l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// Sum over a full wave in a fixed order, the result uniform: within 16 lanes by
-// DPP (lane ^ 1, lane ^ 2, mirrored halves and rows), then the four rows.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_move<0xB1>(v);
-  v += dpp_move<0x4E>(v);
-  v += dpp_move<0x141>(v);
-  v += dpp_move<0x140>(v);
-  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
-}
-
 // Householder vector of x (entries k + 1 .. N - 1): v = x with the entry k + 1
 // replaced by v0, beta = 2 / v^T v; e is the off-diagonal it leaves.  beta = 0
 // when x is already (x_{k+1}, 0, ..., 0).

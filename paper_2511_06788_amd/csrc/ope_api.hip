@@ -10,8 +10,9 @@
 //   S_b = <U,Y>, T = <Y,Y>                     (Grams)
 //   M, B, A, Z                                 (Steps 2-3, one work-group, FP64)
 //   U <- U Z_1 + Y Z_2 in place                (Step 4, predicated on the error flag)
-// The host only synchronises to poll CG convergence every few iterations and
-// to read the step's scalars at the end.
+// The host only synchronises to poll CG convergence every few iterations (a
+// small grid's CG is one launch and needs no poll) and to read the step's
+// scalars at the end.
 #include <stdlib.h>
 #include <string.h>
 
@@ -353,13 +354,35 @@ bool cg_all_done(const ope_ctx* c, int slot) {
   return true;
 }
 
+// The whole CG of a small grid and the copy of its column flags into host slot 0.
+hipError_t cg_cols(ope_ctx* c, int32_t max_iter) {
+  hipError_t e;
+  if ((e = launch_cg_cols(c, cg_y(c), max_iter)) != hipSuccess) return e;
+  c->cg_in_flight = 1;
+  return hipMemcpyAsync(c->hactive, c->active, sizeof(int32_t) * c->N, hipMemcpyDeviceToHost, c->stream);
+}
+
+// Whether the last CG converged in every column, once the stream has been
+// synchronised: run_cg's answer, or the flags that a small grid's CG left.
+bool cg_converged(const ope_ctx* c, bool all_done) { return c->cg_in_flight ? cg_all_done(c, 0) : all_done; }
+
 // CG iterations on H Y = U from the state prepared in rho/target/active, with
 // r in c->Rb[0]; returns the enqueued iteration count in *iters.  The next
 // chunk is enqueued before the flags of the previous one are read, so the GPU
 // does not wait for the host; a chunk enqueued after convergence finds every
 // column inactive and its kernels do nothing (the sweeps exit, the
 // reductions leave inactive columns at alpha = beta = 0).
+// On a small grid the whole CG is one launch (launch_cg_cols): nothing is
+// checked here, and *all_done stays open until the caller has synchronised the
+// stream (cg_converged).
 ope_status run_cg(ope_ctx* c, int32_t max_iter, int32_t* iters, bool* all_done) {
+  if (cg_cols_fits(c)) {
+    HIPCHK(cg_cols(c, max_iter));
+    *iters = 0;
+    *all_done = false;
+    return OPE_OK;
+  }
+  c->cg_in_flight = 0;
   int32_t it = 0;
   bool done = false;
   int slot_next = 0, head = 0, nout = 0;
@@ -561,7 +584,7 @@ ope_status run_step(ope_ctx* c, void* U, double tau, ope_step_info* info, double
   st = sync_and_read_scalars(c);
   if (st != OPE_OK) return st;
   ope_status out = (ope_status)c->hsc->err;
-  if (out == OPE_OK && !cg_done) out = OPE_ECG_MAXIT;
+  if (out == OPE_OK && !cg_converged(c, cg_done)) out = OPE_ECG_MAXIT;
   fill_info(c, info, c->hsc->cg_iters, out);
   return out;
 }
@@ -686,11 +709,11 @@ struct BatchState {
   std::vector<int32_t> it;
 };
 
-// A problem takes part in the shared launches when its column sums fit one
-// work-group's reduction (the same fixed-order sum its own steps use, so that
+// A problem takes part in the shared launches when its CG is not one launch
+// already (a small grid) and its column sums fit one work-group's reduction (the same fixed-order sum its own steps use, so that
 // its shared-launch iterates equal those of its own launches bit for bit); its
 // work items are the tiles of its own sweep shape.
-bool shared_fits(const ope_ctx* c) { return !c->mg_on && reduce_few_fits(c); }
+bool shared_fits(const ope_ctx* c) { return !c->mg_on && reduce_few_fits(c) && !cg_cols_fits(c); }
 
 // The shared CG launches of a set of problems: classes of problems that one
 // kernel instance can sweep (storage type, vector width, passes per plane,
@@ -909,7 +932,18 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
   // read, so the GPU does not drain while the host checks (a chunk enqueued
   // after convergence does nothing).
   std::vector<char> pending(go), shared(P, 0);
-  for (int i = 0; i < P; ++i) shared[i] = go[i] && b->shared && shared_fits(b->ctx[i]);
+  for (int i = 0; i < P; ++i) {
+    ope_ctx* c = b->ctx[i];
+    c->cg_in_flight = 0;
+    shared[i] = go[i] && b->shared && shared_fits(c);
+    if (go[i] && cg_cols_fits(c)) {      // a small grid: the whole CG in one launch, its flags read at the end
+      pending[i] = 0;
+      if (cg_cols(c, c->max_iter) != hipSuccess) {
+        bs.st[i] = OPE_EHIP;
+        go[i] = 0;
+      }
+    }
+  }
   std::vector<int> head(P, 0), nout(P, 0), slot_next(P, 0), q0(P, 0), q1(P, 0);
   int32_t it_shared = 0;
   for (;;) {
@@ -990,7 +1024,7 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
     if (go[i]) {
       HIPCHK(hipStreamSynchronize(c->stream));
       ope_status out = (ope_status)c->hsc->err;
-      if (out == OPE_OK && !bs.cgdone[i]) out = OPE_ECG_MAXIT;
+      if (out == OPE_OK && !cg_converged(c, bs.cgdone[i] != 0)) out = OPE_ECG_MAXIT;
       fill_info(c, &bs.info[i], c->hsc->cg_iters, out);
       bs.st[i] = out;
     }
@@ -1379,7 +1413,7 @@ ope_status ope_source_solve(ope_ctx* c, const double* U, double* Y, const double
   if (st != OPE_OK) return st;
   if (iterations) *iterations = c->hsc->cg_iters;
   if (c->hsc->err != 0) return (ope_status)c->hsc->err;
-  if (!done) {
+  if (!cg_converged(c, done)) {
     // the last chunk may have converged exactly at the cap
     HIPCHK(hipMemcpy(c->hactive, c->active, sizeof(int32_t) * N, hipMemcpyDeviceToHost));
     int cnt = 0;
@@ -2099,8 +2133,12 @@ ope_status ope_batch_capture(ope_batch* b, void* const* U, double tau, int32_t c
         continue;
       }
       // own launches, the whole step on the problem's stream
-      for (int32_t it = 0; it < cg_iterations; ++it) HIPCHK(cg_iteration(c, it));
-      HIPCHK(cg_flush(c, cg_iterations, c->stream));
+      if (cg_cols_fits(c)) {
+        HIPCHK(launch_cg_cols(c, cg_y(c), cg_iterations));
+      } else {
+        for (int32_t it = 0; it < cg_iterations; ++it) HIPCHK(cg_iteration(c, it));
+        HIPCHK(cg_flush(c, cg_iterations, c->stream));
+      }
       HIPCHK(hipMemcpyAsync(b->h_gflags + b->gflag_off[i], c->active, sizeof(int32_t) * c->N,
                             hipMemcpyDeviceToHost, c->stream));
       if ((st = finish(i)) != OPE_OK) return st;

@@ -139,6 +139,7 @@ struct ope_ctx {
   OpeScalars* sc;               // device
   OpeScalars* hsc;              // pinned host mirror
   int32_t* hactive;             // pinned host mirrors of active[] (two slots of N)
+  int32_t cg_in_flight;         // the last CG ran without a host check: slot 0 holds its flags after a synchronisation
   hipEvent_t chunk_ev[2];       // marks each slot's copy
   double* hbuf;                 // pinned host scratch (N doubles)
   // policy
@@ -254,6 +255,10 @@ hipError_t launch_y_flush(ope_ctx* c, hipStream_t s, void* y, const void* p, con
 // y += x over an n x N FP64 block
 hipError_t launch_add_block(ope_ctx* c, double* y, const double* x);
 hipError_t launch_cg_setup_reduce(ope_ctx* c, int mode);
+// small grids (k_cgcols.hip): the whole CG, one work-group per column, from the
+// state in rho/target/active and r in Rb[0]; y is updated in place
+bool cg_cols_fits(const ope_ctx* c);
+hipError_t launch_cg_cols(ope_ctx* c, void* y, int32_t max_iter);
 
 // multigrid preconditioner (k_mg.hip)
 ope_status mg_build(ope_ctx* c);          // the hierarchy for the context's operator and N
@@ -388,5 +393,32 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t G) {
   uint32_t q = G >> 3, r = G & 7u;
   uint32_t x = b & 7u, k = b >> 3;
   return x * q + (x < r ? x : r) + k;
+}
+
+// The value of another lane of the same 16, by a DPP control.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// The value held by lane `l` (uniform).
+__device__ __forceinline__ double lane_value(double v, uint32_t l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, (int)l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), (int)l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Sum over a full wave in a fixed order, the result uniform: within 16 lanes by
+// DPP (lane ^ 1, lane ^ 2, mirrored halves and rows), then the four rows.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<0xB1>(v);
+  v += dpp_move<0x4E>(v);
+  v += dpp_move<0x141>(v);
+  v += dpp_move<0x140>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 #endif

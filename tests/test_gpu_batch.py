@@ -163,3 +163,11 @@ def test_batched_workload_step_matches_oracle():
         assert np.max(np.abs(got[i] - p.U0)) > 1e-5, i
         assert abs(info[i].energy - O.energy(op, p.U0)) <= 1e-12 * abs(info[i].energy), i
         assert abs(info[i].residual - O.residual(op, p.U0)) <= 1e-10 * info[i].residual, i
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_shared_launches_of_several_problems_past_the_one_launch_grids(prec, monkeypatch):
+    """Grids of more than 16384 points, which the shared launches still take."""
+    probs = [W.wells_3d(m=26, N=5, seed=1), W.wells_3d(m=27, N=16, seed=2), W.harmonic_2d_32(m=130)]
+    monkeypatch.setattr("tests.test_gpu_batch._ragged", lambda: probs)
+    test_batch_steps_equal_single_steps(prec, True)

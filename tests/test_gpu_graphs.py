@@ -40,3 +40,9 @@ def test_graph_chunks_equal_eager(prec, mk, tau, steps):
     assert ig == ie
     assert sg == se
     assert sum(i[3] for i in ig) > 4 * steps      # the chunks did run
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_graph_chunks_equal_eager_past_the_one_launch_grids(prec):
+    """The same on a grid of more than 16384 points, whose CG runs in chunks."""
+    test_graph_chunks_equal_eager(prec, lambda: W.wells_3d(m=26, N=12, seed=4), 30.0, 6)

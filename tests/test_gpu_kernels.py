@@ -335,3 +335,28 @@ def test_wide_row_chunks_agree(N, narrow):
         S = to_host(Sd)
     assert np.max(np.abs(Y - O.apply_H(op, X))) <= stencil_bound(op, X)
     assert np.all(np.linalg.norm(U - O.apply_H(op, S), axis=0) <= 20 * 1e-11)
+
+
+@pytest.mark.parametrize("m", [(5, 3), (32, 32), (33, 32), (1, 64, 64), (9, 7, 5), (64, 128), (91, 90), (127, 129),
+                               (25, 25, 26), (128, 128), (41, 20, 20)])
+@pytest.mark.parametrize("N,k", [(1, 3), (5, 7), (16, 2)])
+def test_small_grid_cg_equals_textbook_cg(m, N, k):
+    """The one-launch CG of small grids (up to 16384 points: every points-per-
+    thread variant, their edges, grids one node thick) and the first grid past
+    it, capped after k iterations, against the oracle's textbook iterate."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    rng = np.random.default_rng(len(m) * 1000 + N)
+    V = rng.uniform(0.0, 50.0, g.n)
+    op = O.Operator(g.m, g.h, V)
+    N = min(N, g.n)
+    U, Y0 = rng.standard_normal((g.n, N)), 1e-3 * rng.standard_normal((g.n, N))
+    say(f"small-grid CG m={m} N={N} k={k}")
+    with ope.Context(g, V, N) as ctx:
+        Yd = empty_dev(g.n, N)
+        its = ope.ope_source_solve(ctx.handle, to_dev(U), Yd, to_dev(Y0), 1e-14, k, allow_maxit=True)
+        Y = to_host(Yd)
+    st = {}
+    Y_ref = O.cg_source(op, U, Y0, tol=1e-14, max_iter=k, stats=st)
+    assert its == st["iterations"]
+    assert np.max(np.abs(Y - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
