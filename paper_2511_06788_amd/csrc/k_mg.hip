@@ -15,10 +15,11 @@
 // (omega = 0.8) once on each side of the coarse correction:
 //   x0 = omega b / d;  r1 = b - H x0;  e = B_{k+1}(R r1);  x1 = x0 + P e;
 //   z = x1 + omega (b - H x1) / d.
-// Kernels, per level: k_mg_tstencil<0> (r1, one stencil over x0 formed on the
-// fly from b), k_mg_zrestrict (R r1), k_mg_dense (coarsest), k_mg_zprolong
-// (x1 = x0 + P e), k_mg_tstencil<1> (z, one stencil over x1; on level 0 also
-// the per-column partial sums of r^T z and r^T r that the PCG needs).  The
+// Kernels, per level: k_mg_tstencil (r1, one stencil over x0 formed on the
+// fly from b), k_mg_zrestrict (R r1), k_mg_tpost (x1 = x0 + P e and z, one
+// stencil over x1; on level 0 also the per-column partial sums of r^T z and
+// r^T r that the PCG needs); from the first level of at most 4096 nodes down,
+// all levels in one launch (k_mg_coarse).  The
 // stencil and transfer kernels march along z (see zmarch_shape, tshape); the
 // smoother's factors omega / d are precomputed per level.
 // Layout: every block is n x N row-major (a grid point's N values
@@ -98,65 +99,247 @@ __device__ __forceinline__ void jac0(const T* __restrict__ b, const double* __re
 // zero; an axis that is not coarsened has the one tap I with weight 1.  The
 // fixed count lets every load of a gather be issued before the first is used.
 __device__ __forceinline__ void restrict_taps(uint32_t I, uint32_t mf, uint32_t (&f)[4], double (&w)[4]) {
-  if (mf == 1) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      f[t] = I;
-      w[t] = t == 1 ? 1.0 : 0.0;
-    }
-    return;
-  }
-  const double cw[4] = {0.125, 0.375, 0.375, 0.125};
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int64_t c = 2 * (int64_t)I - 1 + t;
-    const bool in = c >= 0 && c < (int64_t)mf;
-    f[t] = in ? (uint32_t)c : (uint32_t)(2 * I);
-    w[t] = in ? cw[t] : 0.0;
-  }
+  const bool one = mf == 1;                       // uniform: selects, no branch
+  const uint32_t c = one ? I : 2 * I;
+  f[0] = I > 0 ? c - 1 : c;
+  f[1] = c;
+  f[2] = c + 1 < mf ? c + 1 : c;
+  f[3] = c + 2 < mf ? c + 2 : c;
+  w[0] = I > 0 ? 0.125 : 0.0;
+  w[1] = one ? 1.0 : 0.375;
+  w[2] = c + 1 < mf ? 0.375 : 0.0;
+  w[3] = c + 2 < mf ? 0.125 : 0.0;
 }
 
-// coarsest level: E = A^{-1} B with the dense inverse (row-major nc x nc)
-template <typename T, int VW>
-__global__ __launch_bounds__(MG_WG) void k_mg_dense(const double* __restrict__ Ainv, const T* __restrict__ B,
-                                                   T* __restrict__ E, uint32_t nc,
-                                                   const int32_t* __restrict__ active, uint32_t N, uint32_t NV,
-                                                   uint64_t total) {
-  const uint64_t e = (uint64_t)blockIdx.x * MG_WG + threadIdx.x;
-  if (e >= total) return;
-  const uint32_t v = (uint32_t)(e % NV);
-  const uint32_t i = (uint32_t)(e / NV);
-  if (!vec_active<VW>(active, v)) return;
-  T acc[VW];
+// Coarse nodes and weights of fine node f along one axis: always two taps,
+// the parent f / 2 with 3/4 and the other neighbour (f / 2 - 1 for even f,
+// f / 2 + 1 for odd f) with 1/4, or weight zero (clamped to the parent) when
+// it is missing; an axis that is not coarsened has the tap f with weight 1.
+__device__ __forceinline__ void prolong_taps(uint32_t f, uint32_t mf, uint32_t mc, uint32_t (&I)[2], double (&w)[2]) {
+  const bool one = mf == 1;                       // uniform: selects, no branch
+  const uint32_t h = f / 2;                       // (0 on an axis that is not coarsened)
+  const bool odd = (f & 1u) != 0;
+  const bool in = odd ? h + 1 < mc : h > 0;
+  I[0] = h;
+  I[1] = in ? (odd ? h + 1 : h - 1) : h;
+  w[0] = one ? 1.0 : 0.75;
+  w[1] = in ? 0.25 : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// The coarse end of a V-cycle in one launch.  From the first level of at most
+// MC_MAX nodes down, one work-group takes one column through every level: the
+// field being smoothed and each level's right-hand side and correction stay in
+// LDS, the coarsest level is a product with the dense inverse.  The levels'
+// own launches (three per level) move next to nothing and cost a launch's 4-5 us
+// each, one after the other: at 64^3, N = 17, the four launches from the 8^3
+// level down took 23 us, this one 7.5 us (8.3 at N = 128).  Bound by the
+// instructions of one compute unit per column (about 2000 per thread with two
+// levels), which is why the line is not drawn higher: with the 16^3 level in it,
+// it took 27 us, against 16 us for that level's three launches.
+// ---------------------------------------------------------------------------
+constexpr uint32_t MC_MAX = 2048;                 // nodes of the first fused level
+constexpr uint32_t MC_WG = 512;
+constexpr uint32_t MC_PPT = MC_MAX / MC_WG;       // nodes per thread
+constexpr int MC_LEVELS = 8;                      // levels fused (at most)
+constexpr size_t MC_LDS = 131072;                 // LDS bytes of the fused levels (at most)
+
+struct McLevel {
+  uint32_t m0, m1, m2, n;
+  uint32_t mag0, mag1;                            // ceil(2^32 / m) of m0 and m1 (0 for m = 1), for divisions of i < 2^16
+  uint32_t b, e, wd, dg;                          // LDS offsets below the first level: right-hand side, correction,
+                                                  // omega / diagonal, diagonal
+  double cx, cy, cz;
+};
+struct McArgs {
+  int32_t nl;                                     // levels, the last one solved with inv
+  uint32_t cst, ncst;                             // LDS offset and length of the lower levels' constants
+  const double *diag0, *wd0;                      // the first level's diagonal and omega / diagonal
+  const double* cdat;                             // the lower levels' (the order of the LDS offsets)
+  const double* inv;
+  McLevel lv[MC_LEVELS];
+};
+
+struct McNode {
+  uint32_t x, y, z;
+};
+__device__ __forceinline__ McNode mc_node(const McLevel& L, uint32_t i) {
+  McNode q;
+  const uint32_t r = L.mag0 ? __umulhi(i, L.mag0) : i;
+  q.x = i - r * L.m0;
+  q.z = L.mag1 ? __umulhi(r, L.mag1) : r;
+  q.y = r - q.z * L.m1;
+  return q;
+}
+
+// (H f)_i for the level's field f in LDS, d its diagonal there; f[n] is the zero
+// that stands for every neighbour outside the grid
+template <typename T>
+__device__ __forceinline__ T mc_apply(const McLevel& L, const T* f, uint32_t i, T d) {
+  const McNode q = mc_node(L, i);
+  const uint32_t s1 = L.m0, s2 = L.m0 * L.m1;
+  const T xs = f[q.x > 0 ? i - 1 : L.n] + f[q.x + 1 < L.m0 ? i + 1 : L.n];
+  const T ys = f[q.y > 0 ? i - s1 : L.n] + f[q.y + 1 < L.m1 ? i + s1 : L.n];
+  const T zs = f[q.z > 0 ? i - s2 : L.n] + f[q.z + 1 < L.m2 ? i + s2 : L.n];
+  return d * f[i] - ((T)L.cx * xs + (T)L.cy * ys + (T)L.cz * zs);
+}
+
+// (R f)_i of the finer level L's field f at node i of the coarser level C
+template <typename T>
+__device__ __forceinline__ T mc_restrict(const McLevel& L, const McLevel& C, const T* f, uint32_t i) {
+  const McNode q = mc_node(C, i);
+  uint32_t fx[4], fy[4], fz[4];
+  double wx[4], wy[4], wz[4];
+  restrict_taps(q.x, L.m0, fx, wx);
+  restrict_taps(q.y, L.m1, fy, wy);
+  restrict_taps(q.z, L.m2, fz, wz);
+  T o = T(0);
 #pragma unroll
-  for (int k = 0; k < VW; ++k) acc[k] = 0.0;
-  const double* a = Ainv + (uint64_t)i * nc;
-  // four running sums over j = 4 u + s (their loads are issued together), added in order
-  T part[4][VW];
+  for (int cc = 0; cc < 4; ++cc) {
+    T az = T(0);
 #pragma unroll
-  for (int s = 0; s < 4; ++s) zero(part[s]);
-  uint32_t j = 0;
-  for (; j + 4 <= nc; j += 4) {
-    T t[4][VW];
+    for (int bb = 0; bb < 4; ++bb) {
+      const T* row = f + (fz[cc] * L.m1 + fy[bb]) * L.m0;
+      T ax = T(0);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) ldr<T, VW>(B, j + s, N, v, t[s]);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const T w = (T)a[j + s];
-#pragma unroll
-      for (int k = 0; k < VW; ++k) part[s][k] += w * t[s][k];
+      for (int aa = 0; aa < 4; ++aa) ax += (T)wx[aa] * row[fx[aa]];
+      az += (T)wy[bb] * ax;
     }
+    o += (T)wz[cc] * az;
   }
-  for (; j < nc; ++j) {
-    T t[VW];
-    ldr<T, VW>(B, j, N, v, t);
-    const T w = (T)a[j];
+  return o;
+}
+
+// (P e)_i at node i of the finer level L from the coarser level C's e
+template <typename T>
+__device__ __forceinline__ T mc_prolong(const McLevel& L, const McLevel& C, const T* e, uint32_t i) {
+  const McNode q = mc_node(L, i);
+  uint32_t Ix[2], Iy[2], Iz[2];
+  double wx[2], wy[2], wz[2];
+  prolong_taps(q.x, L.m0, C.m0, Ix, wx);
+  prolong_taps(q.y, L.m1, C.m1, Iy, wy);
+  prolong_taps(q.z, L.m2, C.m2, Iz, wz);
+  T o = T(0);
 #pragma unroll
-    for (int k = 0; k < VW; ++k) part[0][k] += w * t[k];
+  for (int cc = 0; cc < 2; ++cc) {
+    T az = T(0);
+#pragma unroll
+    for (int bb = 0; bb < 2; ++bb) {
+      const T* row = e + (Iz[cc] * C.m1 + Iy[bb]) * C.m0;
+      az += (T)wy[bb] * ((T)wx[0] * row[Ix[0]] + (T)wx[1] * row[Ix[1]]);
+    }
+    o += (T)wz[cc] * az;
   }
+  return o;
+}
+
+// Every global load is issued before the first phase (the first level's values
+// and the inverse's rows into registers, the lower levels' constants into LDS):
+// a load inside a phase would put an L2 latency between two barriers.
+template <typename T>
+__global__ __launch_bounds__(MC_WG, 4) void k_mg_coarse(const T* __restrict__ B, T* __restrict__ E, McArgs a,
+                                                     const int32_t* __restrict__ active, uint32_t N) {
+  extern __shared__ __align__(16) char mc_lds[];
+  T* const s = reinterpret_cast<T*>(mc_lds);
+  T* const f = s;                                 // the field: n values of the level at hand and the zero
+  const uint32_t t = threadIdx.x;
+  const uint32_t col = xcd_remap(blockIdx.x, gridDim.x);
+  if (active && active[col] == 0) return;         // uniform over the work-group
+  const McLevel& L0 = a.lv[0];
+  const McLevel& LC = a.lv[a.nl - 1];
+  T b0[MC_PPT], w0[MC_PPT], d0[MC_PPT], iv[8];    // iv: entries p + 8 u of row t / 8 of the inverse
 #pragma unroll
-  for (int k = 0; k < VW; ++k) acc[k] = (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
-  str<T, VW>(E, i, N, v, acc);
+  for (uint32_t u = 0; u < MC_PPT; ++u) b0[u] = B[(uint64_t)min(t + u * MC_WG, L0.n - 1) * N + col];
+#pragma unroll
+  for (uint32_t u = 0; u < MC_PPT; ++u) {
+    const uint32_t i = min(t + u * MC_WG, L0.n - 1);
+    w0[u] = (T)a.wd0[i];
+    d0[u] = (T)a.diag0[i];
+  }
+  const uint32_t ri = t / 8u, rp = t % 8u;
+#pragma unroll
+  for (uint32_t u = 0; u < 8; ++u)
+    iv[u] = (ri < LC.n && rp + 8 * u < LC.n) ? (T)a.inv[ri * LC.n + rp + 8 * u] : T(0);
+  for (uint32_t i = t; i < a.ncst; i += MC_WG) s[a.cst + i] = (T)a.cdat[i];
+  if (a.nl == 1) {
+    // the coarsest level alone
+#pragma unroll
+    for (uint32_t u = 0; u < MC_PPT; ++u)
+      if (t + u * MC_WG < L0.n) f[t + u * MC_WG] = b0[u];
+  } else {
+    // first level, down
+#pragma unroll
+    for (uint32_t u = 0; u < MC_PPT; ++u)
+      if (t + u * MC_WG < L0.n) f[t + u * MC_WG] = w0[u] * b0[u];
+    if (t == 0) f[L0.n] = T(0);
+    __syncthreads();
+    T r[MC_PPT];                                  // r1 = b - H x0 replaces x0 once every thread has read it
+#pragma unroll
+    for (uint32_t u = 0; u < MC_PPT; ++u) {
+      const uint32_t i = t + u * MC_WG;
+      r[u] = i < L0.n ? b0[u] - mc_apply(L0, f, i, d0[u]) : T(0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < MC_PPT; ++u)
+      if (t + u * MC_WG < L0.n) f[t + u * MC_WG] = r[u];
+    __syncthreads();
+    for (uint32_t i = t; i < a.lv[1].n; i += MC_WG) s[a.lv[1].b + i] = mc_restrict(L0, a.lv[1], f, i);
+  }
+  __syncthreads();
+  for (int k = 1; k + 1 < a.nl; ++k) {            // the lower levels, down
+    const McLevel& L = a.lv[k];
+    const McLevel& C = a.lv[k + 1];
+    const T *b = s + L.b, *wd = s + L.wd, *dg = s + L.dg;
+    T* e = s + L.e;                               // r1 until the correction takes its place
+    for (uint32_t i = t; i < L.n; i += MC_WG) f[i] = wd[i] * b[i];
+    if (t == 0) f[L.n] = T(0);
+    __syncthreads();
+    for (uint32_t i = t; i < L.n; i += MC_WG) e[i] = b[i] - mc_apply(L, f, i, dg[i]);
+    __syncthreads();
+    for (uint32_t i = t; i < C.n; i += MC_WG) s[C.b + i] = mc_restrict(L, C, e, i);
+    __syncthreads();
+  }
+  {
+    // e = A^{-1} b on the coarsest level: eight threads to a row
+    const T* b = a.nl == 1 ? f : s + LC.b;
+    T v = T(0);
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u)
+      if (rp + 8 * u < LC.n) v += iv[u] * b[rp + 8 * u];
+    v += __shfl_xor(v, 1);
+    v += __shfl_xor(v, 2);
+    v += __shfl_xor(v, 4);
+    if (ri < LC.n && rp == 0) {
+      if (a.nl == 1) E[(uint64_t)ri * N + col] = v;
+      else s[LC.e + ri] = v;
+    }
+    if (a.nl == 1) return;
+    __syncthreads();
+  }
+  for (int k = a.nl - 2; k >= 1; --k) {           // the lower levels, up
+    const McLevel& L = a.lv[k];
+    const McLevel& C = a.lv[k + 1];
+    const T *b = s + L.b, *wd = s + L.wd, *dg = s + L.dg;
+    for (uint32_t i = t; i < L.n; i += MC_WG) f[i] = wd[i] * b[i] + mc_prolong(L, C, s + C.e, i);
+    if (t == 0) f[L.n] = T(0);
+    __syncthreads();
+    for (uint32_t i = t; i < L.n; i += MC_WG) s[L.e + i] = f[i] + wd[i] * (b[i] - mc_apply(L, f, i, dg[i]));
+    __syncthreads();
+  }
+  // first level, up
+#pragma unroll
+  for (uint32_t u = 0; u < MC_PPT; ++u) {
+    const uint32_t i = t + u * MC_WG;
+    if (i < L0.n) f[i] = w0[u] * b0[u] + mc_prolong(L0, a.lv[1], s + a.lv[1].e, i);
+  }
+  if (t == 0) f[L0.n] = T(0);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t u = 0; u < MC_PPT; ++u) {
+    const uint32_t i = t + u * MC_WG;
+    if (i < L0.n) E[(uint64_t)i * N + col] = f[i] + w0[u] * (b0[u] - mc_apply(L0, f, i, d0[u]));
+  }
 }
 
 // z-march decomposition of a level: a work-group owns PL = 256 / NV
@@ -432,26 +615,6 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
     dc = d2;
   }
 }
-
-// Coarse nodes and weights of fine node f along one axis: always two taps,
-// the parent f / 2 with 3/4 and the other neighbour (f / 2 - 1 for even f,
-// f / 2 + 1 for odd f) with 1/4, or weight zero (clamped to the parent) when
-// it is missing; an axis that is not coarsened has the tap f with weight 1.
-__device__ __forceinline__ void prolong_taps(uint32_t f, uint32_t mf, uint32_t mc, uint32_t (&I)[2], double (&w)[2]) {
-  if (mf == 1) {
-    I[0] = I[1] = f;
-    w[0] = 1.0;
-    w[1] = 0.0;
-    return;
-  }
-  I[0] = f / 2;
-  w[0] = 0.75;
-  const int64_t J = (f % 2 == 0) ? (int64_t)(f / 2) - 1 : (int64_t)(f / 2) + 1;
-  const bool in = J >= 0 && J < (int64_t)mc;
-  I[1] = in ? (uint32_t)J : f / 2;
-  w[1] = in ? 0.25 : 0.0;
-}
-
 
 // Coarse x-y interpolation of coarse plane K at a fine column (fixed taps).
 template <typename T, int VW>
@@ -752,41 +915,109 @@ __global__ __launch_bounds__(MG_WG) void k_mg_zrestrict(const T* __restrict__ R1
   }
 }
 
-// PCG start: rho = r^T z (the CG set-up has already set the targets and the
-// convergence flags from |r|^2).
-__global__ __launch_bounds__(MG_WG) void k_pcg_start(const double* __restrict__ dots, uint32_t N,
-                                                    double* __restrict__ rho) {
-  for (uint32_t j = threadIdx.x; j < N; j += MG_WG) rho[j] = dots[j];
-}
+// The PCG's scalars from the partial rows of r^T z and r^T r, in one
+// work-group: column sums in a fixed order (thread t: column t % 2N, rows
+// t / 2N, t / 2N + G, ...; 8 running sums, then the G groups in order), then
+//   START: rho = r^T z (the CG set-up has already set the targets and the
+//          convergence flags from |r|^2);
+//   else:  for a running column beta = r^T z / rho, rho = r^T z, and it keeps
+//          running while |r|^2 > target (a non-positive r^T z, which an SPD
+//          preconditioner cannot give, stops it); flags (nullable, pinned host
+//          memory) receives a copy of the flags.
+// One launch instead of three (two reduction stages and the scalars): the rows
+// are few (a tile's slices share one), 2 us of reads even at 2N = 1024.
+constexpr uint32_t PS_WG = 1024;
 
-// PCG after the preconditioning of the new residual: for a running column,
-// beta = r^T z / rho, rho = r^T z, and it keeps running while |r|^2 > target
-// (a non-positive r^T z, which an SPD preconditioner cannot give, stops it).
-__global__ __launch_bounds__(MG_WG) void k_pcg_beta(const double* __restrict__ dots, uint32_t N,
-                                                   double* __restrict__ rho, double* __restrict__ beta,
-                                                   const double* __restrict__ target, int32_t* __restrict__ active,
-                                                   OpeScalars* __restrict__ sc) {
-  for (uint32_t j = threadIdx.x; j < N; j += MG_WG) {
-    if (!active[j]) {
-      beta[j] = 0.0;
-      continue;
+template <bool START>
+__global__ __launch_bounds__(PS_WG) void k_pcg_scalars(const double* __restrict__ part, uint32_t nrows, uint32_t N,
+                                                      double* __restrict__ rho, double* __restrict__ beta,
+                                                      const double* __restrict__ target,
+                                                      int32_t* __restrict__ active, OpeScalars* __restrict__ sc,
+                                                      int32_t* __restrict__ flags) {
+  __shared__ double red[PS_WG], dots[PS_WG];
+  const uint32_t nc = 2 * N, G = PS_WG / nc;                   // 2N <= 1024 (N <= 512)
+  const uint32_t col = threadIdx.x % nc, gi = threadIdx.x / nc;
+  double a = 0.0;
+  if (gi < G) {
+    double q[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    uint32_t w = gi;
+    for (; w + 7 * G < nrows; w += 8 * G) {
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u) q[u] += part[(uint64_t)(w + u * G) * nc + col];
     }
-    const double rz = dots[j], rr = dots[N + j];
+    for (; w < nrows; w += G) q[0] += part[(uint64_t)w * nc + col];
+    a = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+  }
+  red[threadIdx.x] = a;
+  __syncthreads();
+  if (gi == 0) {
+    double t = 0.0;
+    for (uint32_t k = 0; k < G; ++k) t += red[k * nc + col];
+    dots[col] = t;
+  }
+  __syncthreads();
+  const uint32_t j = threadIdx.x;
+  if (j >= N) return;
+  const double rz = dots[j], rr = dots[N + j];
+  if (START) {
+    rho[j] = rz;
+    return;
+  }
+  int32_t act = 0;
+  double b = 0.0;
+  if (active[j]) {
     if (!isfinite(rz) || !isfinite(rr)) {
       if (sc->err == 0) sc->err = OPE_ENONFINITE;
-      active[j] = 0;
-      beta[j] = 0.0;
-      continue;
+    } else {
+      b = rz / rho[j];
+      rho[j] = rz;
+      act = (rr > target[j] && rz > 0.0) ? 1 : 0;
     }
-    beta[j] = rz / rho[j];
-    rho[j] = rz;
-    active[j] = (rr > target[j] && rz > 0.0) ? 1 : 0;
   }
+  beta[j] = b;
+  active[j] = act;
+  if (flags) flags[j] = act;
+}
+
+// The fused levels' geometry and LDS layout: the field of the first (and its
+// zero), the lower levels' constants (omega / diagonal and diagonal, level by
+// level, as mg_build lays them out in mg_cdat), then each lower level's
+// right-hand side and correction.  *values: the LDS needed.
+McArgs coarse_args(const MgLevel* lv, int nl, int k0, size_t* values) {
+  McArgs a{};
+  a.nl = nl - k0;
+  auto magic = [](uint32_t m) -> uint32_t { return m > 1 ? (uint32_t)((((uint64_t)1 << 32) + m - 1) / m) : 0u; };
+  uint32_t off = (uint32_t)lv[k0].n + 1;
+  a.cst = off;
+  for (int k = 0; k < a.nl; ++k) {
+    const MgLevel& g = lv[k0 + k];
+    McLevel& L = a.lv[k];
+    L.m0 = g.m0;
+    L.m1 = g.m1;
+    L.m2 = g.m2;
+    L.n = (uint32_t)g.n;
+    L.mag0 = magic(g.m0);
+    L.mag1 = magic(g.m1);
+    L.cx = g.cx;
+    L.cy = g.cy;
+    L.cz = g.cz;
+    if (k == 0) continue;
+    L.wd = off;
+    L.dg = off + L.n;
+    off += 2 * L.n;
+  }
+  a.ncst = off - a.cst;
+  for (int k = 1; k < a.nl; ++k) {
+    McLevel& L = a.lv[k];
+    L.b = off;
+    L.e = off + L.n;
+    off += 2 * L.n;
+  }
+  *values = off;
+  return a;
 }
 
 inline MgGeom geom(const MgLevel& L) { return MgGeom{L.m0, L.m1, L.m2, L.cx, L.cy, L.cz}; }
-
-inline uint32_t grid_of(uint64_t total) { return (uint32_t)((total + MG_WG - 1) / MG_WG); }
 
 // Storage type of the blocks (the context's: FP64, or FP32 for OPE_MIXED) and
 // elements per thread (16 bytes when N allows).
@@ -841,15 +1072,16 @@ void mg_free(ope_ctx* c) {
   }
   if (c->mg_mem) (void)hipFree(c->mg_mem);
   if (c->mg_inv) (void)hipFree(c->mg_inv);
+  if (c->mg_cdat) (void)hipFree(c->mg_cdat);
   if (c->mg_part) (void)hipFree(c->mg_part);
-  if (c->mg_dots) (void)hipFree(c->mg_dots);
   c->mg_mem = nullptr;
   c->mg_inv = nullptr;
+  c->mg_cdat = nullptr;
   c->mg_part = nullptr;
-  c->mg_dots = nullptr;
   c->mg_Z = nullptr;
   for (int k = 0; k < OPE_MG_MAX_LEVELS; ++k) c->mg[k] = MgLevel{};
   c->mg_levels = 0;
+  c->mg_k0 = 0;
   c->mg_on = 0;
 }
 
@@ -933,8 +1165,22 @@ ope_status mg_build(ope_ctx* c) {
       }
   if (!spd_inverse(A, nc)) return OPE_ENOTSPD;
   // device memory: level diagonals, blocks (level 0: T and Z; others: B, E, T)
+  // (levels 1 .. k0 - 1: B, E and T; level k0: B and E; the fused levels below
+  // it live in LDS)
+  int k0 = nl - 1;                                // first fused level
+  while (k0 > 1 && lv[k0 - 1].n <= MC_MAX && nl - (k0 - 1) <= MC_LEVELS) {
+    size_t values = 0;
+    (void)coarse_args(lv, nl, k0 - 1, &values);
+    if (values * sizeof(double) > MC_LDS) break;  // levels that shrink along one axis only
+    --k0;
+  }
+  std::vector<double> cdat;                       // constants of the levels below k0
+  for (int k = k0 + 1; k < nl; ++k) {
+    for (const double d : diags[(size_t)k]) cdat.push_back(MG_OMEGA / d);
+    cdat.insert(cdat.end(), diags[(size_t)k].begin(), diags[(size_t)k].end());
+  }
   int64_t elems = 2 * c->n * N;
-  for (int k = 1; k < nl; ++k) elems += 3 * lv[k].n * N;
+  for (int k = 1; k <= k0; ++k) elems += (k < k0 ? 3 : 2) * lv[k].n * N;
   const uint32_t esz = mg_esz(c);
   {
     const uint32_t NV = (uint32_t)N / mg_vw(c);
@@ -943,8 +1189,8 @@ ope_status mg_build(ope_ctx* c) {
   }
   bool ok = hipMalloc(&c->mg_mem, (size_t)esz * (size_t)elems) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->mg_inv, sizeof(double) * (size_t)nc * nc) == hipSuccess;
+  ok = ok && hipMalloc((void**)&c->mg_cdat, sizeof(double) * std::max<size_t>(cdat.size(), 1)) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->mg_part, sizeof(double) * (size_t)c->mg_rows * 2 * N) == hipSuccess;
-  ok = ok && hipMalloc((void**)&c->mg_dots, sizeof(double) * 2 * (size_t)N) == hipSuccess;
   for (int k = 1; k < nl && ok; ++k) ok = hipMalloc((void**)&lv[k].diag, sizeof(double) * lv[k].n) == hipSuccess;
   for (int k = 0; k < nl && ok; ++k) ok = hipMalloc((void**)&lv[k].wd, sizeof(double) * lv[k].n) == hipSuccess;
   c->mg_levels = nl;
@@ -958,15 +1204,19 @@ ope_status mg_build(ope_ctx* c) {
   mem += (size_t)esz * c->n * N;
   c->mg_Z = mem;
   mem += (size_t)esz * c->n * N;
-  for (int k = 1; k < nl; ++k) {
+  for (int k = 1; k <= k0; ++k) {
     c->mg[k].B = mem;
     mem += (size_t)esz * c->mg[k].n * N;
     c->mg[k].E = mem;
     mem += (size_t)esz * c->mg[k].n * N;
+    if (k == k0) break;
     c->mg[k].T = mem;
     mem += (size_t)esz * c->mg[k].n * N;
   }
+  c->mg_k0 = k0;
   ok = hipMemcpy(c->mg_inv, A.data(), sizeof(double) * (size_t)nc * nc, hipMemcpyHostToDevice) == hipSuccess;
+  if (!cdat.empty())
+    ok = ok && hipMemcpy(c->mg_cdat, cdat.data(), sizeof(double) * cdat.size(), hipMemcpyHostToDevice) == hipSuccess;
   for (int k = 1; k < nl && ok; ++k)
     ok = hipMemcpy(c->mg[k].diag, diags[(size_t)k].data(), sizeof(double) * c->mg[k].n, hipMemcpyHostToDevice) ==
          hipSuccess;
@@ -985,9 +1235,9 @@ ope_status mg_build(ope_ctx* c) {
 template <typename T, int VW>
 static hipError_t vcycle_t(ope_ctx* c, const T* r, T* z, const int32_t* active, bool dots) {
   const uint32_t N = (uint32_t)c->N, NV = N / VW;
-  const int L = c->mg_levels;
+  const int k0 = c->mg_k0;                        // first fused level, at least 1
   hipStream_t s = c->stream;
-  for (int k = 0; k + 1 < L; ++k) {
+  for (int k = 0; k < k0; ++k) {
     const MgLevel& f = c->mg[k];
     const MgLevel& q = c->mg[k + 1];
     const T* in = k == 0 ? r : (const T*)f.B;
@@ -1010,11 +1260,15 @@ static hipError_t vcycle_t(ope_ctx* c, const T* r, T* z, const int32_t* active, 
     hipLaunchKernelGGL((k_mg_zrestrict<T, VW>), dim3(zq.nxs * q.m1 * zq.nzc), dim3(MG_WG), 0, s, (const T*)f.T,
                        (T*)q.B, geom(f), geom(q), active, N, NV, zq);
   }
-  const MgLevel& cl = c->mg[L - 1];
-  const uint64_t tcl = (uint64_t)cl.n * NV;
-  hipLaunchKernelGGL((k_mg_dense<T, VW>), dim3(grid_of(tcl)), dim3(MG_WG), 0, s, c->mg_inv, (const T*)cl.B, (T*)cl.E,
-                     (uint32_t)cl.n, active, N, NV, tcl);
-  for (int k = L - 2; k >= 0; --k) {
+  size_t values = 0;
+  McArgs ma = coarse_args(c->mg, c->mg_levels, k0, &values);
+  ma.diag0 = c->mg[k0].diag;
+  ma.wd0 = c->mg[k0].wd;
+  ma.cdat = c->mg_cdat;
+  ma.inv = c->mg_inv;
+  hipLaunchKernelGGL((k_mg_coarse<T>), dim3(N), dim3(MC_WG), values * sizeof(T), s, (const T*)c->mg[k0].B, (T*)c->mg[k0].E, ma, active,
+                     N);
+  for (int k = k0 - 1; k >= 0; --k) {
     const MgLevel& f = c->mg[k];
     const MgLevel& q = c->mg[k + 1];
     const T* in = k == 0 ? r : (const T*)f.B;
@@ -1061,12 +1315,14 @@ hipError_t mg_vcycle(ope_ctx* c, const void* r, void* z, const int32_t* active, 
 }
 
 hipError_t launch_pcg_start(ope_ctx* c) {
-  hipLaunchKernelGGL(k_pcg_start, dim3(1), dim3(MG_WG), 0, c->stream, c->mg_dots, (uint32_t)c->N, c->rho);
+  hipLaunchKernelGGL(k_pcg_scalars<true>, dim3(1), dim3(PS_WG), 0, c->stream, c->mg_part, (uint32_t)c->mg_rows_used,
+                     (uint32_t)c->N, c->rho, c->beta, c->target, c->active, c->sc, (int32_t*)nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_pcg_beta(ope_ctx* c) {
-  hipLaunchKernelGGL(k_pcg_beta, dim3(1), dim3(MG_WG), 0, c->stream, c->mg_dots, (uint32_t)c->N, c->rho, c->beta,
-                     c->target, c->active, c->sc);
+hipError_t launch_pcg_beta(ope_ctx* c, int32_t* flags) {
+  ProfScope ps(c, OPE_KERNEL_CG_REDUCE);
+  hipLaunchKernelGGL(k_pcg_scalars<false>, dim3(1), dim3(PS_WG), 0, c->stream, c->mg_part, (uint32_t)c->mg_rows_used,
+                     (uint32_t)c->N, c->rho, c->beta, c->target, c->active, c->sc, flags);
   return hipGetLastError();
 }

@@ -209,20 +209,18 @@ ope_status phase_residual(ope_ctx* c, const void* Uv) {
 // buffer roles of iteration `it` (r and p alternate between two buffers, alpha
 // between the two halves of its array).  The y term of an even iteration is
 // added by the next iteration's sweep B, together with its own.
-hipError_t cg_iteration_body(ope_ctx* c, int it);
 
 // The buffer the CG iterates on: Y, or in a recycled step the correction Dr.
 static inline void* cg_y(const ope_ctx* c) { return c->cg_on_d ? c->Dr : c->Y; }
 
-// One CG iteration; its timed launches are tagged with the iteration index.
-hipError_t cg_iteration(ope_ctx* c, int it) {
+// The sweeps of iteration `it` and the column reductions between them; its
+// timed launches are tagged with the iteration index.
+hipError_t cg_sweeps(ope_ctx* c, int it) {
+  struct Tag {
+    ope_ctx* c;
+    ~Tag() { c->prof_tag = -1; }
+  } tag{c};
   c->prof_tag = it;
-  const hipError_t r = cg_iteration_body(c, it);
-  c->prof_tag = -1;
-  return r;
-}
-
-hipError_t cg_iteration_body(ope_ctx* c, int it) {
   void* r_cur = c->Rb[it & 1];
   void* r_nxt = c->Rb[(it + 1) & 1];
   void* p_old = (it & 1) ? c->Pb : c->HU;    // never read on the first iteration
@@ -240,27 +238,34 @@ hipError_t cg_iteration_body(ope_ctx* c, int it) {
   }
   if (it & 1) e = launch_cg_update(c, r_cur, p_new, r_nxt, a_cur, cg_y(c), p_old, a_prev);
   else e = launch_cg_update(c, r_cur, p_new, r_nxt, a_cur, nullptr, nullptr, nullptr);
-  if (e != hipSuccess) return e;
-  if (c->mg_on) {
-    // z = B r', then beta = r'^T z / rho and the stop test on |r'|^2
-    if ((e = mg_vcycle(c, r_nxt, c->mg_Z, c->active, true)) != hipSuccess) return e;
-    ProfScope ps(c, OPE_KERNEL_CG_REDUCE);
-    if ((e = launch_reduce_cols(c, c->mg_part, c->mg_rows_used, 2 * N, c->mg_dots, RED_PLAIN)) != hipSuccess)
-      return e;
-    return launch_pcg_beta(c);
-  }
+  if (e != hipSuccess || c->mg_on) return e;
   ProfScope ps(c, OPE_KERNEL_CG_REDUCE);
   return launch_reduce_cols(c, c->part, march_rows(c), N, nullptr, RED_CG_BETA, a_cur);
+}
+
+// The preconditioner's part of iteration `it`: z = B r', then beta = r'^T z / rho
+// and the stop test on |r'|^2 (flags as for launch_pcg_beta).
+hipError_t pcg_precondition(ope_ctx* c, int it, int32_t* flags) {
+  struct Tag {
+    ope_ctx* c;
+    ~Tag() { c->prof_tag = -1; }
+  } tag{c};
+  c->prof_tag = it;
+  const hipError_t e = mg_vcycle(c, c->Rb[(it + 1) & 1], c->mg_Z, c->active, true);
+  return e != hipSuccess ? e : launch_pcg_beta(c, flags);
+}
+
+// One whole CG iteration.
+hipError_t cg_iteration(ope_ctx* c, int it) {
+  const hipError_t e = cg_sweeps(c, it);
+  return e != hipSuccess || !c->mg_on ? e : pcg_precondition(c, it, nullptr);
 }
 
 // Preconditioned CG start, after the CG set-up (targets and flags from |r0|^2):
 // z0 = B r0 and rho = r0^T z0.
 hipError_t pcg_begin(ope_ctx* c) {
-  hipError_t e;
-  if ((e = mg_vcycle(c, c->Rb[0], c->mg_Z, c->active, true)) != hipSuccess) return e;
-  if ((e = launch_reduce_cols(c, c->mg_part, c->mg_rows_used, 2 * c->N, c->mg_dots, RED_PLAIN)) != hipSuccess)
-    return e;
-  return launch_pcg_start(c);
+  const hipError_t e = mg_vcycle(c, c->Rb[0], c->mg_Z, c->active, true);
+  return e != hipSuccess ? e : launch_pcg_start(c);
 }
 
 // After `its` CG iterations: when the last one was even, add its deferred y
@@ -315,22 +320,41 @@ void build_graphs(ope_ctx* c) {
 }
 
 // Host convergence checks of the preconditioned CG: it converges in a few
-// iterations (about 2-4 per step) that each cost about 1 ms, and the chunk
-// enqueued behind the one being checked runs past convergence as no-op
-// launches (about 0.1 ms per iteration), so every iteration is checked; graph
-// chunks hold pairs of iterations.
+// iterations (about 2-4 per step) that each cost about 1 ms at 64^3, N = 128, so
+// every iteration is checked (see split_chunks); graph chunks hold pairs of
+// iterations.
 int mg_check_every(const ope_ctx* c) { return c->use_graphs ? 2 : 1; }
+
+// The preconditioned CG without graphs is checked after every iteration, with
+// the next iteration's sweeps (not its V-cycle) enqueued behind the check: they
+// keep the GPU busy while the host reads the flags, and past convergence they
+// are three launches that do nothing instead of a whole iteration's fourteen.
+bool split_chunks(const ope_ctx* c) { return c->mg_on && !c->use_graphs; }
+
+// CG chunks in flight at once.
+int chunk_depth(const ope_ctx* c) { return split_chunks(c) ? 1 : 2; }
+
+// Iterations whose sweeps are enqueued once the chunks up to iteration `it` are.
+int32_t swept(const ope_ctx* c, int32_t it, int32_t max_iter) { return split_chunks(c) && it > 0 ? std::min(it + 1, max_iter) : it; }
 
 // Enqueues CG iterations up to the next host check (a multiple of
 // check_every, or max_iter), the copy of the column flags into host slot
 // `slot` and that slot's event.  Whole chunks run as graph replays when graphs
 // are on (and no kernel is being timed), the rest as eager launches.
 hipError_t cg_chunk(ope_ctx* c, int32_t* it, int32_t max_iter, int slot) {
+  hipError_t e;
+  int32_t* flags = c->hactive + (size_t)slot * c->N;
+  if (split_chunks(c)) {
+    if (*it == 0 && (e = cg_sweeps(c, 0)) != hipSuccess) return e;
+    if ((e = pcg_precondition(c, *it, flags)) != hipSuccess) return e;
+    if ((e = hipEventRecord(c->chunk_ev[slot], c->stream)) != hipSuccess) return e;
+    *it += 1;
+    return *it < max_iter ? cg_sweeps(c, *it) : hipSuccess;
+  }
   const int K = c->check_every;
   const bool graphs = c->use_graphs && c->prof_kernel < 0 && K % 2 == 0 && !c->recycle;
   if (graphs && c->graph_state == 0) build_graphs(c);
   const int32_t end = std::min<int32_t>(max_iter, (*it / K + 1) * K);
-  hipError_t e;
   while (*it < end) {
     if (graphs && c->graph_state == 1 && *it % K == 0 && *it + K <= end) {
       if ((e = hipGraphLaunch(c->cg_graph[*it == 0 ? 0 : 1], c->stream)) != hipSuccess) return e;
@@ -340,8 +364,7 @@ hipError_t cg_chunk(ope_ctx* c, int32_t* it, int32_t max_iter, int slot) {
       *it += 1;
     }
   }
-  if ((e = hipMemcpyAsync(c->hactive + (size_t)slot * c->N, c->active, sizeof(int32_t) * c->N,
-                          hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
+  if ((e = hipMemcpyAsync(flags, c->active, sizeof(int32_t) * c->N, hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
     return e;
   return hipEventRecord(c->chunk_ev[slot], c->stream);
 }
@@ -388,7 +411,7 @@ ope_status run_cg(ope_ctx* c, int32_t max_iter, int32_t* iters, bool* all_done) 
   int slot_next = 0, head = 0, nout = 0;
   int q[2] = {0, 0};
   for (;;) {
-    while (it < max_iter && nout < 2) {
+    while (it < max_iter && nout < chunk_depth(c)) {
       HIPCHK(cg_chunk(c, &it, max_iter, slot_next));
       q[(head + nout) & 1] = slot_next;
       ++nout;
@@ -404,6 +427,7 @@ ope_status run_cg(ope_ctx* c, int32_t max_iter, int32_t* iters, bool* all_done) 
       break;
     }
   }
+  it = swept(c, it, max_iter);
   HIPCHK(cg_flush(c, it, c->stream));
   *iters = it;
   *all_done = done;
@@ -956,7 +980,7 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
         continue;
       }
       ope_ctx* c = b->ctx[i];
-      while (bs.it[i] < c->max_iter && nout[i] < 2) {
+      while (bs.it[i] < c->max_iter && nout[i] < chunk_depth(c)) {
         if (cg_chunk(c, &bs.it[i], c->max_iter, slot_next[i]) != hipSuccess) {
           bs.st[i] = OPE_EHIP;
           pending[i] = go[i] = 0;
@@ -1009,7 +1033,8 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
   for (int i = 0; i < P; ++i) {
     if (!go[i]) continue;
     ope_ctx* c = b->ctx[i];
-    ope_status st = cg_flush(c, bs.it[i], c->stream) == hipSuccess ? OPE_OK : OPE_EHIP;   // shared CG: synchronised
+    ope_status st = cg_flush(c, swept(c, bs.it[i], c->max_iter), c->stream) == hipSuccess ? OPE_OK
+                                                                                    : OPE_EHIP;   // shared CG: synchronised
     if (st == OPE_OK) st = phase_update(c, U[i], tau);
     if (st == OPE_OK && hipMemcpyAsync(c->hsc, c->sc, sizeof(OpeScalars), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
       st = OPE_EHIP;

@@ -186,13 +186,14 @@ struct ope_ctx {
   // multigrid-preconditioned Step 1 (ope_set_multigrid; FP64)
   int mg_on;
   int mg_levels;
+  int mg_k0;                    // first level of the fused coarse end (its B and E are the last level blocks)
   MgLevel mg[OPE_MG_MAX_LEVELS];
   double* mg_inv;               // coarsest level: dense inverse, row-major nc x nc
+  double* mg_cdat;              // omega / diagonal and diagonal of the levels below mg_k0
   void* mg_Z;                   // preconditioned residual z (n x N, the context's storage type)
   double* mg_part;              // partial rows of r^T z and r^T r (mg_rows x 2N)
   int64_t mg_rows;
   int64_t mg_rows_used;         // partial rows written by the last V-cycle with dots
-  double* mg_dots;              // 2N: r^T z, r^T r
   void* mg_mem;                 // one allocation holding the level blocks
   // kernel timing (ope_profile_begin / ope_profile_end)
   int prof_kernel;              // kernel id being timed, -1 when off
@@ -266,9 +267,10 @@ void mg_free(ope_ctx* c);
 // z = B r (one V-cycle) for the columns still active (all when active is
 // NULL); with dots, also the partial rows of r^T z and r^T r into c->mg_part
 hipError_t mg_vcycle(ope_ctx* c, const void* r, void* z, const int32_t* active, bool dots);
-// PCG scalars from the reduced dots: start (rho = r^T z) and the beta update
+// PCG scalars from the V-cycle's partial rows: start (rho = r^T z) and the beta
+// update (flags, nullable: a copy of the column flags in pinned host memory)
 hipError_t launch_pcg_start(ope_ctx* c);
-hipError_t launch_pcg_beta(ope_ctx* c);
+hipError_t launch_pcg_beta(ope_ctx* c, int32_t* flags);
 
 // column sums of partials: out[j] = sum_w part[w*ncols + j], fixed order
 // (the CG modes write alpha, default c->alpha)

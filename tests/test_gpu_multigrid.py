@@ -326,3 +326,27 @@ def test_mixed_solve_with_multigrid_reaches_dense_eigenvalues():
     assert sf.converged == 1
     assert np.max(np.abs(ritz - w[:p.N]) / w[:p.N]) <= 1e-10
     assert drift <= 1e-12
+
+
+@pytest.mark.parametrize("m,N", [((25, 25, 25), 3), ((26, 25, 25), 5), ((24, 26, 28), 2), ((4000, 1), 3), ((1, 97, 41), 4),
+                                 ((6000, 2), 1), ((9, 7, 5), 212), ((5, 4, 4), 1), ((2, 2, 30), 6)])
+def test_vcycle_at_the_edges_of_the_fused_coarse_end(m, N):
+    """Grids whose levels meet the fused coarse end at its largest size (13^3 =
+    2197 nodes stay outside, 12 x 13 x 14 = 2184 too, levels below go in), whose
+    levels shrink along one axis only, or whose first coarse level is already
+    the coarsest."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    rng = np.random.default_rng(len(m) * 100 + N)
+    V = rng.uniform(0.0, 40.0, g.n)
+    N = min(N, g.n)
+    hier = O.Hierarchy(O.Operator(g.m, g.h, V))
+    R = rng.standard_normal((g.n, N))
+    ref = hier.vcycle(R)
+    say(f"mg vcycle coarse end m={m} N={N}")
+    with ope.Context(g, V, N) as c:
+        ope.ope_set_multigrid(c.handle, True)
+        Z = empty_dev(g.n, N)
+        ope.ope_mg_vcycle(c.handle, to_dev(R), Z)
+        got = to_host(Z)
+    assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
