@@ -82,15 +82,24 @@ __device__ __forceinline__ bool vec_active(const int32_t* __restrict__ active, u
   return a;
 }
 
-// x0 = (omega / d) b at point q, with wd = omega / d (zero outside the grid is
-// the caller's job)
-template <typename T, int VW>
-__device__ __forceinline__ void jac0(const T* __restrict__ b, const double* __restrict__ wd, uint64_t q, uint32_t N,
-                                     uint32_t v, T (&o)[VW]) {
-  ldr<T, VW>(b, q, N, v, o);
-  const T w = (T)wd[q];
+// VW elements at a lane's byte offset `o` into a plane whose pointer is the same
+// for the whole wave.  A lane's columns do not change over a march along z, so
+// its offsets are formed once and a plane costs one scalar addition instead of a
+// 64-bit multiplication per access.  O is 32 bits wide where a plane of every
+// array is smaller than 4 GiB (narrow_planes), else 64.
+template <typename T, int VW, typename O>
+__device__ __forceinline__ void ldo(const T* __restrict__ plane, O o, T (&v)[VW]) {
+  const Chunk<T, VW> t = *reinterpret_cast<const Chunk<T, VW>*>(reinterpret_cast<const char*>(plane) + o);
 #pragma unroll
-  for (int k = 0; k < VW; ++k) o[k] = w * o[k];
+  for (int k = 0; k < VW; ++k) v[k] = t.v[k];
+}
+
+template <typename T, int VW, typename O>
+__device__ __forceinline__ void sto(T* __restrict__ plane, O o, const T (&v)[VW]) {
+  Chunk<T, VW> t;
+#pragma unroll
+  for (int k = 0; k < VW; ++k) t.v[k] = v[k];
+  *reinterpret_cast<Chunk<T, VW>*>(reinterpret_cast<char*>(plane) + o) = t;
 }
 
 // Fine nodes and weights of coarse node I along one axis: always four taps
@@ -434,11 +443,20 @@ TShape tshape(uint32_t m0, uint32_t m1, uint32_t m2, uint32_t NV, uint32_t N, ui
   }
   s.nxt = (m0 + s.TX - 1) / s.TX;
   s.nyt = (m1 + s.TY - 1) / s.TY;
+  // z ranges: one work-group of this size fits a compute unit (256 of them), so a
+  // launch runs in rounds of 256, each as long as a range and about two planes of
+  // set-up; the count with the shortest total (64^3, N = 17, 80 tiles: 480
+  // work-groups of 11 planes in 2 rounds, against 560 of 10 in 3)
   const uint64_t tiles = (uint64_t)s.nxt * s.nyt * s.NS;
-  uint64_t nzc = (512 + tiles - 1) / tiles;       // at least 512 work-groups when the grid allows
-  if (nzc > m2) nzc = m2;
-  if (nzc < 1) nzc = 1;
-  s.ZC = (uint32_t)((m2 + nzc - 1) / nzc);
+  uint64_t best = UINT64_MAX;
+  for (uint32_t nzc = 1; nzc <= m2 && nzc <= 64; ++nzc) {
+    const uint32_t ZC = (m2 + nzc - 1) / nzc, nr = (m2 + ZC - 1) / ZC;
+    const uint64_t cost = ((tiles * nr + 255) / 256) * (ZC + 2);
+    if (cost < best) {
+      best = cost;
+      s.ZC = ZC;
+    }
+  }
   s.nzc = (m2 + s.ZC - 1) / s.ZC;
   return s;
 }
@@ -469,10 +487,10 @@ __device__ __forceinline__ TPos tpos(const TShape& ts, uint32_t L) {
 }
 
 // Ring column j of a tiled work-group (k = pt + j P, k < 2 (TX + TY): bottom
-// row, top row, left column, right column): its grid x-y index (when inside
+// row, top row, left column, right column): its grid column (when inside
 // the grid) and its LDS slot.
 struct RingCol {
-  uint64_t col;
+  uint32_t x, y;
   uint32_t slot;
   bool ok, in;
 };
@@ -483,7 +501,7 @@ __device__ __forceinline__ RingCol ring_col(const MgGeom& g, const TShape& ts, u
   const uint32_t RING = 2 * (ts.TX + ts.TY), W = ts.TX + 2;
   rc.ok = k < RING;
   rc.in = false;
-  rc.col = 0;
+  rc.x = rc.y = 0;
   rc.slot = 0;
   if (!rc.ok) return rc;
   int64_t hx, hy;
@@ -500,7 +518,10 @@ __device__ __forceinline__ RingCol ring_col(const MgGeom& g, const TShape& ts, u
   }
   rc.slot = ((cy * W + cx) * NVS + vl) * VW;
   rc.in = act && hx >= 0 && hx < (int64_t)g.m0 && hy >= 0 && hy < (int64_t)g.m1;
-  if (rc.in) rc.col = (uint64_t)hy * g.m0 + (uint64_t)hx;
+  if (rc.in) {
+    rc.x = (uint32_t)hx;
+    rc.y = (uint32_t)hy;
+  }
   return rc;
 }
 
@@ -509,7 +530,7 @@ __device__ __forceinline__ RingCol ring_col(const MgGeom& g, const TShape& ts, u
 // (the ring's b and omega/d of the next plane, the own column's two planes
 // ahead), so a plane's wait finds them arrived; the two tile buffers
 // alternate, one barrier per plane.
-template <typename T, int VW, int R>
+template <typename T, int VW, int R, typename O>
 __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b, T* __restrict__ out, MgGeom g,
                                                        const double* __restrict__ diag, const double* __restrict__ wd,
                                                        const int32_t* __restrict__ active, uint32_t N, TShape ts) {
@@ -527,22 +548,34 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
   if (!__syncthreads_or(act ? 1 : 0)) return;     // every column of the slice has stopped
   const bool own = inb && act;
   const uint32_t z0 = wp.zc * ts.ZC, z1 = z0 + ts.ZC < g.m2 ? z0 + ts.ZC : g.m2;
-  const uint64_t s2 = (uint64_t)g.m0 * g.m1;
+  const uint64_t s2 = (uint64_t)g.m0 * g.m1, s2N = s2 * N;       // points and elements of a plane
   const uint32_t W = ts.TX + 2, P = ts.TX * ts.TY;
   auto slot = [&](uint32_t cx, uint32_t cy) -> uint32_t { return ((cy * W + cx) * NVS + vl) * VW; };
+  auto field_off = [&](uint32_t cx, uint32_t cy) -> O {
+    return (((O)cy * g.m0 + cx) * N + (O)VW * v) * (O)sizeof(T);
+  };
+  auto coef_off = [&](uint32_t cx, uint32_t cy) -> O { return ((O)cy * g.m0 + cx) * (O)sizeof(double); };
   RingCol rc[R];
+  O ro[R], rwo[R];
   T rb[R][VW], rw[R];
 #pragma unroll
-  for (int j = 0; j < R; ++j) rc[j] = ring_col(g, ts, x0, y0, pt + (uint32_t)j * P, NVS, vl, VW, act);
+  for (int j = 0; j < R; ++j) {
+    rc[j] = ring_col(g, ts, x0, y0, pt + (uint32_t)j * P, NVS, vl, VW, act);
+    ro[j] = field_off(rc[j].x, rc[j].y);
+    rwo[j] = coef_off(rc[j].x, rc[j].y);
+  }
+  const O oo = own ? field_off(x, y) : 0, owo = own ? coef_off(x, y) : 0;
+  auto coef = [&](const double* plane, O o) -> T {
+    return (T)*reinterpret_cast<const double*>(reinterpret_cast<const char*>(plane) + o);
+  };
   auto ring_load = [&](uint32_t z) {
 #pragma unroll
     for (int j = 0; j < R; ++j) {
       zero(rb[j]);
       rw[j] = T(0);
       if (rc[j].in) {
-        const uint64_t q = (uint64_t)z * s2 + rc[j].col;
-        ldr<T, VW>(b, q, N, v, rb[j]);
-        rw[j] = (T)wd[q];
+        ldo<T, VW, O>(b + z * s2N, ro[j], rb[j]);
+        rw[j] = coef(wd + z * s2, rwo[j]);
       }
     }
   };
@@ -553,21 +586,25 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
   zero(fc);
   zero(bc);
   zero(bn);
-  uint64_t p = ((uint64_t)z0 * g.m1 + (inb ? y : 0)) * g.m0 + (inb ? x : 0);
   if (own) {
-    if (z0 > 0) jac0<T, VW>(b, wd, p - s2, N, v, fm);
-    ldr<T, VW>(b, p, N, v, bc);
-    const T w0 = (T)wd[p];
+    if (z0 > 0) {
+      ldo<T, VW, O>(b + (z0 - 1) * s2N, oo, fm);
+      const T wm = coef(wd + (z0 - 1) * s2, owo);
+#pragma unroll
+      for (int k = 0; k < VW; ++k) fm[k] = wm * fm[k];
+    }
+    ldo<T, VW, O>(b + z0 * s2N, oo, bc);
+    const T w0 = coef(wd + z0 * s2, owo);
 #pragma unroll
     for (int k = 0; k < VW; ++k) fc[k] = w0 * bc[k];
-    dc = (T)diag[p];
+    dc = coef(diag + z0 * s2, owo);
     if (z0 + 1 < g.m2) {
-      ldr<T, VW>(b, p + s2, N, v, bn);
-      wn = (T)wd[p + s2];
+      ldo<T, VW, O>(b + (z0 + 1) * s2N, oo, bn);
+      wn = coef(wd + (z0 + 1) * s2, owo);
     }
   }
   ring_load(z0);
-  for (uint32_t z = z0; z < z1; ++z, p += s2) {
+  for (uint32_t z = z0; z < z1; ++z) {
     T* tile = tiles[z & 1];
 #pragma unroll
     for (int k = 0; k < VW; ++k) tile[slot(tx + 1, ty + 1) + k] = fc[k];
@@ -586,10 +623,10 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
     zero(b2);
     if (own && z + 1 < z1) {
       if (z + 2 < g.m2) {
-        ldr<T, VW>(b, p + 2 * s2, N, v, b2);
-        w2 = (T)wd[p + 2 * s2];
+        ldo<T, VW, O>(b + (z + 2) * s2N, oo, b2);
+        w2 = coef(wd + (z + 2) * s2, owo);
       }
-      d2 = (T)diag[p + s2];
+      d2 = coef(diag + (z + 1) * s2, owo);
     }
     __syncthreads();
     if (own) {
@@ -602,7 +639,7 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
                                     (T)g.cy * (tile[sym + k] + tile[syp + k]) + (T)g.cz * (fm[k] + fp[k]));
         o[k] = bc[k] - hxv;
       }
-      str<T, VW>(out, p, N, v, o);
+      sto<T, VW, O>(out + z * s2N, oo, o);
     }
 #pragma unroll
     for (int k = 0; k < VW; ++k) {
@@ -616,68 +653,62 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
   }
 }
 
-// Coarse x-y interpolation of coarse plane K at a fine column (fixed taps).
-template <typename T, int VW>
-__device__ __forceinline__ void coarse_xy(const T* __restrict__ E, const MgGeom& cg, const uint32_t (&Ix)[2],
-                                          const double (&wx)[2], const uint32_t (&Iy)[2], const double (&wy)[2],
-                                          uint32_t K, uint32_t N, uint32_t v, T (&o)[VW]) {
-  zero(o);
-#pragma unroll
-  for (int bb = 0; bb < 2; ++bb) {
-    T ax[VW];
-    zero(ax);
-    const uint64_t row = ((uint64_t)K * cg.m1 + Iy[bb]) * cg.m0;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      T t[VW];
-      ldr<T, VW>(E, row + Ix[a], N, v, t);
-#pragma unroll
-      for (int k = 0; k < VW; ++k) ax[k] += (T)wx[a] * t[k];
-    }
-#pragma unroll
-    for (int k = 0; k < VW; ++k) o[k] += (T)wy[bb] * ax[k];
-  }
-}
-
 // The prolongation P e along one fine column, marched plane by plane: the
-// x-y interpolations of the coarse planes K0 - 1, K0, K0 + 1 around the
-// current plane's parent K0 stay in registers (each coarse plane read once).
-template <typename T, int VW>
+// x-y interpolations of the coarse planes K - 1, K, K + 1 around the current
+// plane's parent K = z / 2 stay in registers (each coarse plane read once,
+// through four offsets fixed over the march).
+template <typename T, int VW, typename O>
 struct PeMarch {
-  uint32_t Ix[2], Iy[2];
-  double wx[2], wy[2];
+  O off[2][2];                                    // [y tap][x tap]
+  T wx[2], wy[2];
   T lo[VW], mid[VW], hi[VW];
-  uint32_t K0;
-  bool flat;                                      // no z axis: the one coarse plane 0
 
-  __device__ __forceinline__ void init(const T* __restrict__ E, const MgGeom& fg, const MgGeom& cg,
+  // x-y interpolation of the coarse plane at `plane`
+  __device__ __forceinline__ void interp(const T* __restrict__ plane, T (&o)[VW]) const {
+    T e[2][2][VW];
+#pragma unroll
+    for (int bb = 0; bb < 2; ++bb)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) ldo<T, VW, O>(plane, off[bb][a], e[bb][a]);
+#pragma unroll
+    for (int k = 0; k < VW; ++k)
+      o[k] = wy[0] * (wx[0] * e[0][0][k] + wx[1] * e[0][1][k]) + wy[1] * (wx[0] * e[1][0][k] + wx[1] * e[1][1][k]);
+  }
+  // planes around z (flat: no z axis, the one coarse plane 0); csN: elements of a coarse plane
+  __device__ __forceinline__ void init(const T* __restrict__ E, const MgGeom& fg, const MgGeom& cg, uint64_t csN,
                                        uint32_t fx, uint32_t fy, uint32_t z, uint32_t N, uint32_t v) {
-    prolong_taps(fx, fg.m0, cg.m0, Ix, wx);
-    prolong_taps(fy, fg.m1, cg.m1, Iy, wy);
-    flat = fg.m2 == 1;
+    uint32_t Ix[2], Iy[2];
+    double dx[2], dy[2];
+    prolong_taps(fx, fg.m0, cg.m0, Ix, dx);
+    prolong_taps(fy, fg.m1, cg.m1, Iy, dy);
+#pragma unroll
+    for (int bb = 0; bb < 2; ++bb) {
+      wx[bb] = (T)dx[bb];
+      wy[bb] = (T)dy[bb];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) off[bb][a] = (((O)Iy[bb] * cg.m0 + Ix[a]) * N + (O)VW * v) * (O)sizeof(T);
+    }
     zero(lo);
     zero(hi);
-    K0 = flat ? 0 : z / 2;
-    coarse_xy<T, VW>(E, cg, Ix, wx, Iy, wy, K0, N, v, mid);
-    if (!flat) {
-      if (K0 >= 1) coarse_xy<T, VW>(E, cg, Ix, wx, Iy, wy, K0 - 1, N, v, lo);
-      if (K0 + 1 < cg.m2) coarse_xy<T, VW>(E, cg, Ix, wx, Iy, wy, K0 + 1, N, v, hi);
+    const uint32_t K = fg.m2 == 1 ? 0 : z / 2;
+    interp(E + K * csN, mid);
+    if (fg.m2 > 1) {
+      if (K >= 1) interp(E + (K - 1) * csN, lo);
+      if (K + 1 < cg.m2) interp(E + (K + 1) * csN, hi);
     }
   }
   // move to plane z (the plane after the current one)
-  __device__ __forceinline__ void step(const T* __restrict__ E, const MgGeom& cg, uint32_t z, uint32_t N,
-                                       uint32_t v) {
-    if (flat || z % 2 != 0) return;
-    K0 = z / 2;
+  __device__ __forceinline__ void step(const T* __restrict__ E, const MgGeom& cg, uint64_t csN, uint32_t z) {
+    if (z % 2 != 0) return;
 #pragma unroll
     for (int k = 0; k < VW; ++k) {
       lo[k] = mid[k];
       mid[k] = hi[k];
     }
     zero(hi);
-    if (K0 + 1 < cg.m2) coarse_xy<T, VW>(E, cg, Ix, wx, Iy, wy, K0 + 1, N, v, hi);
+    if (z / 2 + 1 < cg.m2) interp(E + (z / 2 + 1) * csN, hi);
   }
-  __device__ __forceinline__ void value(uint32_t z, T (&pe)[VW]) const {
+  __device__ __forceinline__ void value(uint32_t z, bool flat, T (&pe)[VW]) const {
 #pragma unroll
     for (int k = 0; k < VW; ++k) pe[k] = flat ? mid[k] : T(0.75) * mid[k] + T(0.25) * (z % 2 == 0 ? lo[k] : hi[k]);
   }
@@ -686,9 +717,15 @@ struct PeMarch {
 // Prolongation and post-smoothing in one x-y tiled sweep (as k_mg_tstencil):
 // x1 = omega b / d + P e is formed on the fly for the tile's columns and its
 // ring, then z = x1 + omega (b - H x1) / d; with DOTS also the per-column
-// sums of b z and b b (row blockIdx.x of part).  The ring columns are spread
-// over the threads (at most two per thread), each with its own P e march.
-template <typename T, int VW, bool DOTS, int R>
+// sums of b z and b b (row `wp.row` of part).  The ring columns are spread
+// over the threads, each with its own P e march; b and the coefficients are
+// loaded one plane ahead (the own column's two).  Bound by one work-group's
+// progress per compute unit (its registers and threads leave room for no
+// second): instructions and the barrier of every plane.  Offsets fixed over the
+// march, the loads a plane ahead and rounds without a short last one (tshape)
+// took it from 60 to 40 us at 64^3, N = 17 (its bytes alone take 16 us), 193 to
+// 163 us at N = 128 (121 us) and 110 to 95 us in FP32.
+template <typename T, int VW, bool DOTS, int R, typename O>
 __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, const T* __restrict__ E,
                                                     T* __restrict__ out, MgGeom g, MgGeom cg,
                                                     const double* __restrict__ diag, const double* __restrict__ wd,
@@ -701,7 +738,7 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
   const uint32_t vl = t % NVS, pt = t / NVS;
   const uint32_t tx = pt % ts.TX, ty = pt / ts.TX;
   const TPos wp = tpos(ts, xcd_remap(blockIdx.x, gridDim.x));
-  const uint32_t v = wp.sl * NVS + vl, zc = wp.zc;
+  const uint32_t v = wp.sl * NVS + vl;
   const uint32_t x0 = wp.xt * ts.TX, y0 = wp.yt * ts.TY;
   const uint32_t x = x0 + tx, y = y0 + ty;
   const bool inb = x < g.m0 && y < g.m1;
@@ -717,93 +754,121 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
     return;
   }
   const bool own = inb && act;
-  const uint32_t z0 = zc * ts.ZC, z1 = z0 + ts.ZC < g.m2 ? z0 + ts.ZC : g.m2;
-  const uint64_t s2 = (uint64_t)g.m0 * g.m1;
-  const uint32_t W = ts.TX + 2, RING = 2 * (ts.TX + ts.TY), P = ts.TX * ts.TY;
+  const uint32_t z0 = wp.zc * ts.ZC, z1 = z0 + ts.ZC < g.m2 ? z0 + ts.ZC : g.m2;
+  const uint64_t s2 = (uint64_t)g.m0 * g.m1, s2N = s2 * N;       // points and elements of a plane
+  const uint64_t csN = (uint64_t)cg.m0 * cg.m1 * N;              // elements of a coarse plane
+  const bool flat = g.m2 == 1;
+  const uint32_t W = ts.TX + 2, P = ts.TX * ts.TY;
   auto slot = [&](uint32_t cx, uint32_t cy) -> uint32_t { return ((cy * W + cx) * NVS + vl) * VW; };
-  // x1 at fine point `at` with the column's P e value pe
-  auto x1 = [&](uint64_t at, const T(&pe)[VW], T(&f)[VW]) {
-    jac0<T, VW>(b, wd, at, N, v, f);
-#pragma unroll
-    for (int k = 0; k < VW; ++k) f[k] = f[k] + pe[k];
+  auto field_off = [&](uint32_t cx, uint32_t cy) -> O {
+    return (((O)cy * g.m0 + cx) * N + (O)VW * v) * (O)sizeof(T);
+  };
+  auto coef_off = [&](uint32_t cx, uint32_t cy) -> O { return ((O)cy * g.m0 + cx) * (O)sizeof(double); };
+  auto coef = [&](const double* plane, O o) -> T {
+    return (T)*reinterpret_cast<const double*>(reinterpret_cast<const char*>(plane) + o);
   };
   // ring columns of this thread: k = pt + j P, j < R (R P at least the ring's
-  // 2 (TX + TY) columns)
-  uint32_t rk[R], rcx[R], rcy[R];
-  int64_t rhx[R], rhy[R];
-  bool rin[R];
-  PeMarch<T, VW> rm[R];
+  // 2 (TX + TY) columns); b and omega/d of the current plane
+  RingCol rc[R];
+  O ro[R], rwo[R];
+  T rb[R][VW], rw[R];
+  PeMarch<T, VW, O> rm[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) {
-    const uint32_t k = pt + j * P;
-    rk[j] = k;
-    rin[j] = false;
-    if (k >= RING) continue;
-    if (k < ts.TX) {
-      rhx[j] = (int64_t)x0 + k; rhy[j] = (int64_t)y0 - 1; rcx[j] = k + 1; rcy[j] = 0;
-    } else if (k < 2 * ts.TX) {
-      rhx[j] = (int64_t)x0 + (k - ts.TX); rhy[j] = (int64_t)y0 + ts.TY; rcx[j] = k - ts.TX + 1; rcy[j] = ts.TY + 1;
-    } else if (k < 2 * ts.TX + ts.TY) {
-      rhx[j] = (int64_t)x0 - 1; rhy[j] = (int64_t)y0 + (k - 2 * ts.TX); rcx[j] = 0; rcy[j] = k - 2 * ts.TX + 1;
-    } else {
-      rhx[j] = (int64_t)x0 + ts.TX; rhy[j] = (int64_t)y0 + (k - 2 * ts.TX - ts.TY); rcx[j] = ts.TX + 1;
-      rcy[j] = k - 2 * ts.TX - ts.TY + 1;
-    }
-    rin[j] = act && rhx[j] >= 0 && rhx[j] < (int64_t)g.m0 && rhy[j] >= 0 && rhy[j] < (int64_t)g.m1;
-    if (rin[j]) rm[j].init(E, g, cg, (uint32_t)rhx[j], (uint32_t)rhy[j], z0, N, v);
+    rc[j] = ring_col(g, ts, x0, y0, pt + (uint32_t)j * P, NVS, vl, VW, act);
+    ro[j] = field_off(rc[j].x, rc[j].y);
+    rwo[j] = coef_off(rc[j].x, rc[j].y);
+    if (rc[j].in) rm[j].init(E, g, cg, csN, rc[j].x, rc[j].y, z0, N, v);
   }
-  // own column: the march starts one plane below z0 when there is one
-  PeMarch<T, VW> om;
-  T fm[VW], fc[VW], fp[VW], pe[VW];
+  auto ring_load = [&](uint32_t z) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      zero(rb[j]);
+      rw[j] = T(0);
+      if (rc[j].in) {
+        ldo<T, VW, O>(b + z * s2N, ro[j], rb[j]);
+        rw[j] = coef(wd + z * s2, rwo[j]);
+      }
+    }
+  };
+  // own column: x1 at z - 1 and z; b, omega/d and d at z; b and omega/d at z + 1
+  PeMarch<T, VW, O> om;
+  T fm[VW], fc[VW], bc[VW], bn[VW], pe[VW];
+  T wc = T(0), wn = T(0), dc = T(0);
   zero(fm);
   zero(fc);
-  uint64_t p = ((uint64_t)z0 * g.m1 + (inb ? y : 0)) * g.m0 + (inb ? x : 0);
+  zero(bc);
+  zero(bn);
+  const O oo = own ? field_off(x, y) : 0, owo = own ? coef_off(x, y) : 0;
   if (own) {
-    if (z0 > 0) {
-      om.init(E, g, cg, x, y, z0 - 1, N, v);
-      om.value(z0 - 1, pe);
-      x1(p - s2, pe, fm);
-      om.step(E, cg, z0, N, v);
+    if (z0 > 0) {                                 // the march starts one plane below
+      om.init(E, g, cg, csN, x, y, z0 - 1, N, v);
+      om.value(z0 - 1, flat, pe);
+      ldo<T, VW, O>(b + (z0 - 1) * s2N, oo, fm);
+      const T wm = coef(wd + (z0 - 1) * s2, owo);
+#pragma unroll
+      for (int k = 0; k < VW; ++k) fm[k] = wm * fm[k] + pe[k];
+      om.step(E, cg, csN, z0);
     } else {
-      om.init(E, g, cg, x, y, z0, N, v);
+      om.init(E, g, cg, csN, x, y, z0, N, v);
     }
-    om.value(z0, pe);
-    x1(p, pe, fc);
+    om.value(z0, flat, pe);
+    ldo<T, VW, O>(b + z0 * s2N, oo, bc);
+    wc = coef(wd + z0 * s2, owo);
+    dc = coef(diag + z0 * s2, owo);
+#pragma unroll
+    for (int k = 0; k < VW; ++k) fc[k] = wc * bc[k] + pe[k];
+    if (z0 + 1 < g.m2) {
+      ldo<T, VW, O>(b + (z0 + 1) * s2N, oo, bn);
+      wn = coef(wd + (z0 + 1) * s2, owo);
+    }
   }
+  ring_load(z0);
   double srz[VW], srr[VW];
   zero(srz);
   zero(srr);
-  for (uint32_t z = z0; z < z1; ++z, p += s2) {
+  for (uint32_t z = z0; z < z1; ++z) {
     T* tile = tiles[z & 1];
 #pragma unroll
     for (int k = 0; k < VW; ++k) tile[slot(tx + 1, ty + 1) + k] = fc[k];
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      if (rk[j] >= RING) continue;
-      T hv[VW];
-      zero(hv);
-      if (rin[j]) {
-        T rp[VW];
-        rm[j].value(z, rp);
-        x1(((uint64_t)z * g.m1 + (uint64_t)rhy[j]) * g.m0 + (uint64_t)rhx[j], rp, hv);
-        if (z + 1 < z1) rm[j].step(E, cg, z + 1, N, v);
-      }
+    for (int j = 0; j < R; ++j)
+      if (rc[j].ok) {
+        T hv[VW];
+        zero(hv);
+        if (rc[j].in) {
+          rm[j].value(z, flat, hv);
 #pragma unroll
-      for (int kk = 0; kk < VW; ++kk) tile[slot(rcx[j], rcy[j]) + kk] = hv[kk];
-    }
-    zero(fp);
-    T bc[VW];
-    zero(bc);
-    T d = T(0), w = T(0);
-    if (own) {
-      if (z + 1 < g.m2) {
-        om.step(E, cg, z + 1, N, v);
-        om.value(z + 1, pe);
-        x1(p + s2, pe, fp);
+          for (int k = 0; k < VW; ++k) hv[k] = rw[j] * rb[j][k] + hv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < VW; ++k) tile[rc[j].slot + k] = hv[k];
       }
-      ldr<T, VW>(b, p, N, v, bc);
-      d = (T)diag[p];
-      w = (T)wd[p];
+    // the next plane's ring, the own column two planes ahead
+    if (z + 1 < z1) {
+      ring_load(z + 1);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (rc[j].in) rm[j].step(E, cg, csN, z + 1);
+    }
+    T fp[VW], b2[VW];
+    T w2 = T(0), d2 = T(0);
+    zero(fp);
+    zero(b2);
+    if (own) {
+      if (z + 1 < z1) {
+        if (z + 2 < g.m2) {
+          ldo<T, VW, O>(b + (z + 2) * s2N, oo, b2);
+          w2 = coef(wd + (z + 2) * s2, owo);
+        }
+        d2 = coef(diag + (z + 1) * s2, owo);
+      }
+      if (z + 1 < g.m2) {
+        om.step(E, cg, csN, z + 1);
+        om.value(z + 1, flat, pe);
+#pragma unroll
+        for (int k = 0; k < VW; ++k) fp[k] = wn * bn[k] + pe[k];
+      }
     }
     __syncthreads();
     if (own) {
@@ -812,11 +877,11 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
                      syp = slot(tx + 1, ty + 2);
 #pragma unroll
       for (int k = 0; k < VW; ++k) {
-        const T hxv = d * fc[k] - ((T)g.cx * (tile[sxm + k] + tile[sxp + k]) +
-                                   (T)g.cy * (tile[sym + k] + tile[syp + k]) + (T)g.cz * (fm[k] + fp[k]));
-        o[k] = fc[k] + w * (bc[k] - hxv);
+        const T hxv = dc * fc[k] - ((T)g.cx * (tile[sxm + k] + tile[sxp + k]) +
+                                    (T)g.cy * (tile[sym + k] + tile[syp + k]) + (T)g.cz * (fm[k] + fp[k]));
+        o[k] = fc[k] + wc * (bc[k] - hxv);
       }
-      str<T, VW>(out, p, N, v, o);
+      sto<T, VW, O>(out + z * s2N, oo, o);
       if constexpr (DOTS) {
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
@@ -829,7 +894,12 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
     for (int k = 0; k < VW; ++k) {
       fm[k] = fc[k];
       fc[k] = fp[k];
+      bc[k] = bn[k];
+      bn[k] = b2[k];
     }
+    wc = wn;
+    wn = w2;
+    dc = d2;
   }
   if constexpr (DOTS) {
     // per-column sums over the tile's columns in order, b z then b b (LDS
@@ -1232,7 +1302,7 @@ ope_status mg_build(ope_ctx* c) {
   return OPE_OK;
 }
 
-template <typename T, int VW>
+template <typename T, int VW, typename O>
 static hipError_t vcycle_t(ope_ctx* c, const T* r, T* z, const int32_t* active, bool dots) {
   const uint32_t N = (uint32_t)c->N, NV = N / VW;
   const int k0 = c->mg_k0;                        // first fused level, at least 1
@@ -1246,15 +1316,15 @@ static hipError_t vcycle_t(ope_ctx* c, const T* r, T* z, const int32_t* active, 
     const dim3 sgrid(ts.nxt * ts.nyt * ts.nzc * ts.NS), sblock(ts.TX * ts.TY * ts.NVS);
     switch (ring_per_thread(ts)) {
       case 1:
-        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 1>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
+        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 1, O>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
                            N, ts);
         break;
       case 2:
-        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 2>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
+        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 2, O>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
                            N, ts);
         break;
       default:
-        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 4>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
+        hipLaunchKernelGGL((k_mg_tstencil<T, VW, 4, O>), sgrid, sblock, 0, s, in, (T*)f.T, geom(f), f.diag, f.wd, active,
                            N, ts);
     }
     hipLaunchKernelGGL((k_mg_zrestrict<T, VW>), dim3(zq.nxs * q.m1 * zq.nzc), dim3(MG_WG), 0, s, (const T*)f.T,
@@ -1287,30 +1357,43 @@ static hipError_t vcycle_t(ope_ctx* c, const T* r, T* z, const int32_t* active, 
     {
       ProfScope ps(c, d ? OPE_KERNEL_MG_POST : OPE_KERNEL_COUNT);   // only the finest level is timed
       if (d) {
-        if (R == 1) post(k_mg_tpost<T, VW, true, 1>);
-        else if (R == 2) post(k_mg_tpost<T, VW, true, 2>);
-        else post(k_mg_tpost<T, VW, true, 4>);
+        if (R == 1) post(k_mg_tpost<T, VW, true, 1, O>);
+        else if (R == 2) post(k_mg_tpost<T, VW, true, 2, O>);
+        else post(k_mg_tpost<T, VW, true, 4, O>);
         c->mg_rows_used = rows;
       } else {
-        if (R == 1) post(k_mg_tpost<T, VW, false, 1>);
-        else if (R == 2) post(k_mg_tpost<T, VW, false, 2>);
-        else post(k_mg_tpost<T, VW, false, 4>);
+        if (R == 1) post(k_mg_tpost<T, VW, false, 1, O>);
+        else if (R == 2) post(k_mg_tpost<T, VW, false, 2, O>);
+        else post(k_mg_tpost<T, VW, false, 4, O>);
       }
     }
   }
   return hipGetLastError();
 }
 
+// Whether a plane of the finest level's blocks (and of its coefficients, at most
+// 8 bytes a point) stays below 4 GiB: always in 3D (checked when the context is
+// created), in 2D, where the one plane is the whole block, up to 2^29 FP64 values.
+static bool narrow_planes(const ope_ctx* c) {
+  return (uint64_t)c->mg[0].m0 * c->mg[0].m1 * (uint64_t)c->N * 8u < ((uint64_t)1 << 32);
+}
+
+template <typename T, int VW>
+static hipError_t vcycle(ope_ctx* c, const void* r, void* z, const int32_t* active, bool dots) {
+  return narrow_planes(c) ? vcycle_t<T, VW, uint32_t>(c, (const T*)r, (T*)z, active, dots)
+                          : vcycle_t<T, VW, uint64_t>(c, (const T*)r, (T*)z, active, dots);
+}
+
 hipError_t mg_vcycle(ope_ctx* c, const void* r, void* z, const int32_t* active, bool dots) {
   ProfScope ps(c, OPE_KERNEL_MG);
   if (c->prec == OPE_FP64) {
-    if (mg_vw(c) == 2) return vcycle_t<double, 2>(c, (const double*)r, (double*)z, active, dots);
-    return vcycle_t<double, 1>(c, (const double*)r, (double*)z, active, dots);
+    if (mg_vw(c) == 2) return vcycle<double, 2>(c, r, z, active, dots);
+    return vcycle<double, 1>(c, r, z, active, dots);
   }
   switch (mg_vw(c)) {
-    case 4: return vcycle_t<float, 4>(c, (const float*)r, (float*)z, active, dots);
-    case 2: return vcycle_t<float, 2>(c, (const float*)r, (float*)z, active, dots);
-    default: return vcycle_t<float, 1>(c, (const float*)r, (float*)z, active, dots);
+    case 4: return vcycle<float, 4>(c, r, z, active, dots);
+    case 2: return vcycle<float, 2>(c, r, z, active, dots);
+    default: return vcycle<float, 1>(c, r, z, active, dots);
   }
 }
 

@@ -334,7 +334,9 @@ def test_vcycle_at_the_edges_of_the_fused_coarse_end(m, N):
     """Grids whose levels meet the fused coarse end at its largest size (13^3 =
     2197 nodes stay outside, 12 x 13 x 14 = 2184 too, levels below go in), whose
     levels shrink along one axis only, or whose first coarse level is already
-    the coarsest."""
+    the coarsest.  The set-up recovers the potential from the diagonal, V + 2 sum
+    c_a, so it is off by eps 2 sum c_a and the result by up to that over the
+    smallest eigenvalue of -Lap_h beside the sums' rounding."""
     from paper_2511_06788_amd import ope
     g = W.unit_box_grid(m)
     rng = np.random.default_rng(len(m) * 100 + N)
@@ -349,4 +351,30 @@ def test_vcycle_at_the_edges_of_the_fused_coarse_end(m, N):
         Z = empty_dev(g.n, N)
         ope.ope_mg_vcycle(c.handle, to_dev(R), Z)
         got = to_host(Z)
-    assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
+    lam = sum(4.0 / h ** 2 * np.sin(0.5 * np.pi / (k + 1)) ** 2 for k, h in zip(g.m, g.h))
+    tol = 1e-12 + np.finfo(float).eps * sum(2.0 / h ** 2 for h in g.h) / lam
+    assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(ref))
+
+
+def test_vcycle_on_a_plane_of_more_than_4_gib():
+    """A 2D block of 2^29 FP64 values and more takes 64-bit offsets: the same
+    columns in a block half as wide, below the line, give the same V-cycle."""
+    import torch
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid((2050, 2050))
+    V = W.harmonic_potential(g, 100.0, (0.5, 0.5))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    R = torch.randn(g.n, 64, dtype=torch.float64, device="cuda", generator=gen)
+    out = []
+    for N in (64, 128):
+        Rn = R if N == 64 else torch.cat([R, R.flip(1)], dim=1).contiguous()
+        Z = torch.empty_like(Rn)
+        say(f"mg vcycle 2050^2 N={N}")
+        with ope.Context(g, V, N) as c:
+            ope.ope_set_multigrid(c.handle, True)
+            ope.ope_mg_vcycle(c.handle, Rn, Z)
+        out.append(Z)
+        del Rn
+    scale = float(out[0].abs().max())
+    assert float((out[1][:, :64] - out[0]).abs().max()) <= 1e-13 * scale
+    assert float((out[1][:, 64:].flip(1) - out[0]).abs().max()) <= 1e-13 * scale
