@@ -21,12 +21,18 @@
 // writes one partial per split (in FP64); a fixed-order column reduction
 // follows, so results are bitwise reproducible.
 //
-// Kernels by shape: wide operands (>= 128 columns, 16-byte rows) stage
-// panels in LDS with 128 x 128 work-group tiles (k_gram_lds, k_rowmm_lds);
-// narrow blocks (<= 32 columns) use k_gram_narrow (the four waves split the
-// rows of one 32 x 32 tile) and k_rowmm_narrow (128-row tiles through LDS);
-// the rest read their operands straight from global memory (k_gram,
-// k_gram_wide, k_rowmm).
+// Kernels by shape.  Grams: wide operands (>= 128 columns, 16-byte rows) stage
+// panels in LDS with 128 x 128 work-group tiles (k_gram_lds); narrow blocks
+// (<= 32 columns) use k_gram_narrow (the four waves split the rows of one
+// 32 x 32 tile); the rest read their operands straight from global memory
+// (k_gram, k_gram_wide).  Row products: k_rowmm_strip (M in LDS, 16 rows per
+// wave from global memory) for FP64 up to 112 columns or of any unaligned rows
+// and for FP32 up to 80; wide aligned rows k_rowmm_lds (both panels in LDS); of
+// the rest (BF16, and the FP32 widths that the strip is slower at) up to 32
+// columns k_rowmm_narrow and above k_rowmm.
+#include <algorithm>
+#include <type_traits>
+
 #include "ope_internal.h"
 
 namespace {
@@ -617,6 +623,189 @@ __global__ __launch_bounds__(256, RTW == RT2H ? 3 : 2) void k_rowmm_lds(const TI
   }
 }
 
+// Row-block products of the FP64 and FP32 kinds at any width (k_rowmm_strip).  A
+// work-group of eight waves holds a chunk of M in LDS (KC contraction indices x
+// 128 columns, two buffers) and walks over 128-row tiles; a wave takes 16 rows by
+// all 128 columns, so no other wave reads its rows and their values go from
+// global memory straight into the A operand.  The contraction order is free, so
+// a lane takes 16 consecutive bytes of its row (VPC values) and the VPC
+// instructions of a group use the k = VPC kr + e it then holds: 16 rows x 64
+// contiguous bytes per load, against 16 x 8 values of one MFMA.
+// With one source and N <= 2 KC both chunks of M stay in LDS for the whole
+// launch, and the waves run on with no barrier, one wave's epilogue under
+// another's matrix instructions; otherwise chunks stream through the two buffers
+// (one barrier per chunk of 128 matrix instructions per wave).  The next chunk's
+// loads are in flight while the current one is multiplied.
+// Columns in blocks of 16 (NB of them, so that a narrow M costs no idle
+// instructions).  VEC: rows split into whole aligned 16-byte chunks; else values
+// are loaded one by one.
+// Bound by memory up to about 64 columns and by the matrix cores above; what the
+// kernels before it lost was a whole 128-column tile of instructions for any
+// width above 32, rows re-read by the waves of the other column half, and a
+// barrier per panel.  One step's four products at 48^3, FP64: N = 17 113 -> 81 us,
+// 45 262 -> 146, 96 391 -> 324, 127 722 -> 538 (the full table is at the rule in
+// rowmm_t).
+template <typename TI>
+struct Strip {
+  static constexpr int VPC = 16 / (int)sizeof(TI);
+  static constexpr int XG = 8;                        // 16-byte groups of a row per chunk and lane
+  static constexpr int KC = XG * 4 * VPC;             // 64 (FP64) or 128 (FP32) contraction indices per chunk
+  // row stride of M in LDS: the four kr rows of an operand read fall in distinct
+  // banks (rows VPC apart: 2 * 136 * 2 words = 32 mod 64; 4 * 132 = 16 mod 64)
+  static constexpr int LD = sizeof(TI) == 8 ? 136 : 132;
+  static constexpr int BUF = KC * LD;                 // elements of a buffer
+};
+constexpr int ST_ROWS = 128;                          // rows per tile
+constexpr int ST_WG = 512;
+
+template <typename TI, int KIND, int NB, bool VEC>
+__global__ __launch_bounds__(ST_WG, 2) void k_rowmm_strip(const TI* X0, const TI* __restrict__ M0, const TI* X1,
+                                                          const TI* __restrict__ M1, const TI* Cm, double cbeta,
+                                                          double ascale, TI* Out, uint32_t n, uint32_t N,
+                                                          uint32_t ntiles, int want_colsq, int predicated,
+                                                          const OpeScalars* __restrict__ sc,
+                                                          double* __restrict__ part) {
+  using MK = Mk<KIND>;
+  using acc_t = typename MK::acc_t;
+  using S = Strip<TI>;
+  constexpr int VPC = S::VPC, XG = S::XG, KC = S::KC, LD = S::LD;
+  constexpr int MR = 128 / VPC;                       // 16-byte chunks per row of M
+  constexpr int MT = KC * MR / ST_WG;                 // of them per thread
+  static_assert(MT * ST_WG == KC * MR, "M chunks must divide the work-group");
+  typedef unsigned int Chunk __attribute__((ext_vector_type(4)));
+  union ChunkV {
+    Chunk c;
+    TI v[VPC];
+  };
+  extern __shared__ __align__(16) char strip_lds[];
+  TI* const ml = reinterpret_cast<TI*>(strip_lds);    // one or two buffers, then the column sums
+  if (rowmm_skip(predicated, sc)) return;
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t kr = lane >> 4, ci = lane & 15u;
+  const uint32_t col0 = blockIdx.y * 128u;
+  const uint32_t kc = (N + KC - 1) / KC;              // chunks per source
+  const uint32_t nch = X1 ? 2 * kc : kc;
+  const bool resident = nch <= 2;
+  auto load_x = [&](uint32_t tile, uint32_t c, ChunkV(&x)[XG]) {
+    const TI* X = c < kc ? X0 : X1;
+    const uint32_t kb = (c < kc ? c : c - kc) * KC, k0 = kb + VPC * kr;
+    const uint32_t row = tile * ST_ROWS + wave * 16u + ci;
+    const TI* p = X + (uint64_t)row * N + k0;
+    const bool rok = tile < ntiles && row < n;
+#pragma unroll
+    for (int t = 0; t < XG; ++t) {
+      if (kb + 4 * VPC * t >= N) break;               // uniform: nothing is left of the contraction
+      if constexpr (VEC) {
+        x[t].c = (rok && k0 + 4 * VPC * t < N) ? *reinterpret_cast<const Chunk*>(p + 4 * VPC * t) : Chunk{0u, 0u, 0u, 0u};
+      } else {
+#pragma unroll
+        for (int e = 0; e < VPC; ++e) x[t].v[e] = (rok && k0 + 4 * VPC * t + e < N) ? p[4 * VPC * t + e] : TI(0);
+      }
+    }
+  };
+  ChunkV mc[MT];
+  auto load_m = [&](uint32_t c) {
+    const TI* M = c < kc ? M0 : M1;
+    const uint32_t k0 = (c < kc ? c : c - kc) * KC;
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+      const uint32_t q = threadIdx.x + (uint32_t)ST_WG * u;
+      const uint32_t k = k0 + q / MR, col = col0 + (q % MR) * VPC;
+      const TI* p = M + (uint64_t)k * N + col;
+      if constexpr (VEC) {
+        mc[u].c = (k < N && col < N) ? *reinterpret_cast<const Chunk*>(p) : Chunk{0u, 0u, 0u, 0u};
+      } else {
+#pragma unroll
+        for (int e = 0; e < VPC; ++e) mc[u].v[e] = (k < N && col + e < N) ? p[e] : TI(0);
+      }
+    }
+  };
+  auto store_m = [&](uint32_t buf) {
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+      const uint32_t q = threadIdx.x + (uint32_t)ST_WG * u;
+      *reinterpret_cast<Chunk*>(ml + buf * S::BUF + (q / MR) * LD + (q % MR) * VPC) = mc[u].c;
+    }
+  };
+  double sq[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) sq[b] = 0.0;
+  ChunkV xc[XG], xn[XG];
+  load_x(blockIdx.x, 0, xn);
+  load_m(0);
+  store_m(0);
+  if (resident && nch == 2) {
+    load_m(1);
+    store_m(1);
+  }
+  __syncthreads();
+  uint32_t step = 0;                                  // streamed chunks so far
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    acc_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = zero_acc<acc_t>();
+    for (uint32_t c = 0; c < nch; ++c, ++step) {
+      const bool last = c + 1 == nch;
+      const uint32_t nt = last ? tile + gridDim.x : tile, ncx = last ? 0 : c + 1;    // the next chunk
+#pragma unroll
+      for (int t = 0; t < XG; ++t) xc[t] = xn[t];
+      load_x(nt, ncx, xn);
+      const bool more = !resident && nt < ntiles;     // uniform
+      if (more) load_m(ncx);
+      const TI* mb = ml + (resident ? c : (step & 1u)) * S::BUF + VPC * kr * LD + ci;
+      const uint32_t left = N - (c < kc ? c : c - kc) * KC;
+#pragma unroll
+      for (int t = 0; t < XG; ++t) {
+        if (4u * VPC * t >= left) break;              // uniform
+#pragma unroll
+        for (int e = 0; e < VPC; ++e) {
+          const TI av[1] = {xc[t].v[e]};
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            const TI bv[1] = {mb[(4 * VPC * t + e) * LD + 16 * b]};
+            acc[b] = mma<KIND, TI>(av, bv, acc[b]);
+          }
+        }
+      }
+      if (more) store_m((step + 1) & 1u);             // its last readers passed the previous barrier
+      if (!resident) __syncthreads();
+    }
+    // every read of this wave's rows is done: Out may alias X0 (in-place Step 4)
+    const uint32_t r0 = tile * ST_ROWS + wave * 16u;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t row = r0 + MK::drow(kr, r), col = col0 + 16u * b + ci;
+        if (row < n && col < N) {
+          const uint64_t o = (uint64_t)row * N + col;
+          TI v = (TI)(ascale * (double)acc[b][r]);
+          if (cbeta != 0.0) v += (TI)cbeta * Cm[o];
+          Out[o] = v;
+          sq[b] += (double)v * (double)v;
+        }
+      }
+  }
+  if (!want_colsq) return;
+  // per-column sums over the work-group's rows: lanes l, l^16, l^32, l^48 share a
+  // column, then the waves in order
+  double* red = reinterpret_cast<double*>(strip_lds);
+  __syncthreads();                                    // M is no longer read
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    sq[b] += __shfl_xor(sq[b], 16);
+    sq[b] += __shfl_xor(sq[b], 32);
+    if (kr == 0) red[wave * 128u + 16u * b + ci] = sq[b];
+  }
+  __syncthreads();
+  if (threadIdx.x < 16u * NB && col0 + threadIdx.x < N) {
+    double t = 0.0;
+#pragma unroll
+    for (uint32_t w = 0; w < ST_WG / 64; ++w) t += red[w * 128u + threadIdx.x];
+    part[(uint64_t)blockIdx.x * N + col0 + threadIdx.x] = t;
+  }
+}
+
 // Square FP64 products of N x N matrices (the small solves for large N):
 // D = alpha op(A) op(B) + beta C + gamma I, op = transpose when ta / tb is
 // set.  Work-group tile 64 x 64 (4 waves of 32 x 32), operands straight from
@@ -966,42 +1155,83 @@ hipError_t rowmm_t(ope_ctx* c, const TI* X0, const TI* M0, const TI* X1, const T
   // LDS-staged panels when every operand row splits into whole, aligned 16-byte chunks
   constexpr uint32_t VPC = 16 / (uint32_t)sizeof(TI);
   auto al16 = [](const void* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
+  const bool aligned = N % VPC == 0 && al16(X0) && al16(M0) && al16(X1) && al16(M1);
+  if constexpr (KIND != MK_BF16) {
+    // Which widths the strip takes, from the products of one step at 48^3 (us,
+    // strip / the kernel it would have had):
+    //   FP64 N = 8: 60/90, 17: 81/113, 33: 126/209, 45: 146/262, 64: 192/284,
+    //   96: 324/391, 112: 401/450, 127: 538/722, 128: 520/520, 192: 1274/1215,
+    //   256: 1688/1561; so all but aligned rows of more than 112.
+    //   FP32 N = 16: 75/84, 17: 111/88, 32: 105/100, 33: 151/165, 48: 142/183,
+    //   64: 187/227, 80: 240/258, 96: 303/298, 127: 519/503, 128: 447/362; an FP32
+    //   instruction takes half the time of an FP64 one, and the LDS reads of 16
+    //   rows per wave (one value per instruction) bound the strip from there on.
+    const bool strip = KIND == MK_F64 ? N <= 112 || !aligned : N <= 16 || (N > 32 && N <= 80);
+    if (strip) {
+      using S = Strip<TI>;
+      const uint32_t gc = (N + 127) / 128, ntiles = (n + ST_ROWS - 1) / ST_ROWS;
+      if (gc != 1 && (Out == X0 || Out == X1)) return hipErrorInvalidValue;   // in place needs one column tile
+      const uint32_t nch = (X1 ? 2 : 1) * ((N + S::KC - 1) / S::KC);
+      // one work-group per compute unit (two where one buffer of M suffices)
+      uint32_t gx = std::max(1u, (nch == 1 ? 512u : 256u) / gc);
+      if (gx > ntiles) gx = ntiles;
+      if (want_colsq && (int64_t)gx * N > c->part_cap) return hipErrorInvalidValue;
+      const size_t lds =
+          std::max<size_t>((size_t)std::min(nch, 2u) * S::BUF * sizeof(TI), ST_WG / 64 * 128 * sizeof(double));
+      ProfScope ps(c, OPE_KERNEL_ROWMM);
+      auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(gx, gc), dim3(ST_WG), lds, c->stream, X0, M0, X1, M1, Cm, cbeta, ascale, Out, n,
+                           N, ntiles, want_colsq, predicated, c->sc, c->part);
+      };
+      auto width = [&](auto v) {
+        constexpr bool VEC = decltype(v)::value;
+        switch (gc > 1 ? 8u : (N + 15) / 16) {
+          case 1: go(k_rowmm_strip<TI, KIND, 1, VEC>); break;
+          case 2: go(k_rowmm_strip<TI, KIND, 2, VEC>); break;
+          case 3: go(k_rowmm_strip<TI, KIND, 3, VEC>); break;
+          case 4: go(k_rowmm_strip<TI, KIND, 4, VEC>); break;
+          case 5: go(k_rowmm_strip<TI, KIND, 5, VEC>); break;
+          default:
+            if constexpr (KIND == MK_F64) {                   // FP32 ends at 80 columns
+              if (N <= 96) go(k_rowmm_strip<TI, KIND, 6, VEC>);
+              else if (N <= 112) go(k_rowmm_strip<TI, KIND, 7, VEC>);
+              else if constexpr (!VEC) go(k_rowmm_strip<TI, KIND, 8, VEC>);
+            }
+        }
+      };
+      if (aligned) width(std::true_type{});
+      else width(std::false_type{});
+      if (nparts) *nparts = gx;
+      return hipGetLastError();
+    }
+  }
   const bool narrow = N <= 32;
-  const bool lds = !narrow && N % VPC == 0 && al16(X0) && al16(M0) && al16(X1) && al16(M1);
+  const bool lds = !narrow && aligned;
   // FP64: 64-row tiles (132 VGPRs, three work-groups per compute unit, whose
   // output stores overlap the others' matrix-core work) measured 4% faster than
   // 128-row tiles (219 VGPRs, two) at 64^3, N = 128
-  const bool half = lds && KIND == MK_F64;
-  const uint32_t rt = narrow ? RTN : (lds ? (half ? RT2H : RT2) : RT);
+  const uint32_t rt = KIND == MK_F64 ? RT2H : narrow ? RTN : (lds ? RT2 : RT);
   const uint32_t gr = (n + rt - 1) / rt, gc = (N + CT - 1) / CT;
   if (gc != 1 && (Out == X0 || Out == X1)) return hipErrorInvalidValue;  // in place needs one column tile
   if (want_colsq && (int64_t)gr * N > c->part_cap) return hipErrorInvalidValue;
   ProfScope ps(c, OPE_KERNEL_ROWMM);
-  if (narrow) {
-    if (X1)
-      hipLaunchKernelGGL((k_rowmm_narrow<TI, KIND, 2>), dim3(gr), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta,
-                         ascale, Out, n, N, want_colsq, predicated, c->sc, c->part);
-    else
-      hipLaunchKernelGGL((k_rowmm_narrow<TI, KIND, 1>), dim3(gr), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta,
-                         ascale, Out, n, N, want_colsq, predicated, c->sc, c->part);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(gr, gc), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta, ascale, Out, n, N,
+                       want_colsq, predicated, c->sc, c->part);
+  };
+  if constexpr (KIND == MK_F64) {                             // aligned and wider than 112
+    if (X1) go(k_rowmm_lds<TI, KIND, 2, RT2H>);
+    else go(k_rowmm_lds<TI, KIND, 1, RT2H>);
+  } else if (narrow) {
+    if (X1) go(k_rowmm_narrow<TI, KIND, 2>);
+    else go(k_rowmm_narrow<TI, KIND, 1>);
   } else if (lds) {
-    auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(gr, gc), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta, ascale, Out, n, N,
-                         want_colsq, predicated, c->sc, c->part);
-    };
-    if (half) {
-      if (X1) go(k_rowmm_lds<TI, KIND, 2, RT2H>);
-      else go(k_rowmm_lds<TI, KIND, 1, RT2H>);
-    } else {
-      if (X1) go(k_rowmm_lds<TI, KIND, 2, RT2>);
-      else go(k_rowmm_lds<TI, KIND, 1, RT2>);
-    }
-  } else if (X1)
-    hipLaunchKernelGGL((k_rowmm<TI, KIND, 2>), dim3(gr, gc), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta,
-                       ascale, Out, n, N, want_colsq, predicated, c->sc, c->part);
-  else
-    hipLaunchKernelGGL((k_rowmm<TI, KIND, 1>), dim3(gr, gc), dim3(256), 0, c->stream, X0, M0, X1, M1, Cm, cbeta,
-                       ascale, Out, n, N, want_colsq, predicated, c->sc, c->part);
+    if (X1) go(k_rowmm_lds<TI, KIND, 2, RT2>);
+    else go(k_rowmm_lds<TI, KIND, 1, RT2>);
+  } else {
+    if (X1) go(k_rowmm<TI, KIND, 2>);
+    else go(k_rowmm<TI, KIND, 1>);
+  }
   if (nparts) *nparts = gr;
   return hipGetLastError();
 }

@@ -125,6 +125,36 @@ def test_update_exact_on_integers(m, N):
     assert np.array_equal(Un, U @ Z[:N] + Y @ Z[N:])
 
 
+@pytest.mark.parametrize("m", [(127, 1), (43, 3), (16, 8), (37, 29)])
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 33, 63, 64, 65, 80, 96, 97, 111, 112, 113, 114, 127])
+def test_row_products_at_the_edges_of_their_tiles(m, N):
+    """Row products at block widths around every 16-column step and row counts
+    around the 128-row tiles: two sources and in place (ope_update, exact on
+    integers), and one source with the column sums of squares (the residual
+    H U - U Lam; a sum of n N squares whose terms are each right to about
+    (n + N) eps of the operand norms, so 4 (n + N) eps |H| covers it)."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    rng = np.random.default_rng(N)
+    U = rng.integers(-4, 5, size=(g.n, N)).astype(np.float64)
+    Y = rng.integers(-4, 5, size=(g.n, N)).astype(np.float64)
+    Z = rng.integers(-3, 4, size=(2 * N, N)).astype(np.float64)
+    Q = W.initial_block(g.n, N, 3)
+    op = O.Operator(g.m, g.h, np.zeros(g.n))
+    HQ = O.apply_H(op, Q)
+    Lam = Q.T @ HQ
+    ref = np.linalg.norm(HQ - Q @ Lam)
+    say(f"row products m={m} N={N}")
+    with ope.Context(g, np.zeros(g.n), N) as ctx:
+        Ud = to_dev(U)
+        ope.ope_update(ctx.handle, Ud, to_dev(Y), to_dev(Z))
+        Un = to_host(Ud)
+        res, _, _ = ope.ope_residual(ctx.handle, to_dev(Q), N, want_ritz=False)
+    assert np.array_equal(Un, U @ Z[:N] + Y @ Z[N:])
+    bound = 4 * (g.n + N) * EPS * (4.0 * np.sum(1.0 / np.asarray(g.h) ** 2)) * np.sqrt(N)
+    assert abs(res * np.linalg.norm(Lam) - ref) <= bound      # the residual is relative to |Lam|
+
+
 @pytest.mark.parametrize("tau", [0.1, 40.0, 1e4])
 @pytest.mark.parametrize("exact", [True, False])
 def test_small_solve_matches_oracle(tau, exact):

@@ -99,6 +99,15 @@ def test_rowmm_kinds_exact_on_integers(kind, m, N):
     assert np.array_equal(Un, U64 + U64 @ Z64[:N] + Y64 @ Z64[N:])
 
 
+@pytest.mark.parametrize("m,N", [((43, 3), 1), ((43, 3), 15), ((43, 3), 16), ((127, 1), 17), ((16, 8), 32),
+                                 ((37, 29), 33), ((43, 3), 48), ((43, 3), 63), ((43, 3), 64), ((43, 3), 65),
+                                 ((37, 29), 79), ((37, 29), 80), ((16, 8), 81), ((37, 29), 84)])
+def test_rowmm_fp32_at_the_edges_of_its_tiles(m, N):
+    """Widths around every 16-column step and around the changes of kernel, row
+    counts around the 128-row tiles; exact on integers."""
+    test_rowmm_kinds_exact_on_integers(1, m, N)
+
+
 @pytest.mark.parametrize("mk", [lambda: W.harmonic_2d_32(), lambda: W.wells_3d(m=13, N=20, seed=3),
                                 lambda: W.wells_3d(m=20, N=128, seed=1)])
 def test_apply_h_fp32_within_rounding(mk):
