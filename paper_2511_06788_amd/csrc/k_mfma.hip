@@ -21,11 +21,10 @@
 // writes one partial per split (in FP64); a fixed-order column reduction
 // follows, so results are bitwise reproducible.
 //
-// Kernels by shape.  Grams: wide operands (>= 128 columns, 16-byte rows) stage
-// panels in LDS with 128 x 128 work-group tiles (k_gram_lds); narrow blocks
-// (<= 32 columns) use k_gram_narrow (the four waves split the rows of one
-// 32 x 32 tile); the rest read their operands straight from global memory
-// (k_gram, k_gram_wide).  Row products: k_rowmm_strip (M in LDS, 16 rows per
+// Kernels by shape.  Grams: straight from global memory into registers
+// (k_gram_rows), except wide aligned products of two FP32 blocks and wide BF16
+// ones, which stage panels in LDS with 128 x 128 work-group tiles (k_gram_lds).
+// Row products: k_rowmm_strip (M in LDS, 16 rows per
 // wave from global memory) for FP64 up to 112 columns or of any unaligned rows
 // and for FP32 up to 80; wide aligned rows k_rowmm_lds (both panels in LDS); of
 // the rest (BF16, and the FP32 widths that the strip is slower at) up to 32
@@ -92,195 +91,251 @@ __device__ __forceinline__ V zero_acc() {
   return z;
 }
 
-// Gram: work-group = 4 waves in a 2 x 2 arrangement over a 64 x 64 output
-// tile; each wave owns a 32 x 32 sub-tile (2 x 2 MFMA blocks).
-constexpr int GT = 64;      // work-group output tile edge
-constexpr int GW = 32;      // wave output tile edge
-
-template <typename TI, int KIND>
-__global__ __launch_bounds__(256) void k_gram(const TI* __restrict__ A, uint64_t lda, uint32_t na,
-                                              const TI* __restrict__ B, uint64_t ldb, uint32_t nb,
-                                              uint32_t rows, uint32_t rows_per_split, double* __restrict__ part) {
-  using M = Mk<KIND>;
-  using acc_t = typename M::acc_t;
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  const uint32_t i_base = blockIdx.y * GT + (wave >> 1) * GW;
-  const uint32_t j_base = blockIdx.x * GT + (wave & 1u) * GW;
-  const uint32_t ks = blockIdx.z;
-  const uint32_t kr = lane >> 4, ci = lane & 15u;
-  acc_t acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = zero_acc<acc_t>();
-  const uint32_t r0 = ks * rows_per_split;
-  const uint32_t r1 = min(rows, r0 + rows_per_split);
-  const bool ia0 = i_base + ci < na, ia1 = i_base + 16 + ci < na;
-  const bool jb0 = j_base + ci < nb, jb1 = j_base + 16 + ci < nb;
-  if (i_base < na && j_base < nb) {
-#pragma unroll 2
-    for (uint32_t p = r0; p < r1; p += M::KSTEP) {
-      TI a0[M::KPL], a1[M::KPL], b0[M::KPL], b1[M::KPL];
-#pragma unroll
-      for (int e = 0; e < M::KPL; ++e) {
-        const uint32_t row = p + kr * M::KPL + e;
-        const bool rok = row < r1;
-        const TI* ar = A + (uint64_t)row * lda + i_base + ci;
-        const TI* br = B + (uint64_t)row * ldb + j_base + ci;
-        a0[e] = (rok && ia0) ? ar[0] : TI(0);
-        a1[e] = (rok && ia1) ? ar[16] : TI(0);
-        b0[e] = (rok && jb0) ? br[0] : TI(0);
-        b1[e] = (rok && jb1) ? br[16] : TI(0);
-      }
-      acc[0][0] = mma<KIND, TI>(a0, b0, acc[0][0]);
-      acc[0][1] = mma<KIND, TI>(a0, b1, acc[0][1]);
-      acc[1][0] = mma<KIND, TI>(a1, b0, acc[1][0]);
-      acc[1][1] = mma<KIND, TI>(a1, b1, acc[1][1]);
-    }
-  }
-  double* out = part + (uint64_t)ks * na * nb;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t i = i_base + a * 16 + M::drow(kr, r);
-        const uint32_t j = j_base + b * 16 + ci;
-        if (i < na && j < nb) out[(uint64_t)i * nb + j] = (double)acc[a][b][r];
-      }
-}
-
-// Wide Grams (both sides >= 128 columns, FP32 and BF16 kinds): work-group tile
-// 128 x 128, each wave a 64 x 64 sub-tile (4 x 4 MFMA blocks), so every
-// operand load feeds four MFMAs instead of two.
-constexpr int GT2 = 128;
+constexpr int GT2 = 128;    // tile edge and wave tile edge of the Grams from LDS
 constexpr int GW2 = 64;
 
-template <typename TI, int KIND>
-__global__ __launch_bounds__(256) void k_gram_wide(const TI* __restrict__ A, uint64_t lda, uint32_t na,
-                                                   const TI* __restrict__ B, uint64_t ldb, uint32_t nb,
-                                                   uint32_t rows, uint32_t rows_per_split, double* __restrict__ part) {
-  using M = Mk<KIND>;
-  using acc_t = typename M::acc_t;
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  const uint32_t i_base = blockIdx.y * GT2 + (wave >> 1) * GW2;
-  const uint32_t j_base = blockIdx.x * GT2 + (wave & 1u) * GW2;
-  const uint32_t ks = blockIdx.z;
-  const uint32_t kr = lane >> 4, ci = lane & 15u;
-  acc_t acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = zero_acc<acc_t>();
-  const uint32_t r0 = ks * rows_per_split;
-  const uint32_t r1 = min(rows, r0 + rows_per_split);
-  bool iok[4], jok[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    iok[a] = i_base + a * 16 + ci < na;
-    jok[a] = j_base + a * 16 + ci < nb;
+// Grams straight from global memory (k_gram_rows).  The four waves of a
+// work-group take the contraction steps w, w + 4, ... of its rows, and every
+// wave holds all the 16 x 16 blocks of the output tile: a value is loaded once
+// per wave and feeds a whole row or column of blocks from its register (for
+// A^T A as both operands), with no LDS and no barrier in the loop.  The loads of
+// the next groups of U steps are in flight while one is multiplied.  The waves' tiles
+// are summed in LDS in wave order at the end.  Bound by memory up to about 64
+// columns of FP64 and by the matrix cores above; the kernels before it loaded
+// every value once per block that used it, computed both triangles and reduced
+// twice as many partials in two launches.  A^T A at 48^3, FP64 (us, before ->
+// after, with the sum of the partials): N = 17 19 -> 14, 45 41 -> 20, 96 120 -> 33,
+// 128 69 -> 57, 161 272 -> 115, 256 292 -> 176, 512 984 -> 652; two blocks 96
+// 119 -> 47.
+//   G_SAME   A^T A, the NB (NB + 1) / 2 blocks on and above the block diagonal
+//   G_UPPER  A^T B known to be symmetric, the same blocks
+//   G_FULL   any A^T B in NB x NB tiles
+// Loads have a uniform base and a fixed 32-bit offset per lane and block (O; 64
+// bits where 32 rows may span 2^31 bytes).  Columns past the edge read the last
+// column: their values reach only output that is not stored.
+enum { G_SAME = 0, G_UPPER = 1, G_FULL = 2 };
+
+// Split and tile of a work-group (grid: splits x tiles, the tiles all of them or
+// those on and above the diagonal).  With the splits a multiple of 8 the tiles of
+// one split run on one XCD (work-groups a multiple of 8 apart), whose L2 then
+// serves the rows they share.
+__device__ __forceinline__ void gram_place(uint32_t ntj, int upper, uint32_t* ks, uint32_t* ti, uint32_t* tj) {
+  const uint32_t nt = gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
+  uint32_t t = blockIdx.y;
+  *ks = blockIdx.x;
+  if (nt > 1 && gridDim.x % 8u == 0) {
+    *ks = lin / (8u * nt) * 8u + lin % 8u;
+    t = lin / 8u % nt;
   }
-  if (i_base < na && j_base < nb) {
-    for (uint32_t p = r0; p < r1; p += M::KSTEP) {
-      TI av[4][M::KPL], bv[4][M::KPL];
-#pragma unroll
-      for (int e = 0; e < M::KPL; ++e) {
-        const uint32_t row = p + kr * M::KPL + e;
-        const bool rok = row < r1;
-        const TI* ar = A + (uint64_t)row * lda + i_base + ci;
-        const TI* br = B + (uint64_t)row * ldb + j_base + ci;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          av[a][e] = (rok && iok[a]) ? ar[16 * a] : TI(0);
-          bv[a][e] = (rok && jok[a]) ? br[16 * a] : TI(0);
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = mma<KIND, TI>(av[a], bv[b], acc[a][b]);
-    }
+  if (!upper) {
+    *ti = t / ntj;
+    *tj = t % ntj;
+    return;
   }
-  double* out = part + (uint64_t)ks * na * nb;
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t i = i_base + a * 16 + M::drow(kr, r);
-        const uint32_t j = j_base + b * 16 + ci;
-        if (i < na && j < nb) out[(uint64_t)i * nb + j] = (double)acc[a][b][r];
-      }
+  uint32_t a = 0;
+  while (t >= ntj - a) t -= ntj - a++;
+  *ti = a;
+  *tj = a + t;
 }
 
-// Narrow Grams (both sides at most 32 columns): one 32 x 32 output tile (2 x 2
-// MFMA blocks) per work-group, and the four waves split the work-group's rows
-// (wave w takes contraction steps w, w + 4, ...) instead of sharing a 64 x 64
-// tile that such a Gram would leave three quarters idle.  The waves' tiles are
-// summed in LDS in wave order.
-template <typename TI, int KIND>
-__global__ __launch_bounds__(256) void k_gram_narrow(const TI* __restrict__ A, uint64_t lda, uint32_t na,
-                                                     const TI* __restrict__ B, uint64_t ldb, uint32_t nb,
-                                                     uint32_t rows, uint32_t rows_per_split,
-                                                     double* __restrict__ part) {
+template <typename TI, int KIND, int NB, int MODE>
+struct GramTile {
+  static constexpr int KPL = Mk<KIND>::KPL;
+  static constexpr int NBLK = MODE == G_FULL ? NB * NB : NB * (NB + 1) / 2;
+  static constexpr int LB = MODE == G_SAME ? NB : 2 * NB;                     // values of a step per lane and row
+  static constexpr int SB = LB * KPL * (int)sizeof(TI);                       // its bytes
+  static constexpr int ACC = NBLK * (KIND == MK_F64 ? 8 : 4);                 // accumulator registers
+  // steps per group: 128 bytes per lane, at most four; where the accumulators
+  // leave one wave per SIMD, one step per group and more groups in flight instead
+  static constexpr int U0 = SB >= 128 ? 1 : (128 + SB - 1) / SB > 4 ? 4 : (128 + SB - 1) / SB;
+  static constexpr int OCC = ACC + U0 * SB / 2 <= 200 ? 2 : 1;                // work-groups per compute unit
+  static constexpr int U = OCC == 2 ? U0 : 1;
+  // (36 FP64 blocks do not fit the 256 accumulation registers: four of them move
+  // in and out by every step, 104 us for A^T A at 64^3, N = 128, of 61 for the
+  // matrix instructions alone)
+  static constexpr int FIT = (352 - ACC) / (SB / 4);
+  static constexpr int DEPTH = OCC == 2 || FIT < 2 ? 2 : FIT > 4 ? 4 : FIT;   // groups in registers
+  static_assert(MODE != G_FULL || NB > 4 || OCC == 2, "gram_t plans two tiles per compute unit");
+  // blocks of tile row a: columns first(a) .. NB - 1, numbered from at(a, first(a))
+  static __device__ constexpr int first(int a) { return MODE == G_FULL ? 0 : a; }
+  static __device__ constexpr int at(int a, int b) { return MODE == G_FULL ? a * NB + b : a * NB - a * (a - 1) / 2 + b - a; }
+};
+
+template <typename TI, int KIND, int NB, int MODE, typename O>
+__global__ __launch_bounds__(256, (GramTile<TI, KIND, NB, MODE>::OCC)) void k_gram_rows(
+    const TI* __restrict__ A, uint64_t lda, uint32_t na, const TI* __restrict__ B, uint64_t ldb, uint32_t nb,
+    uint32_t rows, uint32_t rows_per_split, uint32_t ntj, int upper, double* __restrict__ part) {
   using M = Mk<KIND>;
+  using T = GramTile<TI, KIND, NB, MODE>;
   using acc_t = typename M::acc_t;
-  __shared__ double red[3][2][2][4][64];
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  const uint32_t ks = blockIdx.x;
+  constexpr int KPL = M::KPL, U = T::U, NBLK = T::NBLK;
+  constexpr bool TWO = MODE != G_SAME;
+  __shared__ double red[4][NB][4][64];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   const uint32_t kr = lane >> 4, ci = lane & 15u;
-  acc_t acc[2][2];
+  uint32_t ks, ti, tj;
+  gram_place(ntj, upper, &ks, &ti, &tj);
+  const uint32_t i0 = ti * (16u * NB), j0 = tj * (16u * NB);
+  const uint32_t r0 = (uint32_t)min((uint64_t)rows, (uint64_t)ks * rows_per_split);
+  const uint32_t r1 = r0 + min(rows - r0, rows_per_split);
+  O ao[NB], bo[TWO ? NB : 1];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int x = 0; x < NB; ++x) ao[x] = min(i0 + 16u * x + ci, na - 1u);
+  if constexpr (TWO) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = zero_acc<acc_t>();
-  const uint32_t r0 = ks * rows_per_split;
-  const uint32_t r1 = min(rows, r0 + rows_per_split);
-  const bool ia0 = ci < na, ia1 = 16 + ci < na;
-  const bool jb0 = ci < nb, jb1 = 16 + ci < nb;
-#pragma unroll 4
-  for (uint32_t p = r0 + wave * M::KSTEP; p < r1; p += 4 * M::KSTEP) {
-    TI a0[M::KPL], a1[M::KPL], b0[M::KPL], b1[M::KPL];
+    for (int x = 0; x < NB; ++x) bo[x] = min(j0 + 16u * x + ci, nb - 1u);
+  }
+  acc_t acc[NBLK];
 #pragma unroll
-    for (int e = 0; e < M::KPL; ++e) {
-      const uint32_t row = p + kr * M::KPL + e;
-      const bool rok = row < r1;
-      const TI* ar = A + (uint64_t)row * lda + ci;
-      const TI* br = B + (uint64_t)row * ldb + ci;
-      a0[e] = (rok && ia0) ? ar[0] : TI(0);
-      a1[e] = (rok && ia1) ? ar[16] : TI(0);
-      b0[e] = (rok && jb0) ? br[0] : TI(0);
-      b1[e] = (rok && jb1) ? br[16] : TI(0);
+  for (int q = 0; q < NBLK; ++q) acc[q] = zero_acc<acc_t>();
+  struct Vals {
+    TI a[U][NB][KPL], b[U][TWO ? NB : 1][KPL];
+  };
+  const uint64_t sa = (uint64_t)kr * KPL * lda, sb = (uint64_t)kr * KPL * ldb;
+  auto load = [&](auto tail, uint32_t g, Vals& v) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t st = ((g * U + u) * 4u + wave) * M::KSTEP, p = r0 + st;  // uniform
+#pragma unroll
+      for (int e = 0; e < KPL; ++e) {
+        uint64_t ra = sa, rb = sb;
+        bool ok = true;
+        const TI *pa = A + (uint64_t)(p + e) * lda, *pb = B + (uint64_t)(p + e) * ldb;
+        if constexpr (decltype(tail)::value) {
+          ok = st + kr * KPL + e < r1 - r0;
+          if (!ok) {                                  // any row of the split, and zero instead of its value
+            pa = A + (uint64_t)r0 * lda;
+            pb = B + (uint64_t)r0 * ldb;
+            ra = rb = 0;
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          const TI t = pa[(O)ra + ao[x]];
+          v.a[u][x][e] = ok ? t : TI(0);
+        }
+        if constexpr (TWO) {
+#pragma unroll
+          for (int x = 0; x < NB; ++x) {
+            const TI t = pb[(O)rb + bo[x]];
+            v.b[u][x][e] = ok ? t : TI(0);
+          }
+        }
+      }
     }
-    acc[0][0] = mma<KIND, TI>(a0, b0, acc[0][0]);
-    acc[0][1] = mma<KIND, TI>(a0, b1, acc[0][1]);
-    acc[1][0] = mma<KIND, TI>(a1, b0, acc[1][0]);
-    acc[1][1] = mma<KIND, TI>(a1, b1, acc[1][1]);
+  };
+  auto mul = [&](const Vals& v) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = T::first(i); j < NB; ++j) {
+          if constexpr (TWO) acc[T::at(i, j)] = mma<KIND, TI>(v.a[u][i], v.b[u][j], acc[T::at(i, j)]);
+          else acc[T::at(i, j)] = mma<KIND, TI>(v.a[u][i], v.a[u][j], acc[T::at(i, j)]);
+        }
+  };
+  // groups of 4 U steps (U per wave); the last one may end before its last row
+  constexpr uint32_t GR = 4u * U * M::KSTEP;
+  const uint32_t ng = (r1 - r0) / GR;
+  // a group's registers are loaded again as soon as it is multiplied; with two
+  // groups only, that form spills and the other group is loaded before
+  constexpr uint32_t D = T::DEPTH;
+  constexpr bool BEFORE = T::OCC == 1 && D == 2;
+  Vals v[D];
+  if constexpr (BEFORE) {
+    if (ng > 0) load(std::false_type{}, 0, v[0]);
+    for (uint32_t g = 0; g < ng; g += 2) {
+      if (g + 1 < ng) load(std::false_type{}, g + 1, v[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(v[0]);
+      if (g + 1 < ng) {
+        if (g + 2 < ng) load(std::false_type{}, g + 2, v[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(v[1]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (uint32_t d = 0; d < D; ++d)
+      if (d < ng) load(std::false_type{}, d, v[d]);
+    for (uint32_t g = 0; g < ng; g += D) {
+#pragma unroll
+      for (uint32_t d = 0; d < D; ++d) {
+        if (g + d >= ng) break;                       // uniform, as the next
+        __builtin_amdgcn_sched_barrier(0);
+        mul(v[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (g + d + D < ng) load(std::false_type{}, g + d + D, v[d]);
+      }
+    }
   }
-  if (wave > 0) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave - 1][a][b][r][lane] = (double)acc[a][b][r];
+  if (r0 + ng * GR < r1) {
+    load(std::true_type{}, ng, v[0]);
+    mul(v[0]);
   }
-  __syncthreads();
-  if (wave != 0) return;
   double* out = part + (uint64_t)ks * na * nb;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NB; ++a) {                      // the blocks of tile row a over the four waves
+    if (a > 0) __syncthreads();
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = T::first(a); b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t i = a * 16 + M::drow(kr, r);
-        const uint32_t j = b * 16 + ci;
-        const double v = (double)acc[a][b][r] + red[0][a][b][r][lane] + red[1][a][b][r][lane] + red[2][a][b][r][lane];
-        if (i < na && j < nb) out[(uint64_t)i * nb + j] = v;
-      }
+      for (int r = 0; r < 4; ++r) red[wave][b][r][lane] = (double)acc[T::at(a, b)][r];
+    __syncthreads();
+    const uint32_t i = i0 + 16u * a + M::drow(kr, (int)wave);
+#pragma unroll
+    for (int b = T::first(a); b < NB; ++b) {
+      const uint32_t j = j0 + 16u * b + ci;
+      const double v = red[0][b][wave][lane] + red[1][b][wave][lane] + red[2][b][wave][lane] + red[3][b][wave][lane];
+      if (i < na && j < nb) out[(uint64_t)i * nb + j] = v;
+    }
+  }
+}
+
+// Sum of the ks partial Grams, 64 entries (four rows of one 16 x 16 block) per
+// work-group of 16 waves that split the partials, added in a fixed order.  UPPER:
+// the blocks on and above the block diagonal hold values; the others mirror them.
+// A launch of few loads in flight is bound by their latency, so each thread keeps
+// eight.
+template <bool UPPER>
+__global__ __launch_bounds__(1024) void k_gram_sum(const double* __restrict__ part, uint32_t ks, uint32_t na,
+                                                   uint32_t nb, double* __restrict__ out) {
+  __shared__ double red[16][64];
+  const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t nbj = (nb + 15u) / 16u;
+  uint32_t a = 0, b = blockIdx.x >> 2;
+  if constexpr (UPPER) {
+    while (b >= nbj - a) b -= nbj - a++;
+    b += a;
+  } else {
+    a = b / nbj;
+    b %= nbj;
+  }
+  const uint32_t i = 16u * a + 4u * (blockIdx.x & 3u) + (lane >> 4), j = 16u * b + (lane & 15u);
+  const bool ok = i < na && j < nb;
+  const uint64_t o = (uint64_t)i * nb + j, sz = (uint64_t)na * nb;
+  double s = 0.0;
+  if (ok) {
+    const uint32_t n = ks > w ? (ks - w + 15u) / 16u : 0u;      // partials w, w + 16, ...
+    const double* p = part + w * sz + o;
+    uint32_t k = 0;
+    for (; k + 8 <= n; k += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[(uint64_t)(k + u) * 16u * sz];
+      s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    }
+    for (; k < n; ++k) s += p[(uint64_t)k * 16u * sz];
+  }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w != 0 || !ok) return;
+  double t = red[0][lane];
+#pragma unroll
+  for (int u = 1; u < 16; ++u) t += red[u][lane];
+  out[o] = t;
+  if (UPPER && a != b) out[(uint64_t)j * nb + i] = t;
 }
 
 // Row-block products Out = cbeta Cm + ascale (X0 M0 + X1 M1).  Work-group =
@@ -877,21 +932,15 @@ __global__ __launch_bounds__(256) void k_sqmm(const double* __restrict__ A, int 
   if (threadIdx.x == 0) res[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
 }
 
-// Wide Grams from LDS (both sides >= 128 columns, 16-byte aligned rows):
-// work-group tile 128 x 128, each wave a 64 x 64 sub-tile (4 x 4 MFMA blocks).
-// The work-group stages KC-row panels of both operands in LDS (double
+// Wide FP32 and BF16 Grams from LDS (both sides >= 128 columns, 16-byte aligned
+// rows): work-group tile 128 x 128, each wave a 64 x 64 sub-tile (4 x 4 MFMA
+// blocks).  The work-group stages KC-row panels of both operands in LDS (double
 // buffered; the next panel's 16-byte loads are in flight while the current one
 // is consumed), so each operand element crosses L2 once per work-group
-// instead of once per wave: at the MFMA rate the 64 x 64-tile Gram needs more
+// instead of once per wave: at these instructions' rate smaller tiles need more
 // L1-to-L2 traffic than the chip sustains.
-//
-// A Gram of one block with itself (X^T X) that fits one tile (at most 128
-// columns) runs as k_gram_lds_diag, which stages one panel and computes only
-// the 36 MFMA blocks on or above the block diagonal (nine per wave, each
-// block off the diagonal also written mirrored) instead of 64: the matrix
-// cores do 36/64 of the work.
 
-// Panel staging shared by the two kernels: the 16-byte chunks of KC rows
+// Panel staging: the 16-byte chunks of KC rows
 // starting at row p of columns c0 .. c0 + 127 of X (zero outside the rows
 // [.., r1) and the columns [.., nc)).
 template <typename TI, int KC>
@@ -925,7 +974,8 @@ struct PanelChunks {
 template <typename TI, int KIND>
 __global__ __launch_bounds__(256) void k_gram_lds(const TI* __restrict__ A, uint64_t lda, uint32_t na,
                                                   const TI* __restrict__ B, uint64_t ldb, uint32_t nb,
-                                                  uint32_t rows, uint32_t rows_per_split, double* __restrict__ part) {
+                                                  uint32_t rows, uint32_t rows_per_split, uint32_t ntj, int upper,
+                                                  double* __restrict__ part) {
   using M = Mk<KIND>;
   using acc_t = typename M::acc_t;
   constexpr int KC = PanelRows<KIND>::KC;
@@ -933,11 +983,12 @@ __global__ __launch_bounds__(256) void k_gram_lds(const TI* __restrict__ A, uint
   __shared__ __align__(16) TI pb[2][KC][GT2];
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint32_t wi = (wave >> 1) * GW2, wj = (wave & 1u) * GW2;     // the wave's sub-tile in the tile
-  const uint32_t i0 = blockIdx.y * GT2, j0 = blockIdx.x * GT2;
-  const uint32_t ks = blockIdx.z;
+  uint32_t ks, ti, tj;
+  gram_place(ntj, upper, &ks, &ti, &tj);
+  const uint32_t i0 = ti * GT2, j0 = tj * GT2;
   const uint32_t kr = lane >> 4, ci = lane & 15u;
-  const uint32_t r0 = ks * rows_per_split;
-  const uint32_t r1 = min(rows, r0 + rows_per_split);
+  const uint32_t r0 = (uint32_t)min((uint64_t)rows, (uint64_t)ks * rows_per_split);
+  const uint32_t r1 = r0 + min(rows - r0, rows_per_split);
   acc_t acc[4][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -994,158 +1045,134 @@ __global__ __launch_bounds__(256) void k_gram_lds(const TI* __restrict__ A, uint
       }
 }
 
-// The nine 16 x 16 blocks (a, b), a <= b, of a diagonal tile that wave w
-// computes: together the 36 blocks of the upper block triangle of 8 x 8.
-__device__ __forceinline__ void sym_blocks(uint32_t w, uint32_t (&oa)[9], uint32_t (&ob)[9]) {
-  constexpr unsigned char T[4][9][2] = {
-      {{0, 0}, {0, 1}, {0, 2}, {0, 3}, {0, 4}, {0, 5}, {0, 6}, {0, 7}, {1, 1}},
-      {{1, 2}, {1, 3}, {1, 4}, {1, 5}, {1, 6}, {1, 7}, {2, 2}, {2, 3}, {2, 4}},
-      {{2, 5}, {2, 6}, {2, 7}, {3, 3}, {3, 4}, {3, 5}, {3, 6}, {3, 7}, {4, 4}},
-      {{4, 5}, {4, 6}, {4, 7}, {5, 5}, {5, 6}, {5, 7}, {6, 6}, {6, 7}, {7, 7}}};
-#pragma unroll
-  for (int p = 0; p < 9; ++p) {
-    uint32_t a = T[0][p][0], b = T[0][p][1];
-    if (w == 1u) a = T[1][p][0], b = T[1][p][1];
-    if (w == 2u) a = T[2][p][0], b = T[2][p][1];
-    if (w == 3u) a = T[3][p][0], b = T[3][p][1];
-    oa[p] = 16u * a;
-    ob[p] = 16u * b;
+// Splits of the rows over a Gram's work-groups (nt tiles, occ of them per compute
+// unit at a time).  One tile: one work-group per place.  Several: a multiple of 8
+// (see gram_place), the k per XCD for which whole rounds of its 32 occ places
+// lose least; cost is the time relative to a tile's work of one round.  Returns
+// the splits, at most max_ks.
+int64_t gram_splits(int64_t nt, int64_t occ, int64_t max_ks, double* cost) {
+  int64_t best = std::min<int64_t>(max_ks, std::max<int64_t>(1, 256 * occ / nt));
+  *cost = (double)((nt * best + 256 * occ - 1) / (256 * occ) * occ) / (double)best;
+  if (nt == 1) return best;
+  double at = 0;
+  for (int64_t k = 1; k <= 64 && 8 * k <= max_ks; ++k) {
+    const double v = (double)((nt * k + 32 * occ - 1) / (32 * occ) * occ) / (double)(8 * k);
+    if (k == 1 || v < 0.98 * at) best = 8 * k, *cost = at = v;
   }
-}
-
-// A symmetric A^T B for at most 128 columns (X^T X, or TWO: A != B known to
-// give a symmetric product): the one tile, split blockIdx.z.
-template <typename TI, int KIND, bool TWO>
-__global__ __launch_bounds__(256) void k_gram_lds_diag(const TI* __restrict__ A, uint64_t lda, uint32_t na,
-                                                       const TI* __restrict__ B, uint64_t ldb,
-                                                       uint32_t rows, uint32_t rows_per_split,
-                                                       double* __restrict__ part) {
-  using M = Mk<KIND>;
-  using acc_t = typename M::acc_t;
-  constexpr int KC = PanelRows<KIND>::KC;
-  __shared__ __align__(16) TI pa[2][KC][GT2];
-  __shared__ __align__(16) TI pb[TWO ? 2 : 1][TWO ? KC : 1][TWO ? GT2 : 1];
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-  const uint32_t i0 = blockIdx.x * GT2;
-  const uint32_t ks = blockIdx.z;
-  const uint32_t kr = lane >> 4, ci = lane & 15u;
-  const uint32_t r0 = ks * rows_per_split;
-  const uint32_t r1 = min(rows, r0 + rows_per_split);
-  uint32_t oa[9], ob[9];
-  sym_blocks(wave, oa, ob);
-  acc_t acc[9];
-#pragma unroll
-  for (int q = 0; q < 9; ++q) acc[q] = zero_acc<acc_t>();
-  PanelChunks<TI, KC> ca, cb;
-  const uint32_t npan = (r1 > r0) ? (r1 - r0 + KC - 1) / KC : 0;
-  if (npan > 0) {
-    ca.load(A, lda, na, i0, r0, r1);
-    ca.store(pa[0]);
-    if constexpr (TWO) {
-      cb.load(B, ldb, na, i0, r0, r1);
-      cb.store(pb[0]);
-    }
-  }
-  __syncthreads();
-  for (uint32_t t = 0; t < npan; ++t) {
-    const int buf = (int)(t & 1u);
-    if (t + 1 < npan) {
-      ca.load(A, lda, na, i0, r0 + (t + 1) * KC, r1);
-      if constexpr (TWO) cb.load(B, ldb, na, i0, r0 + (t + 1) * KC, r1);
-    }
-#pragma unroll
-    for (int kk = 0; kk < KC / M::KSTEP; ++kk) {
-#pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        TI av[M::KPL], bv[M::KPL];
-#pragma unroll
-        for (int e = 0; e < M::KPL; ++e) {
-          const uint32_t row = kk * M::KSTEP + kr * M::KPL + e;
-          av[e] = pa[buf][row][oa[q] + ci];
-          if constexpr (TWO) bv[e] = pb[buf][row][ob[q] + ci];
-          else bv[e] = pa[buf][row][ob[q] + ci];
-        }
-        acc[q] = mma<KIND, TI>(av, bv, acc[q]);
-      }
-    }
-    if (t + 1 < npan) {
-      ca.store(pa[buf ^ 1]);
-      if constexpr (TWO) cb.store(pb[buf ^ 1]);
-    }
-    __syncthreads();
-  }
-  double* out = part + (uint64_t)ks * na * na;
-#pragma unroll
-  for (int q = 0; q < 9; ++q)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t i = i0 + oa[q] + M::drow(kr, r);
-      const uint32_t j = i0 + ob[q] + ci;
-      if (i < na && j < na) {
-        out[(uint64_t)i * na + j] = (double)acc[q][r];
-        if (oa[q] != ob[q]) out[(uint64_t)j * na + i] = (double)acc[q][r];
-      }
-    }
+  return best;
 }
 
 template <typename TI, int KIND>
 hipError_t gram_t(ope_ctx* c, const TI* A, int64_t lda, int na, const TI* B, int64_t ldb, int nb, int64_t rows,
                   double* out, bool symmetric = false) {
-  // 128 x 128 tiles from LDS when both sides are wide and rows split into
-  // whole 16-byte chunks; else the wide tile from global memory (FP32 and
-  // BF16 kinds), else 64 x 64 tiles
   constexpr int64_t VPC = 16 / (int64_t)sizeof(TI);
-  const bool lds = na >= GT2 && nb >= GT2 && (reinterpret_cast<uintptr_t>(A) % 16) == 0 &&
-                   (reinterpret_cast<uintptr_t>(B) % 16) == 0 && lda % VPC == 0 && ldb % VPC == 0 &&
-                   na % VPC == 0 && nb % VPC == 0;
-  const bool wide = lds || (KIND != MK_F64 && na >= GT2 && nb >= GT2);
-  // a Gram of one block with itself in one tile: the MFMA blocks on and
-  // above the block diagonal (with several tiles the two launches of fewer
-  // work-groups each were measured slower than the full product)
-  const bool same = A == B && lda == ldb;
-  const bool sym = lds && (same || symmetric) && na == nb && na <= GT2;
-  const int tile = wide ? GT2 : GT;
-  const uint32_t ti = (uint32_t)((na + tile - 1) / tile), tj = (uint32_t)((nb + tile - 1) / tile);
-  // about 1024 work-groups in total (512, two per CU, for the LDS kernels),
-  // within the partial buffer
-  int64_t ks = (lds ? 512 : 1024) / (int64_t)(ti * tj);
-  if (ks < 1) ks = 1;
+  // A^T A (or a product known to be symmetric): the blocks on and above the diagonal
+  const bool same = A == B && lda == ldb && na == nb;
+  const bool upper = na == nb && (same || symmetric);
   const int64_t max_ks = c->part_cap / ((int64_t)na * nb);
-  if (ks > max_ks) ks = max_ks;
-  if (ks < 1) return hipErrorInvalidValue;
-  const int64_t kstep = Mk<KIND>::KSTEP;
-  int64_t rps = (rows + ks - 1) / ks;
-  rps = ((rps + kstep - 1) / kstep) * kstep;
-  if (rps < kstep) rps = kstep;
-  ks = (rows + rps - 1) / rps;
-  if (ks < 1) ks = 1;
-  const bool narrow = na <= 32 && nb <= 32;    // one 32 x 32 tile; all four waves split the rows
+  if (max_ks < 1) return hipErrorInvalidValue;
+  auto tiles = [&](int edge, uint32_t* tj) {
+    const uint32_t ti = (uint32_t)((na + edge - 1) / edge);
+    *tj = (uint32_t)((nb + edge - 1) / edge);
+    return upper ? *tj * (*tj + 1) / 2 : ti * *tj;
+  };
+  uint32_t tj = 1;
+  // Tiles of 128 staged in LDS, or smaller ones from registers.  From registers
+  // each tile loads its own columns through L2 (about 7 TB/s of it at 64 x 64
+  // tiles), which FP64 instructions leave time for and faster ones do not.
+  // Products at 48^3, LDS / registers, us:
+  //   FP64 two blocks N = 128 93/75, 256 309/290, 512 1021/981; A^T A 256 258/176,
+  //   512 919/652 (ten tiles fill the chip badly): registers at every width.
+  //   FP32 two blocks 128 57/78, 192 140/84, 256 148/176, 320 297/289, 512 508/706,
+  //   so by the tiles each needs (a 128 tile costs 1.6 times a 96 one); A^T A 192
+  //   112/75, 256 138/129, 384 293/193, 512 502/380: registers.
+  //   BF16 two blocks 128 39/59, 256 76/86; A^T A 128 46/23 (one tile), 256 62/63.
+  const bool aligned = (reinterpret_cast<uintptr_t>(A) % 16) == 0 && (reinterpret_cast<uintptr_t>(B) % 16) == 0 &&
+                       lda % VPC == 0 && ldb % VPC == 0 && na % VPC == 0 && nb % VPC == 0;
+  const bool lds = KIND != MK_F64 && aligned && na >= GT2 && nb >= GT2 &&
+                   (KIND == MK_F32 ? !upper && 8 * tiles(GT2, &tj) < 5 * tiles(96, &tj) : !(upper && na == GT2));
+  int64_t ks = 1, rps = 0;
+  auto split = [&](int64_t want, int64_t group) {     // into whole groups of rows
+    rps = ((rows + want - 1) / want + group - 1) / group * group;
+    const int64_t used = (rows + rps - 1) / rps;      // later splits would hold no rows
+    rps = std::min<int64_t>(rps, 0xffffffff);
+    ks = want % 8 == 0 ? std::min(want, (used + 7) / 8 * 8) : used;
+  };
   {
     ProfScope ps(c, OPE_KERNEL_GRAM);
-    if (narrow)
-      hipLaunchKernelGGL((k_gram_narrow<TI, KIND>), dim3((uint32_t)ks), dim3(256), 0, c->stream, A, (uint64_t)lda,
-                         (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows, (uint32_t)rps, c->part);
-    else if (sym && same)
-      hipLaunchKernelGGL((k_gram_lds_diag<TI, KIND, false>), dim3(1, 1, (uint32_t)ks), dim3(256), 0, c->stream, A,
-                         (uint64_t)lda, (uint32_t)na, A, (uint64_t)lda, (uint32_t)rows, (uint32_t)rps, c->part);
-    else if (sym)
-      hipLaunchKernelGGL((k_gram_lds_diag<TI, KIND, true>), dim3(1, 1, (uint32_t)ks), dim3(256), 0, c->stream, A,
-                         (uint64_t)lda, (uint32_t)na, B, (uint64_t)ldb, (uint32_t)rows, (uint32_t)rps, c->part);
-    else if (lds)
-      hipLaunchKernelGGL((k_gram_lds<TI, KIND>), dim3(tj, ti, (uint32_t)ks), dim3(256), 0, c->stream, A,
-                         (uint64_t)lda, (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows, (uint32_t)rps,
-                         c->part);
-    else if (wide)
-      hipLaunchKernelGGL((k_gram_wide<TI, KIND>), dim3(tj, ti, (uint32_t)ks), dim3(256), 0, c->stream, A,
-                         (uint64_t)lda, (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows, (uint32_t)rps,
-                         c->part);
-    else
-      hipLaunchKernelGGL((k_gram<TI, KIND>), dim3(tj, ti, (uint32_t)ks), dim3(256), 0, c->stream, A, (uint64_t)lda,
-                         (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows, (uint32_t)rps, c->part);
+    double cost = 0;
+    auto go = [&](auto nbt, auto modet, auto off) {
+      constexpr int NB = decltype(nbt)::value, MODE = decltype(modet)::value;
+      using T = GramTile<TI, KIND, NB, MODE>;
+      const uint32_t nt = tiles(16 * NB, &tj);
+      split(gram_splits(nt, T::OCC, max_ks, &cost), 4 * T::U * Mk<KIND>::KSTEP);
+      hipLaunchKernelGGL((k_gram_rows<TI, KIND, NB, MODE, decltype(off)>), dim3((uint32_t)ks, nt), dim3(256), 0,
+                         c->stream, A, (uint64_t)lda, (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows,
+                         (uint32_t)rps, tj, upper, c->part);
+    };
+    auto at = [&](auto nbt, auto modet) { go(nbt, modet, uint32_t{}); };
+    auto one_tile = [&](auto modet) {
+      switch ((na + 15) / 16) {
+        case 1: at(std::integral_constant<int, 1>{}, modet); break;
+        case 2: at(std::integral_constant<int, 2>{}, modet); break;
+        case 3: at(std::integral_constant<int, 3>{}, modet); break;
+        case 4: at(std::integral_constant<int, 4>{}, modet); break;
+        case 5: at(std::integral_constant<int, 5>{}, modet); break;
+        case 6: at(std::integral_constant<int, 6>{}, modet); break;
+        case 7: at(std::integral_constant<int, 7>{}, modet); break;
+        default: at(std::integral_constant<int, 8>{}, modet); break;
+      }
+    };
+    constexpr std::integral_constant<int, G_SAME> SAME{};
+    constexpr std::integral_constant<int, G_UPPER> UPPER{};
+    constexpr std::integral_constant<int, G_FULL> FULL{};
+    if (lds) {
+      if constexpr (KIND != MK_F64) {
+        const uint32_t nt = tiles(GT2, &tj);
+        split(gram_splits(nt, 2, max_ks, &cost), Mk<KIND>::KSTEP);
+        hipLaunchKernelGGL((k_gram_lds<TI, KIND>), dim3((uint32_t)ks, nt), dim3(256), 0, c->stream, A, (uint64_t)lda,
+                           (uint32_t)na, B, (uint64_t)ldb, (uint32_t)nb, (uint32_t)rows, (uint32_t)rps, tj, upper,
+                           c->part);
+      }
+    } else if (std::max(lda, ldb) > (int64_t)1 << 22) {                       // 32-bit offsets do not reach 32 rows
+      go(std::integral_constant<int, 4>{}, FULL, uint64_t{});
+    } else if (same && na <= GT2) {
+      one_tile(SAME);
+    } else if (std::is_same<TI, double>::value && upper && na <= GT2) {
+      if constexpr (std::is_same<TI, double>::value) one_tile(UPPER);
+    } else {
+      // the tile edge (in blocks) of the least work: t^2 instructions and 2 t
+      // loads per step and wave, a load at about one FP64 or FP32 instruction, or
+      // four BF16 ones (whose step is 32 rows).  Edge 6 for FP32 only: the FP64
+      // accumulators of 36 blocks leave one wave per SIMD, too few loads in flight
+      // (A^T A at 512 912 us against 597), and BF16 values are 8 per lane and load.
+      int best = 0;
+      double least = 0;
+      for (int t : {KIND == MK_F32 ? 6 : 4, 4, 3, 2, 1}) {
+        gram_splits(tiles(16 * t, &tj), t == 6 ? GramTile<TI, KIND, 6, G_FULL>::OCC : 2, max_ks, &cost);
+        cost *= t * t + (KIND == MK_BF16 ? 8 : 2) * t;
+        if (best == 0 || cost < least) best = t, least = cost;
+      }
+      switch (best) {
+        case 1: at(std::integral_constant<int, 1>{}, FULL); break;
+        case 2: at(std::integral_constant<int, 2>{}, FULL); break;
+        case 3: at(std::integral_constant<int, 3>{}, FULL); break;
+        case 4: at(std::integral_constant<int, 4>{}, FULL); break;
+        default:
+          if constexpr (KIND == MK_F32) at(std::integral_constant<int, 6>{}, FULL);
+      }
+    }
   }
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_reduce_cols(c, c->part, ks, (int64_t)na * nb, out, RED_PLAIN);
+  const uint32_t bi = (uint32_t)((na + 15) / 16), bj = (uint32_t)((nb + 15) / 16);
+  if (upper)
+    hipLaunchKernelGGL((k_gram_sum<true>), dim3(bi * (bi + 1) / 2 * 4), dim3(1024), 0, c->stream, c->part, (uint32_t)ks,
+                       (uint32_t)na, (uint32_t)nb, out);
+  else
+    hipLaunchKernelGGL((k_gram_sum<false>), dim3(bi * bj * 4), dim3(1024), 0, c->stream, c->part, (uint32_t)ks,
+                       (uint32_t)na, (uint32_t)nb, out);
+  return hipGetLastError();
 }
 
 template <typename TI, int KIND>

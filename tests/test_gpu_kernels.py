@@ -7,6 +7,7 @@ products exact in any summation order, so those are compared bit for bit.
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 import workloads as W
@@ -86,6 +87,53 @@ def test_gram_of_a_block_with_itself_exact_on_integers(n, N):
         ope.ope_gram(ctx.handle, Ad, N, N, Ad, N, N, n, out)
         G = to_host(out)
     assert np.array_equal(G, A.T @ A)
+
+
+@pytest.mark.parametrize("kind", [None, 0, 1, 2], ids=["f64", "f32 in f64", "f32", "bf16"])
+@pytest.mark.parametrize("na,nb", [(1, 1), (15, 16), (17, 33), (48, 48), (49, 64), (65, 65), (80, 80), (96, 97),
+                                   (112, 112), (113, 127), (127, 127), (129, 129), (136, 136), (192, 192), (97, 193),
+                                   (300, 5), (256, 300), (512, 512)])
+def test_gram_at_the_edges_of_its_tiles(kind, na, nb):
+    """Widths around the 16-column blocks and the tiles of several edges, row
+    counts around the contraction steps and their groups, with one operand for
+    both sides where the widths agree; exact on integers."""
+    from paper_2511_06788_amd import ope
+    rng = np.random.default_rng(na + nb)
+    dt = np.float64 if kind is None else np.float32
+    p = W.Problem("sq", W.Grid(m=(520, 1), h=(1.0, 1.0), lo=(0.0, 0.0)), np.zeros(520), 512, 1.0)
+    A = rng.integers(-8, 9, size=(2500, na)).astype(dt)
+    B = rng.integers(-8, 9, size=(2500, nb)).astype(dt)
+    say(f"gram edges kind={kind} na={na} nb={nb}")
+    with ope.Context(p.grid, p.V, 512) as ctx:
+        Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+        for n in (1, 3, 15, 17, 63, 64, 65, 257, 2500):
+            for Xd, X in ((Bd, B),) + (((Ad, A),) if na == nb else ()):
+                out = empty_dev(na, nb)
+                if kind is None:
+                    ope.ope_gram(ctx.handle, Ad, na, na, Xd, nb, nb, n, out)
+                else:
+                    ope.ope_gram_f32(ctx.handle, kind, Ad, na, na, Xd, nb, nb, n, out)
+                G = to_host(out)
+                assert np.array_equal(G, A[:n].astype(np.float64).T @ X[:n].astype(np.float64)), (n, X is A)
+
+
+@pytest.mark.parametrize("lda", [1 << 22, (1 << 22) + 1])
+def test_gram_of_far_apart_rows(lda):
+    """Rows on either side of the distance up to which 32-bit offsets are used."""
+    from paper_2511_06788_amd import ope
+    rng = np.random.default_rng(3)
+    n, na, nb = 13, 70, 9
+    A = rng.integers(-8, 9, size=(n, na)).astype(np.float64)
+    B = rng.integers(-8, 9, size=(n, nb)).astype(np.float64)
+    p = W.harmonic_2d_32(m=8, N=8)
+    say(f"gram lda={lda}")
+    with _ctx(p) as ctx:
+        Ad = torch.zeros(n, lda, dtype=torch.float64, device="cuda")
+        Ad[:, :na] = to_dev(A)
+        out = empty_dev(na, nb)
+        ope.ope_gram(ctx.handle, Ad, lda, na, to_dev(B), nb, nb, n, out)
+        G = to_host(out)
+    assert np.array_equal(G, A.T @ B)
 
 
 @pytest.mark.parametrize("n,lda,na,ldb,nb", [(3001, 40, 33, 24, 20), (3001, 40, 17, 24, 20)])
