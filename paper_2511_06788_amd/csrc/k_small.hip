@@ -2,27 +2,20 @@
 // Steps 2-3 (Section 4.1), the warm-start inverse Lam^{-1}, the per-step
 // scalars, and the Ritz values (Householder tridiagonalisation and bisection).
 //
-// A 1024-thread work-group holds an N x N matrix in registers: thread t owns
-// column j = t % 128 and rows i = t / 128 + 8 r, r = 0..15.  Gauss-Jordan
-// elimination without pivoting runs four pivots per block step, with two
-// barriers per step (the pivot columns and rows are published through
-// double-buffered LDS); this is the path for N <= 128, larger N use the
-// Newton-Schulz pieces below.  No
+// For N <= 128 one work-group of 16 waves holds an N x N matrix in registers, in
+// 16 x 16 blocks in the layout of the FP64 matrix instruction's accumulator, and
+// inverts it by block Gauss-Jordan elimination without pivoting; larger N use
+// the Newton-Schulz pieces below.  No
 // pivoting is needed: the Step-2 matrix has symmetric part >= I (Lemma 3.1 and
 // its generalisation to an inexact GU), and Lam = U^T H U is SPD, so every
 // pivot of either is positive.
+#include <type_traits>
+
 #include "ope_internal.h"
 
 namespace {
 
 constexpr int SW = 1024;      // threads of the small kernels
-constexpr int RPT = 16;       // rows per thread (128 / 8)
-
-struct Own {
-  uint32_t j, q;
-  __device__ Own() : j(threadIdx.x & 127u), q(threadIdx.x >> 7) {}
-  __device__ uint32_t row(int r) const { return q + 8u * (uint32_t)r; }
-};
 
 // Deterministic work-group sum (fixed tree order).
 __device__ double wg_sum(double v, double* red) {
@@ -37,172 +30,293 @@ __device__ double wg_sum(double v, double* red) {
   return out;
 }
 
-// In-place Gauss-Jordan inversion of the register-resident matrix w, four
-// pivots per block step (the arithmetic of four successive single pivots,
-// regrouped):  with K the block's pivot indices, P = W[K,K] and
-// X = P^{-1} [W[K,:] with W[K,K] replaced by I],
-//   rows not in K:  W[i,:] <- W'[i,:] - W[i,K] X   (W' = W with columns K zeroed)
-//   rows in K:      W[K,:] <- X.
-// LDS per block step (double-buffered by step parity): the pivot columns
-// F[c][q * 16 + r] (row q + 8 r, so a thread reads its rows contiguously), the
-// pivot rows R[c][j], and X[c][j], which the 128 threads of row group 0 solve
-// for their column from P by Gauss-Jordan (a 4 x 4 system per column: two
-// barriers per step serve four pivots, instead of one barrier per pivot).  Sets *bad when a
-// pivot of the elimination is not a finite number above 1e-300.
-constexpr int GJB = 4;      // pivots per block step
+// Blocks of an N x N matrix over the 16 waves: a wave holds CB neighbouring blocks
+// of one block row (four waves to a block row for CB = 1, else two), element
+// (kr + 4 r, ci) of a block in register r of lane 16 kr + ci.
+typedef double v4d __attribute__((ext_vector_type(4)));
 
-struct GjLds {
-  double F[2][GJB][128];
-  double R[2][GJB][128];
-  double X[2][GJB][128];
+template <int CB>
+struct Blocks {
+  uint32_t kr, ci, br, bc0, nb;
+  __device__ explicit Blocks(uint32_t N) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    kr = lane >> 4;
+    ci = lane & 15u;
+    br = CB == 1 ? wave >> 2 : wave >> 1;
+    bc0 = CB == 1 ? wave & 3u : (wave & 1u) * CB;
+    nb = (N + 15u) / 16u;
+  }
+  __device__ bool has(int b) const { return br < nb && bc0 + b < nb; }        // uniform over the wave
+  __device__ uint32_t row(int r) const { return 16u * br + kr + 4u * (uint32_t)r; }
+  __device__ uint32_t col(int b) const { return 16u * (bc0 + b) + ci; }
 };
 
-__device__ void gj_invert(double (&w)[RPT], uint32_t N, GjLds& L, int* bad) {
-  const Own o;
-  for (uint32_t k0 = 0, st = 0; k0 < N; k0 += GJB, st ^= 1u) {
-    const uint32_t kb = min((uint32_t)GJB, N - k0);     // pivots of this step
-    double(&F)[GJB][128] = L.F[st];
-    double(&R)[GJB][128] = L.R[st];
-    double(&X)[GJB][128] = L.X[st];
-    const uint32_t kr = k0 >> 3;                         // register row of the pivot rows
-    const uint32_t q0 = k0 & 7u;                         // their row groups: q0 .. q0 + kb - 1
-    const bool krow = o.q >= q0 && o.q < q0 + kb;        // this wave holds a pivot row (as w[kr])
-    // pivot rows first (they include the block), then the pivot columns,
-    // which their lanes then zero
-    if (krow && o.j < N) {
+__device__ __forceinline__ v4d mma64(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+constexpr int LDF = 17, LDX = 144;                     // row strides without bank conflicts
+constexpr int MKC = 32, LDA = 33;                      // contraction indices per chunk of a product
+
+union SmallLds {
+  struct {                                             // of the inversion
+    double F[2][128 * LDF];
+    double R[16 * LDX], X[16 * LDX];
+    double P[16 * LDF];
+  } inv;
+  struct {                                             // of a product: MKC rows of B (and of A, transposed)
+    double A[MKC * LDX], B[MKC * LDX];
+  } mm;
+};
+static_assert(128 * LDA <= MKC * LDX, "A by columns fits where it does by rows");
+
+// acc += op(A) B for the wave's blocks, op the transpose when TA; EYE: A - I.
+// Chunks of MKC contraction indices staged in LDS, the next chunk's loads in
+// flight; zero outside the N x N matrices.  Called by the whole work-group; L must
+// be free, and is when it returns.
+template <int CB, bool TA, bool EYE>
+__device__ void blk_mm(const double* A, const double* B, uint32_t N, const Blocks<CB>& o, SmallLds& lds,
+                       v4d (&acc)[CB]) {
+  auto& L = lds.mm;
+  constexpr int PT = MKC * 128 / SW;                   // values of a chunk per thread
+  double ga[PT], gb[PT];
+  const bool same = TA && A == B;
+  auto load = [&](uint32_t k0) {
 #pragma unroll
-      for (int r = 0; r < RPT; ++r)
-        if ((uint32_t)r == kr) R[o.q - q0][o.j] = w[r];
+    for (int u = 0; u < PT; ++u) {
+      const uint32_t e = threadIdx.x + (uint32_t)SW * u;
+      const uint32_t kb = k0 + e / 128u, j = e % 128u;                         // by rows
+      gb[u] = kb < N && j < N ? B[kb * N + j] : 0.0;
+      if (TA) {
+        ga[u] = !same && kb < N && j < N ? A[kb * N + j] : 0.0;
+      } else {
+        const uint32_t i = e / MKC, k = k0 + e % MKC;                          // by columns
+        ga[u] = i < N && k < N ? A[i * N + k] - (EYE && i == k ? 1.0 : 0.0) : 0.0;
+      }
     }
-    if (o.j >= k0 && o.j < k0 + kb) {
-      const uint32_t c = o.j - k0;
+  };
+  const double* const pa = same ? L.B : L.A;
+  load(0);
+  for (uint32_t k0 = 0; k0 < N; k0 += MKC) {
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
-        F[c][o.q * 16u + r] = w[r];
-        w[r] = 0.0;
+    for (int u = 0; u < PT; ++u) {
+      const uint32_t e = threadIdx.x + (uint32_t)SW * u;
+      L.B[e / 128u * LDX + e % 128u] = gb[u];
+      if (TA) {
+        if (!same) L.A[e / 128u * LDX + e % 128u] = ga[u];
+      } else {
+        L.A[e / MKC * LDA + e % MKC] = ga[u];
+      }
+    }
+    __syncthreads();
+    if (k0 + MKC < N) load(k0 + MKC);
+    if (o.has(0)) {
+#pragma unroll 2
+      for (uint32_t k = o.kr; k < MKC; k += 4) {
+        const double a = TA ? pa[k * LDX + 16 * o.br + o.ci] : L.A[(16 * o.br + o.ci) * LDA + k];
+#pragma unroll
+        for (int b = 0; b < CB; ++b) acc[b] = mma64(a, L.B[k * LDX + o.col(b)], acc[b]);
       }
     }
     __syncthreads();
-    if (o.q == 0 && o.j < N) {
-      // solve P x = b for this column: b = R[:, j], or the unit vector of
-      // column j when j is a pivot column
-      double P[GJB][GJB], x[GJB];
+  }
+}
+
+// Gauss-Jordan inversion of one 16 x 16 block by one wave, a pivot at a time; row
+// P is register P / 4 of the lanes 16 (P % 4) ...  The next pivot's element is
+// updated ahead of the others, by the same operations, and divided while they
+// follow, so the division (the longest chain of a pivot) is hidden.  Returns
+// whether a pivot was not a finite number above 1e-300.
+__device__ __forceinline__ double inv16_recip(double piv, bool* bad) {
+  const bool ok = isfinite(piv) && piv > 1e-300;
+  *bad |= !ok;
+  double q = 1.0 / piv;
+  asm volatile("" : "+v"(q));                          // no branch around the division
+  return ok ? q : 0.0;
+}
+
+template <int P>
+__device__ __forceinline__ void inv16_pivot(v4d& w, double pinv, uint32_t kr, uint32_t ci, bool* bad) {
+  constexpr int R = P >> 2, G = P & 3;
+  double x = __shfl(w[R], (int)(16u * G + ci));        // row P at the lane's column
+  double next = 0.0;
+  if constexpr (P < 15) {
+    constexpr int R1 = (P + 1) >> 2, G1 = (P + 1) & 3;
+    const double a01 = lane_value(w[R], 16u * G + P + 1), a10 = lane_value(w[R1], 16u * G1 + P);
+    const double a11 = lane_value(w[R1], 16u * G1 + P + 1);
+    next = inv16_recip(fma(-a10, a01 * pinv, a11), bad);
+  }
+  const bool pc = ci == (uint32_t)P;
+  x = (pc ? 1.0 : x) * pinv;
 #pragma unroll
-      for (int c = 0; c < GJB; ++c) {
+  for (int r = 0; r < 4; ++r) {
+    const double f = dpp_move<0x150 + P>(w[r]);        // column P at the lane's row
+    const double v = fma(-f, x, pc ? 0.0 : w[r]);
+    w[r] = (r == R && kr == (uint32_t)G) ? x : v;
+  }
+  if constexpr (P < 15) inv16_pivot<P + 1>(w, next, kr, ci, bad);
+}
+
+__device__ __forceinline__ bool inv16(v4d& w, uint32_t kr, uint32_t ci) {
+  bool bad = false;
+  const double pinv = inv16_recip(lane_value(w[0], 0u), &bad);
+  inv16_pivot<0>(w, pinv, kr, ci, &bad);
+  return bad;
+}
+
+// In-place inversion of the matrix in w (padded to whole blocks with the unit
+// matrix), one block of 16 pivots per step.  With K the pivot indices, P = W[K,K]
+// and X = P^{-1} [W[K,:] with W[K,K] replaced by I],
+//   rows not in K:  W[i,:] <- W'[i,:] - W[i,K] X   (W' = W with columns K zeroed)
+//   rows in K:      W[K,:] <- X.
+// The wave that holds the next pivot block updates it first and inverts it while
+// the others work, so a step has two barriers: after the pivot row, column and
+// P^{-1} are published (R, F, P), and after X.  The serial chain of 16 pivots
+// bounds a step: 4900 of 7000 clocks at N = 64, and 7900 of 11400 at N = 128, where
+// the matrix instructions of the wave's neighbours delay it.  lds must be free; *bad is valid after the next barrier.
+template <int CB>
+__device__ void blk_invert(v4d (&w)[CB], const Blocks<CB>& o, SmallLds& lds, int* bad) {
+  auto& L = lds.inv;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (uint32_t K = 0;; ++K) {
+    // the update of step K - 1, then pivot block K
+    double f[4];
+    if (K > 0 && o.br < o.nb) {
 #pragma unroll
-        for (int d = 0; d < GJB; ++d)
-          P[c][d] = ((uint32_t)c < kb && (uint32_t)d < kb) ? R[c][k0 + d] : (c == d ? 1.0 : 0.0);
-        const bool inK = o.j >= k0 && o.j < k0 + kb;
-        x[c] = (uint32_t)c < kb ? (inK ? (o.j - k0 == (uint32_t)c ? 1.0 : 0.0) : R[c][o.j]) : 0.0;
+      for (int s = 0; s < 4; ++s) f[s] = -L.F[~K & 1u][(16 * o.br + o.ci) * LDF + o.kr + 4 * s];
+    }
+    auto update = [&](int b) {
+      if (o.br + 1 == K) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[b][r] = L.X[(o.kr + 4 * r) * LDX + o.col(b)];
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w[b] = mma64(f[s], L.X[(o.kr + 4 * s) * LDX + o.col(b)], w[b]);
       }
+      __builtin_amdgcn_sched_barrier(0);               // one block's operands in registers at a time
+    };
+    const bool own = K < o.nb && o.br == K && o.bc0 <= K && K < o.bc0 + CB;
+    if (own) {
+      __builtin_amdgcn_s_setprio(3);                   // the others wait for this one
+      v4d p;
 #pragma unroll
-      for (int p = 0; p < GJB; ++p) {
-        const double piv = P[p][p];
-        const bool ok = isfinite(piv) && piv > 1e-300;
-        if (!ok && (uint32_t)p < kb && o.j == 0) *bad = 1;
-        const double pinv = ok ? 1.0 / piv : 0.0;
+      for (int b = 0; b < CB; ++b)
+        if (o.bc0 + b == K) {
+          if (K > 0) update(b);
+          p = w[b];
+        }
+      if (inv16(p, o.kr, o.ci)) *bad = 1;
 #pragma unroll
-        for (int d = 0; d < GJB; ++d) P[p][d] *= pinv;
-        x[p] *= pinv;
+      for (int r = 0; r < 4; ++r) L.P[(o.kr + 4 * r) * LDF + o.ci] = p[r];
+      __builtin_amdgcn_s_setprio(0);
+    }
+    if (K > 0) {
 #pragma unroll
-        for (int c = 0; c < GJB; ++c) {
-          if (c == p) continue;
-          const double f = P[c][p];
+      for (int b = 0; b < CB; ++b)
+        if (o.has(b) && !(own && o.bc0 + b == K)) update(b);
+    }
+    if (K == o.nb) break;
 #pragma unroll
-          for (int d = 0; d < GJB; ++d) P[c][d] = fma(-f, P[p][d], P[c][d]);
-          x[c] = fma(-f, x[p], x[c]);
+    for (int b = 0; b < CB; ++b) {
+      if (o.br == K && o.has(b))
+#pragma unroll
+        for (int r = 0; r < 4; ++r) L.R[(o.kr + 4 * r) * LDX + o.col(b)] = w[b][r];
+      if (o.br < o.nb && o.bc0 + b == K) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          L.F[K & 1u][o.row(r) * LDF + o.ci] = w[b][r];
+          w[b][r] = 0.0;
         }
       }
-#pragma unroll
-      for (int c = 0; c < GJB; ++c) X[c][o.j] = x[c];
     }
     __syncthreads();
-    if (o.j < N) {
-      double xj[GJB];
+    if (wave < o.nb) {                                 // X, one block column per wave
+      v4d x = {0.0, 0.0, 0.0, 0.0};
+      if (wave == K) {
 #pragma unroll
-      for (int c = 0; c < GJB; ++c) xj[c] = X[c][o.j];
+        for (int r = 0; r < 4; ++r) x[r] = L.P[(o.kr + 4 * r) * LDF + o.ci];
+      } else {
 #pragma unroll
-      for (int c = 0; c < GJB; ++c) {
-        if ((uint32_t)c >= kb) break;                    // slots past the last pivot hold no column
-        const double2* F2 = reinterpret_cast<const double2*>(&F[c][o.q * 16u]);
-#pragma unroll
-        for (int r = 0; r < RPT / 2; ++r) {
-          const double2 f = F2[r];
-          w[2 * r] = fma(-f.x, xj[c], w[2 * r]);
-          w[2 * r + 1] = fma(-f.y, xj[c], w[2 * r + 1]);
-        }
+        for (int s = 0; s < 4; ++s)
+          x = mma64(L.P[o.ci * LDF + o.kr + 4 * s], L.R[(o.kr + 4 * s) * LDX + 16 * wave + o.ci], x);
       }
-      if (krow) {
 #pragma unroll
-        for (int r = 0; r < RPT; ++r)
-          if ((uint32_t)r == kr) w[r] = xj[o.q - q0];
-      }
+      for (int r = 0; r < 4; ++r) L.X[(o.kr + 4 * r) * LDX + 16 * wave + o.ci] = x[r];
     }
+    __syncthreads();
   }
   __syncthreads();
 }
 
-__device__ void load_own(const double* __restrict__ M, uint32_t N, double (&w)[RPT]) {
-  const Own o;
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    w[r] = (i < N && o.j < N) ? M[(uint64_t)i * N + o.j] : 0.0;
-  }
+// For the one-work-group kernels: the blocks per wave for N (see Blocks); fewer
+// leave fewer waves idle (both kernels of a step at N = 96: 100 us with 3, about
+// 125 with 4).
+template <typename Go>
+void with_blocks(uint32_t N, Go&& go) {
+  if (N <= 64) go(std::integral_constant<int, 1>{});
+  else if (N <= 96) go(std::integral_constant<int, 3>{});
+  else go(std::integral_constant<int, 4>{});
 }
 
-__device__ void store_own(double* __restrict__ M, uint32_t N, const double (&w)[RPT]) {
-  const Own o;
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) M[(uint64_t)i * N + o.j] = w[r];
-  }
-}
-
-// Energy, drift, |Lam|_F, column norms, and Lam^{-1} for the warm start.
+// Energy, drift, |Lam|_F, column norms, and Lam^{-1} for the warm start.  N = 128:
+// 55 us (109 with four pivots per step on the vector units).
+template <int CB>
 __global__ __launch_bounds__(SW) void k_prep_small(const double* __restrict__ C, const double* __restrict__ Lam,
                                                    double* __restrict__ Linv, double* __restrict__ cnorm2,
                                                    uint32_t N, OpeScalars* __restrict__ sc, float* __restrict__ Lam32,
                                                    float* __restrict__ Linv32) {
-  __shared__ double red[SW];
-  __shared__ __align__(16) GjLds gl;
+  __shared__ double red[3][16];
+  __shared__ __align__(16) SmallLds lds;
   __shared__ int bad;
-  const Own o;
+  const Blocks<CB> o(N);
   if (threadIdx.x == 0) bad = 0;
-  double w[RPT];
+  v4d w[CB];
   double e = 0.0, lf = 0.0, dr = 0.0;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) {
-      const double lij = Lam[(uint64_t)i * N + o.j], lji = Lam[(uint64_t)o.j * N + i];
-      const double cij = C[(uint64_t)i * N + o.j] - (i == o.j ? 1.0 : 0.0);
-      w[r] = 0.5 * (lij + lji);
-      if (Lam32) Lam32[(uint64_t)i * N + o.j] = (float)lij;
-      lf += lij * lij;
-      dr += cij * cij;
-      if (i == o.j) {
-        e += lij;
-        cnorm2[i] = C[(uint64_t)i * N + i];
-      }
-    } else {
-      w[r] = 0.0;
-    }
-  }
-  e = wg_sum(e, red);
-  lf = wg_sum(lf, red);
-  dr = wg_sum(dr, red);
-  gj_invert(w, N, gl, &bad);
-  store_own(Linv, N, w);
-  if (Linv32) {
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      const uint32_t i = o.row(r);
-      if (i < N && o.j < N) Linv32[(uint64_t)i * N + o.j] = (float)w[r];
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      w[b][r] = i == j ? 1.0 : 0.0;
+      if (i < N && j < N) {
+        const double lij = Lam[i * N + j], lji = Lam[j * N + i], cij = C[i * N + j], d = cij - w[b][r];
+        if (i == j) {
+          e += lij;
+          cnorm2[i] = cij;
+        }
+        w[b][r] = 0.5 * (lij + lji);
+        if (Lam32) Lam32[i * N + j] = (float)lij;
+        lf += lij * lij;
+        dr += d * d;
+      }
     }
+  e = wave_sum(e);
+  lf = wave_sum(lf);
+  dr = wave_sum(dr);
+  if ((threadIdx.x & 63u) == 0) {
+    red[0][threadIdx.x >> 6] = e;
+    red[1][threadIdx.x >> 6] = lf;
+    red[2][threadIdx.x >> 6] = dr;
   }
+  __syncthreads();
+  blk_invert<CB>(w, o, lds, &bad);
+#pragma unroll
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      if (i < N && j < N) {
+        Linv[i * N + j] = w[b][r];
+        if (Linv32) Linv32[i * N + j] = (float)w[b][r];
+      }
+    }
   if (threadIdx.x == 0) {
+    e = lf = dr = 0.0;
+    for (int u = 0; u < 16; ++u) {
+      e += red[0][u];
+      lf += red[1][u];
+      dr += red[2][u];
+    }
     sc->energy = 0.5 * e;
     sc->lam_fro = sqrt(lf);
     sc->drift = sqrt(dr);
@@ -264,88 +378,59 @@ __global__ __launch_bounds__(SW) void k_solve_setup(const double* __restrict__ r
   }
 }
 
-// The N x N products below run from LDS: a thread's row index is uniform over
-// its wave, so that operand is a broadcast read; from global memory it would be
-// a scalar load, and at most 15 of those can be outstanding.  smat holds one
-// N x N FP64 matrix (dynamic LDS, N*N*8 bytes, at most 128 KiB).
-
 // Steps 2-3: M = I + tau/2 (S_a - S_b) + tau^2/4 (T - S_a S_b), S_a = S_b^T,
 // B = M^{-1}, A = 2/tau (I - B) + S_b B, Z = [I - tau A ; tau B].
+//
+// On one compute unit the FP64 matrix instructions take 14 us for each of the two
+// products and for the inversion at N = 128; the rest is the inversion's pivots
+// (about 300 clocks each, 128 of them in a row).  N = 128: 117 us, against 212 for
+// four pivots at a time on the vector units and products read from LDS value by
+// value; N = 17 15 against 32.
+template <int CB>
 __global__ __launch_bounds__(SW) void k_small_solve(const double* __restrict__ Sb, const double* __restrict__ T,
-                                                    double tau, uint32_t N, double* __restrict__ Bws,
-                                                    double* __restrict__ Z, double* __restrict__ Aout,
-                                                    OpeScalars* __restrict__ sc) {
-  extern __shared__ double smat[];
-  __shared__ __align__(16) GjLds gl;
+                                                    double tau, uint32_t N, double* Bws, double* __restrict__ Z,
+                                                    double* __restrict__ Aout, OpeScalars* __restrict__ sc) {
+  __shared__ __align__(16) SmallLds lds;
   __shared__ int bad;
-  const Own o;
+  const Blocks<CB> o(N);
   if (threadIdx.x == 0) bad = 0;
-  for (uint32_t e = threadIdx.x; e < N * N; e += SW) smat[e] = Sb[e];
-  __syncthreads();
-  const uint32_t jj = o.j < N ? o.j : 0u;
-  double w[RPT];
-  // M, with P = S_a S_b, P_ij = sum_k S_b[k][i] S_b[k][j]
-  double P[RPT];
+  v4d w[CB], acc[CB];
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) P[r] = 0.0;
-#pragma unroll 1
-  for (uint32_t k = 0; k < N; ++k) {
-    const double skj = smat[k * N + jj];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      const uint32_t i = o.row(r);
-      const double ski = smat[k * N + (i < N ? i : 0u)];
-      P[r] += ski * skj;
-    }
-  }
+  for (int b = 0; b < CB; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
+  blk_mm<CB, true, false>(Sb, Sb, N, o, lds, acc);          // S_a S_b
   const double ht = 0.5 * tau, qt = 0.25 * tau * tau;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) {
-      const double sb = Sb[(uint64_t)i * N + o.j], sa = Sb[(uint64_t)o.j * N + i];
-      w[r] = (i == o.j ? 1.0 : 0.0) + ht * (sa - sb) + qt * (T[(uint64_t)i * N + o.j] - P[r]);
-    } else {
-      w[r] = 0.0;
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      w[b][r] = i == j ? 1.0 : 0.0;
+      if (i < N && j < N) w[b][r] += ht * (Sb[j * N + i] - Sb[i * N + j]) + qt * (T[i * N + j] - acc[b][r]);
+      acc[b][r] = 0.0;
     }
-  }
-  gj_invert(w, N, gl, &bad);
-  store_own(Bws, N, w);           // B
   __syncthreads();
-  // A = 2/tau (I - B) + S_b B: B's rows staged through the elimination's LDS
-  // (free now) in chunks of BCH rows, every thread loading its share at once
-  double acc[RPT];
+  blk_invert<CB>(w, o, lds, &bad);
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) acc[r] = 0.0;
-  constexpr uint32_t BCH = sizeof(GjLds) / (sizeof(double) * 128);     // rows of 128 per chunk
-  double* bst = reinterpret_cast<double*>(&gl);
-  for (uint32_t k0 = 0; k0 < N; k0 += BCH) {
-    const uint32_t kn = min(BCH, N - k0);
-    for (uint32_t e = threadIdx.x; e < kn * N; e += SW) bst[e] = Bws[(uint64_t)k0 * N + e];
-    __syncthreads();
-#pragma unroll 1
-    for (uint32_t k = 0; k < kn; ++k) {
-      const double bkj = bst[k * N + jj];
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
-        const uint32_t i = o.row(r);
-        acc[r] += smat[(i < N ? i : 0u) * N + k0 + k] * bkj;
-      }
-    }
-    __syncthreads();
-  }
+    for (int r = 0; r < 4; ++r)
+      if (o.row(r) < N && o.col(b) < N) Bws[o.row(r) * N + o.col(b)] = w[b][r];          // B
+  __syncthreads();
+  blk_mm<CB, false, false>(Sb, Bws, N, o, lds, acc);        // S_b B
   const double it = 2.0 / tau;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) {
-      const double dij = (i == o.j ? 1.0 : 0.0);
-      const double a = it * (dij - w[r]) + acc[r];
-      Z[(uint64_t)i * N + o.j] = dij - tau * a;
-      Z[(uint64_t)(N + i) * N + o.j] = tau * w[r];
-      if (Aout) Aout[(uint64_t)i * N + o.j] = a;
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      if (i < N && j < N) {
+        const double bij = Bws[i * N + j];             // not kept in registers over the product
+        const double dij = i == j ? 1.0 : 0.0, a = it * (dij - bij) + acc[b][r];
+        Z[i * N + j] = dij - tau * a;
+        Z[(N + i) * N + j] = tau * bij;
+        if (Aout) Aout[i * N + j] = a;
+      }
     }
-  }
   if (threadIdx.x == 0 && bad && sc->err == 0) sc->err = OPE_EPIVOT;
 }
 
@@ -358,75 +443,52 @@ __global__ __launch_bounds__(SW) void k_small_solve(const double* __restrict__ S
 // S_b^T (C - I) S_b term keeps the step orthogonality-preserving when the
 // FP32 iterate has drifted; without it the drift is amplified at large tau.
 // Z is written in FP32 (2N x N) for the BF16 product; Wsm is N x N scratch.
+// N = 128: 112 us (294 before, as k_small_solve).
+template <int CB>
 __global__ __launch_bounds__(SW) void k_small_solve_delta(const double* __restrict__ Sb,
                                                           const double* __restrict__ Tp,
                                                           const double* __restrict__ C, double tau, uint32_t N,
-                                                          double* __restrict__ Wsm, float* __restrict__ Z32,
+                                                          double* Wsm, float* __restrict__ Z32,
                                                           OpeScalars* __restrict__ sc) {
-  extern __shared__ double smat[];
-  __shared__ __align__(16) GjLds gl;
+  __shared__ __align__(16) SmallLds lds;
   __shared__ int bad;
-  const Own o;
+  const Blocks<CB> o(N);
   if (threadIdx.x == 0) bad = 0;
-  for (uint32_t e = threadIdx.x; e < N * N; e += SW) smat[e] = C[e];
-  __syncthreads();
-  const uint32_t jj = o.j < N ? o.j : 0u;
-  // Wsm = (C - I) S_b  (C from LDS, S_b's columns from global memory)
-  double acc[RPT];
+  v4d w[CB], acc[CB];
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) acc[r] = 0.0;
-  double snx = Sb[jj];
-#pragma unroll 1
-  for (uint32_t l = 0; l < N; ++l) {
-    const double slj = snx;
-    snx = Sb[(uint64_t)(l + 1 < N ? l + 1 : l) * N + jj];
+  for (int b = 0; b < CB; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
+  blk_mm<CB, false, true>(C, Sb, N, o, lds, acc);           // (C - I) S_b
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      const uint32_t k = o.row(r) < N ? o.row(r) : 0u;
-      acc[r] += (smat[k * N + l] - (k == l ? 1.0 : 0.0)) * slj;
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (o.row(r) < N && o.col(b) < N) Wsm[o.row(r) * N + o.col(b)] = acc[b][r];
+      acc[b][r] = 0.0;
     }
-  }
-  store_own(Wsm, N, acc);
   __syncthreads();
-  for (uint32_t e = threadIdx.x; e < N * N; e += SW) smat[e] = Sb[e];
-  __syncthreads();
-  // Q = S_b^T Wsm  (S_b from LDS, Wsm's columns from global memory)
-  double qv[RPT];
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) qv[r] = 0.0;
-  double wnx = Wsm[jj];
-#pragma unroll 1
-  for (uint32_t k = 0; k < N; ++k) {
-    const double wkj = wnx;
-    wnx = Wsm[(uint64_t)(k + 1 < N ? k + 1 : k) * N + jj];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      const uint32_t i = o.row(r) < N ? o.row(r) : 0u;
-      qv[r] += smat[k * N + i] * wkj;
-    }
-  }
-  double w[RPT];
+  blk_mm<CB, true, false>(Sb, Wsm, N, o, lds, acc);         // S_b^T (C - I) S_b
   const double ht = 0.5 * tau, qt = 0.25 * tau * tau;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) {
-      const double sb = Sb[(uint64_t)i * N + o.j], sa = Sb[(uint64_t)o.j * N + i];
-      w[r] = (i == o.j ? 1.0 : 0.0) + ht * (sa - sb) + qt * (Tp[(uint64_t)i * N + o.j] - qv[r]);
-    } else {
-      w[r] = 0.0;
-    }
-  }
-  gj_invert(w, N, gl, &bad);
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t i = o.row(r);
-    if (i < N && o.j < N) {
-      const double dij = (i == o.j ? 1.0 : 0.0);
-      Z32[(uint64_t)i * N + o.j] = (float)(-2.0 * (dij - w[r]));
-      Z32[(uint64_t)(N + i) * N + o.j] = (float)(tau * w[r]);
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      w[b][r] = i == j ? 1.0 : 0.0;
+      if (i < N && j < N) w[b][r] += ht * (Sb[j * N + i] - Sb[i * N + j]) + qt * (Tp[i * N + j] - acc[b][r]);
     }
-  }
+  __syncthreads();
+  blk_invert<CB>(w, o, lds, &bad);
+#pragma unroll
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t i = o.row(r), j = o.col(b);
+      if (i < N && j < N) {
+        const double dij = i == j ? 1.0 : 0.0;
+        Z32[i * N + j] = (float)(-2.0 * (dij - w[b][r]));
+        Z32[(N + i) * N + j] = (float)(tau * w[b][r]);
+      }
+    }
   if (threadIdx.x == 0 && bad && sc->err == 0) sc->err = OPE_EPIVOT;
 }
 
@@ -1015,16 +1077,20 @@ hipError_t launch_drift_check(ope_ctx* c, const double* C, float* Z32, double th
 hipError_t launch_prep_small(ope_ctx* c) {
   if (c->N > OPE_MAX_N_ONE_WG) return big_prep(c);
   ProfScope ps(c, OPE_KERNEL_SMALL);
-  hipLaunchKernelGGL(k_prep_small, dim3(1), dim3(SW), 0, c->stream, c->C, c->Lam, c->Linv, c->cnorm2, (uint32_t)c->N,
-                     c->sc, c->Lam32, c->Linv32);
+  with_blocks((uint32_t)c->N, [&](auto cb) {
+    hipLaunchKernelGGL((k_prep_small<decltype(cb)::value>), dim3(1), dim3(SW), 0, c->stream, c->C, c->Lam, c->Linv,
+                       c->cnorm2, (uint32_t)c->N, c->sc, c->Lam32, c->Linv32);
+  });
   return hipGetLastError();
 }
 
 hipError_t launch_small_solve_delta(ope_ctx* c, const double* Sb, const double* Tperp, double tau) {
   if (c->N > OPE_MAX_N_ONE_WG) return big_small_solve_delta(c, Sb, Tperp, tau);
   ProfScope ps(c, OPE_KERNEL_SMALL);
-  hipLaunchKernelGGL(k_small_solve_delta, dim3(1), dim3(SW), (size_t)c->N * c->N * sizeof(double), c->stream, Sb,
-                     Tperp, c->C, tau, (uint32_t)c->N, c->Wsm, c->Z32, c->sc);
+  with_blocks((uint32_t)c->N, [&](auto cb) {
+    hipLaunchKernelGGL((k_small_solve_delta<decltype(cb)::value>), dim3(1), dim3(SW), 0, c->stream, Sb, Tperp, c->C,
+                       tau, (uint32_t)c->N, c->Wsm, c->Z32, c->sc);
+  });
   return hipGetLastError();
 }
 
@@ -1061,8 +1127,10 @@ hipError_t launch_small_solve(ope_ctx* c, const double* Sb, const double* T, dou
                               double* B) {
   if (c->N > OPE_MAX_N_ONE_WG) return big_small_solve(c, Sb, T, tau, Z, A, B ? B : c->B);
   ProfScope ps(c, OPE_KERNEL_SMALL);
-  hipLaunchKernelGGL(k_small_solve, dim3(1), dim3(SW), (size_t)c->N * c->N * sizeof(double), c->stream, Sb, T, tau,
-                     (uint32_t)c->N, B ? B : c->B, Z, A, c->sc);
+  with_blocks((uint32_t)c->N, [&](auto cb) {
+    hipLaunchKernelGGL((k_small_solve<decltype(cb)::value>), dim3(1), dim3(SW), 0, c->stream, Sb, T, tau,
+                       (uint32_t)c->N, B ? B : c->B, Z, A, c->sc);
+  });
   return hipGetLastError();
 }
 

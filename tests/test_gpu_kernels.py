@@ -229,6 +229,47 @@ def test_small_solve_matches_oracle(tau, exact):
     assert np.max(np.abs(Z[N:] - tau * B_ref)) <= 1e-13 * tau
 
 
+@pytest.mark.parametrize("N", [1, 2, 15, 16, 17, 33, 64, 65, 95, 96, 97, 113, 127, 128])
+def test_small_solve_at_the_edges_of_its_blocks(N):
+    """Widths around the 16 x 16 blocks and the changes of layout.  M = I + (skew)
+    + (positive) has its inverse bounded by 1; elimination without pivoting on
+    it is backward stable, so B is within a small multiple of N eps cond(M)
+    (taken 8) and A, which multiplies by S_b and 2 / tau, within the same of
+    (2 / tau + |S_b|)."""
+    from paper_2511_06788_amd import ope
+    rng = np.random.default_rng(N)
+    Sb = rng.standard_normal((N, N)) / np.sqrt(N)
+    F = rng.standard_normal((N, 2 * N)) / np.sqrt(N)
+    T = Sb.T @ Sb + F @ F.T
+    tau = 2.5
+    A_ref, B_ref, M = O.small_solve(Sb.T, T, tau, S_b=Sb)
+    g = W.unit_box_grid((12, 12))
+    say(f"small_solve N={N}")
+    with ope.Context(g, np.zeros(g.n), N) as ctx:
+        Zd, Ad, Bd = empty_dev(2 * N, N), empty_dev(N, N), empty_dev(N, N)
+        ope.ope_small_solve(ctx.handle, to_dev(Sb), to_dev(T), tau, Zd, Ad, Bd)
+        Z, A, B = to_host(Zd), to_host(Ad), to_host(Bd)
+    bound = 8 * N * EPS * np.linalg.cond(M)
+    assert np.linalg.norm(B - B_ref, 2) <= bound
+    assert np.linalg.norm(A - A_ref, 2) <= bound * (2 / tau + np.linalg.norm(Sb, 2))
+    assert np.max(np.abs(Z[:N] - (np.eye(N) - tau * A))) <= 4 * EPS * (1 + tau * np.max(np.abs(A)))
+    assert np.array_equal(Z[N:], tau * B)
+
+
+@pytest.mark.parametrize("N,at", [(1, 0), (17, 16), (64, 5), (96, 95), (128, 0), (128, 100)])
+def test_small_solve_flags_a_negative_pivot_anywhere(N, at):
+    """M = I but for one negative diagonal entry."""
+    from paper_2511_06788_amd import ope
+    T = np.zeros((N, N))
+    T[at, at] = -8.0                                    # tau = 1: M = 1 - 8 / 4
+    g = W.unit_box_grid((12, 12))
+    say(f"small_solve pivot N={N} at={at}")
+    with ope.Context(g, np.zeros(g.n), N) as ctx:
+        with pytest.raises(ope.OpeError) as ei:
+            ope.ope_small_solve(ctx.handle, to_dev(np.zeros((N, N))), to_dev(T), 1.0, empty_dev(2 * N, N))
+    assert ei.value.status == ope.OPE_EPIVOT
+
+
 def test_small_solve_flags_bad_pivot():
     """A non-finite input must be reported, not silently used."""
     from paper_2511_06788_amd import ope

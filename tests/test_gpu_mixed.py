@@ -154,6 +154,35 @@ def test_one_mixed_step_matches_oracle_delta_step(autotune):
     assert abs(info.drift - O.ortho_error(U)) <= 1e-12
 
 
+@pytest.mark.parametrize("scale", [1.0, 1.05])
+@pytest.mark.parametrize("N", [1, 15, 17, 64, 65, 96, 97, 128])
+def test_one_mixed_step_at_the_edges_of_the_small_solve(N, scale):
+    """One mixed step vs the oracle's delta-form step at widths around the small
+    solve's blocks and changes of layout (the bounds of the test above).  A block
+    that is not orthonormal makes the S_b^T (C - I) S_b term a tenth of the
+    matrix's; the step then ends in one Newton-Schulz re-normalisation."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid((20, 20))
+    p = W.Problem("t", g, np.zeros(g.n), N, 1.0)
+    op = _op(p)
+    U32 = (scale * W.initial_block(g.n, N, 5)).astype(np.float32)
+    U = U32.astype(np.float64)
+    tau = 20.0
+    ref = O.step_delta(U, O.GSolver(op, "dense")(U), tau)["U"]
+    ref = ref @ (1.5 * np.eye(N) - 0.5 * ref.T @ ref)
+    say(f"one mixed step N={N} scale={scale}")
+    with _ctx(p) as ctx:
+        ope.ope_set_inner(ctx.handle, 0.0, 1e-7, 20000)
+        Ud = _dev32(U32)
+        info = ope.ope_step(ctx.handle, Ud, tau)
+        Un = to_host(Ud).astype(np.float64)
+    step = np.max(np.abs(ref - U))
+    assert step > 1e-3
+    assert np.max(np.abs(Un - ref)) <= 1e-2 * step
+    assert abs(info.energy - O.energy(op, U)) <= 1e-6 * abs(info.energy)
+    assert abs(info.drift - O.ortho_error(U)) <= 1e-12
+
+
 def test_mixed_then_fp64_finish_converges_3d():
     """16^3 wells, N = 17: the mixed phase reaches the FP32 floor with Ritz
     values within 1e-6 and drift below 1e-6; the FP64 finish reaches 1e-10."""
