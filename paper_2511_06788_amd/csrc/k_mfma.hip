@@ -541,7 +541,10 @@ __global__ __launch_bounds__(256) void k_rowmm_narrow(const TI* X0, const TI* __
 // buffered: X's rows (read as 16-byte chunks) are stored transposed, Xt[k][row],
 // so that the MFMA operand reads of both panels are contiguous across lanes,
 // and the KC rows of M beside them.  M is read once per work-group instead of
-// once per wave and 64-row tile.
+// once per wave and 64-row tile.  At N = 128 the four products of an FP64 step
+// move ten blocks of 64^3 rows (571 us at the copy rate) and measured 1030 us, 935
+// with unconditional loads and the xor-ed layout below; at 96^3, N = 512 they are
+// bound by the matrix cores (45.0 -> 42.7 ms, 54 of 73 TFLOP/s).
 constexpr int RT2 = 128;    // rows per work-group tile
 constexpr int RT2H = 64;    // rows per work-group tile of the FP64 kind
 
@@ -583,42 +586,68 @@ __global__ __launch_bounds__(256, RTW == RT2H ? 3 : 2) void k_rowmm_lds(const TI
   const uint32_t npan = NSRC * kpan;
   ChunkV cx[XCT], cm[MCT];
   const Chunk z = {0u, 0u, 0u, 0u};
+  // Loads are unconditional (a branch or a select behind one would wait for it
+  // before the matrix instructions): past the edge they take the last row, column
+  // or contraction index.  Rows' and columns' values reach only output that is not
+  // stored; contraction indices past N are zeroed on the way into LDS.
+  uint32_t ox[XCT], om[MCT];
+#pragma unroll
+  for (int u = 0; u < XCT; ++u) ox[u] = min((threadIdx.x + 256u * u) / XC, n - 1u - row0) * N;
+#pragma unroll
+  for (int u = 0; u < MCT; ++u) om[u] = min((threadIdx.x + 256u * u) % MCR * VPC, N - VPC - col0);
   auto load = [&](uint32_t t) {
-    const TI* X = t < kpan ? X0 : X1;
-    const TI* M = t < kpan ? M0 : M1;
     const uint32_t k0 = (t < kpan ? t : t - kpan) * KC;
+    const TI* X = (t < kpan ? X0 : X1) + (uint64_t)row0 * N + k0;
+    const TI* M = (t < kpan ? M0 : M1) + (uint64_t)k0 * N + col0;
+#pragma unroll
+    for (int u = 0; u < XCT; ++u)
+      cx[u].c = *reinterpret_cast<const Chunk*>(X + ox[u] + min((threadIdx.x + 256u * u) % XC * VPC, N - VPC - k0));
+#pragma unroll
+    for (int u = 0; u < MCT; ++u)
+      cm[u].c = *reinterpret_cast<const Chunk*>(M + min((threadIdx.x + 256u * u) / MCR, N - 1u - k0) * N + om[u]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // FP64: LDS columns are xor-ed with a few bits of the contraction index k, so that
+  // the transposed stores of X and the four k of an operand read spread over the
+  // banks (N = 128, four products at 48^3: 450 -> 425 us; FP32 lost 10% to the
+  // addresses of its 4-byte stores, 361 -> 396)
+  auto swz_x = [](uint32_t k) -> uint32_t { return KIND == MK_F64 ? ((k >> 1 & 3u) << 3) ^ ((k & 1u) << 4) : 0u; };
+  auto swz_m = [](uint32_t k) -> uint32_t { return KIND == MK_F64 ? (k & 1u) << 4 : 0u; };
+  auto store = [&](int buf, uint32_t t) {
+    const uint32_t left = N - (t < kpan ? t : t - kpan) * KC;
+    __builtin_amdgcn_sched_barrier(0);
+    if (left < KC) {                                  // uniform
+#pragma unroll
+      for (int u = 0; u < XCT; ++u)
+        if ((threadIdx.x + 256u * u) % XC * VPC >= left) cx[u].c = z;
+#pragma unroll
+      for (int u = 0; u < MCT; ++u)
+        if ((threadIdx.x + 256u * u) / MCR >= left) cm[u].c = z;
+    }
 #pragma unroll
     for (int u = 0; u < XCT; ++u) {
       const uint32_t c = threadIdx.x + 256u * u;
       const uint32_t r = c / XC, kc = (c % XC) * VPC;
-      const uint32_t gr = row0 + r;
-      cx[u].c = (gr < n && k0 + kc < N) ? *reinterpret_cast<const Chunk*>(X + (uint64_t)gr * N + k0 + kc) : z;
+#pragma unroll
+      for (int e = 0; e < VPC; ++e) xt[buf][kc + e][r ^ swz_x(kc + e)] = cx[u].v[e];
     }
 #pragma unroll
     for (int u = 0; u < MCT; ++u) {
       const uint32_t c = threadIdx.x + 256u * u;
       const uint32_t kk = c / MCR, col = (c % MCR) * VPC;
-      cm[u].c = (k0 + kk < N && col0 + col < N) ? *reinterpret_cast<const Chunk*>(M + (uint64_t)(k0 + kk) * N + col0 + col)
-                                               : z;
+      *reinterpret_cast<Chunk*>(&mp[buf][kk][col ^ swz_m(kk)]) = cm[u].c;
     }
   };
-  auto store = [&](int buf) {
+  // where that puts the columns 16 q + ci, q = 0, 1, for a lane's k = kr mod 4
+  constexpr int NS = KIND == MK_F64 ? 2 : 1;
+  uint32_t bx[NS], bm[NS];
 #pragma unroll
-    for (int u = 0; u < XCT; ++u) {
-      const uint32_t c = threadIdx.x + 256u * u;
-      const uint32_t r = c / XC, kc = (c % XC) * VPC;
-#pragma unroll
-      for (int e = 0; e < VPC; ++e) xt[buf][kc + e][r] = cx[u].v[e];
-    }
-#pragma unroll
-    for (int u = 0; u < MCT; ++u) {
-      const uint32_t c = threadIdx.x + 256u * u;
-      const uint32_t kk = c / MCR, col = (c % MCR) * VPC;
-      *reinterpret_cast<Chunk*>(&mp[buf][kk][col]) = cm[u].c;
-    }
-  };
+  for (uint32_t q = 0; q < (uint32_t)NS; ++q) {
+    bx[q] = (16u * q + ci) ^ (KIND == MK_F64 ? ((kr >> 1) << 3) ^ ((kr & 1u) << 4) : 0u);
+    bm[q] = (16u * q + ci) ^ (KIND == MK_F64 ? (kr & 1u) << 4 : 0u);
+  }
   load(0);
-  store(0);
+  store(0, 0);
   __syncthreads();
   for (uint32_t t = 0; t < npan; ++t) {
     const int buf = (int)(t & 1u);
@@ -630,16 +659,17 @@ __global__ __launch_bounds__(256, RTW == RT2H ? 3 : 2) void k_rowmm_lds(const TI
       for (int e = 0; e < MK::KPL; ++e) {
         const uint32_t k = kk * MK::KSTEP + kr * MK::KPL + e;
 #pragma unroll
-        for (int a = 0; a < AR; ++a) av[a][e] = xt[buf][k][wr * (RTW / 2) + a * 16 + ci];
+        for (int a = 0; a < AR; ++a)
+          av[a][e] = xt[buf][k][wr * (RTW / 2) + a / NS * (16 * NS) + bx[(a ^ kk) % NS]];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) bv[b][e] = mp[buf][k][wc * 64 + b * 16 + ci];
+        for (int b = 0; b < 4; ++b) bv[b][e] = mp[buf][k][wc * 64 + b / NS * (16 * NS) + bm[b % NS]];
       }
 #pragma unroll
       for (int a = 0; a < AR; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = mma<KIND, TI>(av[a], bv[b], acc[a][b]);
     }
-    if (t + 1 < npan) store(buf ^ 1);
+    if (t + 1 < npan) store(buf ^ 1, t + 1);
     __syncthreads();
   }
   // every wave has read all of its rows (the last panel is in LDS) before any
