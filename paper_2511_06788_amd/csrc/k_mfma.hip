@@ -891,6 +891,287 @@ __global__ __launch_bounds__(ST_WG, 2) void k_rowmm_strip(const TI* X0, const TI
   }
 }
 
+// The start of a step in one pass over the block (at most 128 columns): with U, HU,
+// Lam and Lam^{-1},
+//   R = HU - U Lam  (its column sums of squares only: the outer residual),
+//   Y = U Lam^{-1}, r = -R Lam^{-1} and its column sums of squares.
+// As three row products this reads and writes seven blocks; here two are read and
+// two written, and R stays in registers.  A wave takes 16 rows and multiplies
+// transposed, (M^T X^T), so that an accumulator (a lane has one row and columns
+// 16 b + 4 kr + 0..3 of block b) is the next product's operand as it stands: the
+// contraction takes the columns in that order.  Where the accumulator's rows are
+// kr + 4 r (FP64) the columns of M are read in the order 4 (m % 4) + m / 4 instead.
+// M in LDS in chunks of 32 columns, all of them resident up to 80 columns (waves
+// then run free of each other); above, two buffers, one barrier per chunk.
+// Bound by memory up to about 64 columns and by the matrix cores above (353 us of
+// FP64 at 64^3, N = 128).  Against three row products and their two reductions:
+// 64^3, N = 128 632 -> 516 us, mixed 327 -> 264, N = 17 101 -> 36; all products of
+// a step at 48^3: N = 45 146 -> 91 us, 64 192 -> 125, 96 324 -> 280, 112 402 -> 357,
+// 127 538 -> 475, 128 425 -> 406; mixed 64 187 -> 135, 128 358 -> 328.
+template <typename TI, int NB>
+struct StartTile {
+  static constexpr int KR = 16 * NB;                  // rows of a chunk
+  static constexpr int S = 36;                        // its row stride: rows 4 apart in distinct banks
+  static constexpr int NCH = (NB + 1) / 2;            // chunks per matrix
+  static constexpr int BUF = KR * S;
+  static constexpr bool RESIDENT = NB <= 5;
+  static constexpr int LDS = (RESIDENT ? 2 * NCH : 2) * BUF * (int)sizeof(TI);
+  static constexpr int OCC = NB <= (sizeof(TI) == 8 ? 3 : 5) ? 2 : 1;         // work-groups per compute unit
+};
+
+// Sums over the 16 lanes of a row: lane ci gets that of v[ci % 8].
+__device__ __forceinline__ double scatter_sum8(double (&v)[8], uint32_t ci) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] += dpp_move<0x140>(v[i]);                  // lane 15 - ci
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double keep = ci & 4u ? v[i + 4] : v[i], send = ci & 4u ? v[i] : v[i + 4];
+    v[i] = keep + dpp_move<0x141>(send);                                      // lane 7 - ci of eight
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double keep = ci & 2u ? v[i + 2] : v[i], send = ci & 2u ? v[i] : v[i + 2];
+    v[i] = keep + dpp_move<0x4E>(send);                                       // lane ci ^ 2
+  }
+  const double keep = ci & 1u ? v[1] : v[0], send = ci & 1u ? v[0] : v[1];
+  return keep + dpp_move<0xB1>(send);                                         // lane ci ^ 1
+}
+
+template <typename TI, int KIND, int NB, bool VEC>
+__global__ __launch_bounds__(ST_WG, (2 * StartTile<TI, NB>::OCC)) void k_start(
+    const TI* __restrict__ U, const TI* __restrict__ HU, const TI* __restrict__ Lam, const TI* __restrict__ Linv,
+    TI* __restrict__ Y, TI* __restrict__ R0, uint32_t n, uint32_t N, uint32_t ntiles, double* __restrict__ part) {
+  using MK = Mk<KIND>;
+  using acc_t = typename MK::acc_t;
+  using T = StartTile<TI, NB>;
+  constexpr int VPC = 16 / (int)sizeof(TI), NCH = T::NCH, S = T::S;
+  constexpr int PR = 32 / VPC, PT = (T::KR * PR + ST_WG - 1) / ST_WG;
+  typedef unsigned int Chunk __attribute__((ext_vector_type(4)));
+  union Quad {                                        // four consecutive columns of a row
+    Chunk c[4 / VPC];
+    TI v[4];
+  };
+  union ChunkV {
+    Chunk c;
+    TI v[VPC];
+  };
+  extern __shared__ __align__(16) char strip_lds[];
+  TI* const ml = reinterpret_cast<TI*>(strip_lds);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const uint32_t kr = lane >> 4, ci = lane & 15u;
+  const uint32_t mc = KIND == MK_F64 ? 4u * (ci & 3u) + (ci >> 2) : ci;       // the accumulator row's column of M
+  ChunkV mv[PT];
+  // Loads are unconditional: past the edge they take the last row or column, whose
+  // values meet zeros of M in LDS or reach only output that is not stored.
+  auto m_at = [&](uint32_t tid, int u, uint32_t s, int e, bool* in) -> uint32_t {    // value e of 16-byte group u
+    const uint32_t q = tid + (uint32_t)ST_WG * u;
+    const uint32_t k = q / PR, col = 32u * (s < NCH ? s : s - NCH) + (q % PR) * VPC + (uint32_t)e;
+    *in = k < N && col < N;
+    return min(k, N - 1u) * N + min(col, N - (VEC ? (uint32_t)VPC : 1u));
+  };
+  auto load_m = [&](uint32_t s) {                     // chunk s of Lam, then of Lam^{-1}
+    const TI* M = s < NCH ? Lam : Linv;
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                     // every chunk's offsets kept over the tiles would spill
+    bool in;
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+      if constexpr (VEC) {
+        mv[u].c = *reinterpret_cast<const Chunk*>(M + m_at(tid, u, s, 0, &in));
+      } else {
+#pragma unroll
+        for (int e = 0; e < VPC; ++e) mv[u].v[e] = M[m_at(tid, u, s, e, &in)];
+      }
+    }
+  };
+  auto store_m = [&](uint32_t s, uint32_t buf) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+      const uint32_t q = tid + (uint32_t)ST_WG * u;
+      ChunkV v;
+#pragma unroll
+      for (int e = 0; e < VPC; ++e) {
+        bool in;
+        (void)m_at(tid, u, s, e, &in);
+        v.v[e] = in ? mv[u].v[e] : TI(0);
+      }
+      if (PT * ST_WG == T::KR * PR || q < (uint32_t)(T::KR * PR))
+        *reinterpret_cast<Chunk*>(ml + buf * T::BUF + q / PR * S + (q % PR) * VPC) = v.c;
+    }
+  };
+  uint32_t row = 0;
+  bool rok = false;
+  // columns 16 b + 4 kr .. of the lane's row; p: that row's column 4 kr
+  auto load_quad = [&](const TI* p, int b) {
+    Quad v;
+    const uint32_t left = N - 16u * b - (VEC ? (uint32_t)VPC : 1u);           // the block's last group or column
+#pragma unroll
+    for (int e = 0; e < 4; e += VEC ? VPC : 1) {
+      const uint32_t at = b + 1 < NB ? 4u * kr + e : min(4u * kr + e, left);
+      const TI* q = p + 16 * b + (b + 1 < NB ? (int64_t)e : (int64_t)at - 4 * kr);
+      if constexpr (VEC) v.c[e / VPC] = *reinterpret_cast<const Chunk*>(q);
+      else v.v[e] = *q;
+    }
+    return v;
+  };
+  auto store_quad = [&](TI* p, int b, const Quad& v) {
+#pragma unroll
+    for (int e = 0; e < 4; e += VEC ? VPC : 1)
+      if (rok && (b + 1 < NB || 16u * b + 4u * kr + e < N)) {
+        if constexpr (VEC) *reinterpret_cast<Chunk*>(p + 16 * b + e) = v.c[e / VPC];
+        else p[16 * b + e] = v.v[e];
+      }
+  };
+  // the operands of M for half a block of the contraction: two steps of two column blocks
+  struct Ops {
+    TI v[2][2];
+  };
+  auto ops = [&](const TI* m, int t, bool two) {
+    Ops o;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int k = 16 * (t >> 1) + 2 * (t & 1) + r;
+      o.v[r][0] = m[k * S];
+      o.v[r][1] = two ? m[k * S + 16] : TI(0);
+    }
+    return o;
+  };
+  load_m(0);
+  store_m(0, 0);
+  if constexpr (T::RESIDENT) {
+    for (uint32_t s = 1; s < 2u * NCH; ++s) {
+      load_m(s);
+      store_m(s, s);
+    }
+  }
+  __syncthreads();
+  uint32_t step = 0;                                  // chunks so far (streamed)
+  auto begin = [&](uint32_t s) -> const TI* {         // chunk s of this tile; the next one's loads start
+    __builtin_amdgcn_sched_barrier(0);                // a chunk's operands in registers at a time
+    if constexpr (T::RESIDENT) return ml + s * T::BUF;
+    load_m(s + 1 < 2u * NCH ? s + 1 : 0u);
+    __builtin_amdgcn_sched_barrier(0);
+    return ml + (step & 1u) * T::BUF;
+  };
+  auto end = [&](uint32_t s) {
+    if constexpr (!T::RESIDENT) {
+      __builtin_amdgcn_sched_barrier(0);
+      store_m(s + 1 < 2u * NCH ? s + 1 : 0u, ~step & 1u);    // its last readers passed the previous barrier
+      ++step;
+      __syncthreads();
+    }
+  };
+  double sqr[NCH], sq0[NCH];
+#pragma unroll
+  for (int j = 0; j < NCH; ++j) sqr[j] = sq0[j] = 0.0;
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    row = tile * ST_ROWS + wave * 16u + ci;
+    rok = row < n;
+    const uint64_t at = (uint64_t)min(row, n - 1u) * N + 4u * kr;
+    Quad u[NB], res[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) u[b] = load_quad(U + at, b);
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const bool two = 2 * j + 1 < NB;                // static
+      const TI* m = begin(j) + 4u * kr * S + mc;
+      Quad h[2];
+      h[0] = load_quad(HU + at, 2 * j);
+      if (two) h[1] = load_quad(HU + at, 2 * j + 1);
+      acc_t acc[2] = {zero_acc<acc_t>(), zero_acc<acc_t>()};
+      Ops o[2];
+      o[0] = ops(m, 0, two);
+#pragma unroll
+      for (int t = 0; t < 2 * NB; ++t) {
+        if (t + 1 < 2 * NB) o[(t + 1) & 1] = ops(m, t + 1, two);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const TI a0[1] = {o[t & 1].v[r][0]}, a1[1] = {o[t & 1].v[r][1]}, xv[1] = {u[t >> 1].v[2 * (t & 1) + r]};
+          acc[0] = mma<KIND, TI>(a0, xv, acc[0]);
+          if (two) acc[1] = mma<KIND, TI>(a1, xv, acc[1]);
+        }
+      }
+      double v[8];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          v[4 * q + r] = 0.0;
+          if (2 * j + q < NB) {
+            const TI x = h[q].v[r] - (TI)acc[q][r];
+            res[2 * j + q].v[r] = x;
+            v[4 * q + r] = rok ? (double)x * (double)x : 0.0;
+          }
+        }
+      sqr[j] += scatter_sum8(v, ci);
+      end(j);
+    }
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const bool two = 2 * j + 1 < NB;
+      const TI* m = begin(NCH + j) + 4u * kr * S + mc;
+      acc_t ay[2] = {zero_acc<acc_t>(), zero_acc<acc_t>()}, ar[2] = {zero_acc<acc_t>(), zero_acc<acc_t>()};
+      Ops o[2];
+      o[0] = ops(m, 0, two);
+#pragma unroll
+      for (int t = 0; t < 2 * NB; ++t) {
+        if (t + 1 < 2 * NB) o[(t + 1) & 1] = ops(m, t + 1, two);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const TI a0[1] = {o[t & 1].v[r][0]}, a1[1] = {o[t & 1].v[r][1]};
+          const TI xv[1] = {u[t >> 1].v[2 * (t & 1) + r]}, rv[1] = {res[t >> 1].v[2 * (t & 1) + r]};
+          ay[0] = mma<KIND, TI>(a0, xv, ay[0]);
+          ar[0] = mma<KIND, TI>(a0, rv, ar[0]);
+          if (two) {
+            ay[1] = mma<KIND, TI>(a1, xv, ay[1]);
+            ar[1] = mma<KIND, TI>(a1, rv, ar[1]);
+          }
+        }
+      }
+      double v[8];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        Quad yv, rv;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          yv.v[r] = (TI)ay[q][r];
+          rv.v[r] = (TI)-ar[q][r];
+          v[4 * q + r] = rok && 2 * j + q < NB ? (double)rv.v[r] * (double)rv.v[r] : 0.0;
+        }
+        if (2 * j + q < NB) {
+          store_quad(Y + at, 2 * j + q, yv);
+          store_quad(R0 + at, 2 * j + q, rv);
+        }
+      }
+      sq0[j] += scatter_sum8(v, ci);
+      end(NCH + j);
+    }
+  }
+  // a lane's sums belong to column 32 j + 16 (ci % 8 / 4) + 4 kr + ci % 4; then the waves in order
+  double* red = reinterpret_cast<double*>(strip_lds);
+  __syncthreads();                                    // M is no longer read
+#pragma unroll
+  for (int j = 0; j < NCH; ++j) {
+    const uint32_t col = 32u * j + 16u * (ci >> 2 & 1u) + 4u * kr + (ci & 3u);
+    if (ci < 8u) {
+      red[wave * 256u + col] = sq0[j];
+      red[wave * 256u + 128u + col] = sqr[j];
+    }
+  }
+  __syncthreads();
+  for (uint32_t c = threadIdx.x; c < 2u * N; c += ST_WG) {
+    const uint32_t at = c < N ? c : 128u + c - N;
+    double t = 0.0;
+#pragma unroll
+    for (uint32_t w = 0; w < ST_WG / 64; ++w) t += red[w * 256u + at];
+    part[(uint64_t)blockIdx.x * 2u * N + c] = t;
+  }
+}
+
 // Square FP64 products of N x N matrices (the small solves for large N):
 // D = alpha op(A) op(B) + beta C + gamma I, op = transpose when ta / tb is
 // set.  Work-group tile 64 x 64 (4 waves of 32 x 32), operands straight from
@@ -1293,6 +1574,45 @@ hipError_t rowmm_t(ope_ctx* c, const TI* X0, const TI* M0, const TI* X1, const T
   return hipGetLastError();
 }
 
+template <typename TI, int KIND>
+hipError_t start_t(ope_ctx* c, const TI* U, const TI* HU, const TI* Lam, const TI* Linv, TI* Y, TI* R0,
+                   int64_t* nparts) {
+  const uint32_t n = (uint32_t)c->n, N = (uint32_t)c->N;
+  constexpr uint32_t VPC = 16 / (uint32_t)sizeof(TI);
+  auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
+  const bool aligned = N % VPC == 0 && al16(U) && al16(HU) && al16(Lam) && al16(Linv) && al16(Y) && al16(R0);
+  const uint32_t ntiles = (n + ST_ROWS - 1) / ST_ROWS;
+  uint32_t gx = 0;
+  ProfScope ps(c, OPE_KERNEL_ROWMM);
+  auto go = [&](auto nbt, auto vect) {
+    constexpr int NB = decltype(nbt)::value;
+    constexpr bool VEC = decltype(vect)::value;
+    using T = StartTile<TI, NB>;
+    gx = (uint32_t)std::min<int64_t>(std::min<int64_t>(ntiles, 256 * T::OCC), c->part_cap / (2 * (int64_t)N));
+    if (gx < 1) return;
+    hipLaunchKernelGGL((k_start<TI, KIND, NB, VEC>), dim3(gx), dim3(ST_WG),
+                       std::max<size_t>(T::LDS, ST_WG / 64 * 256 * sizeof(double)), c->stream, U, HU, Lam, Linv, Y, R0,
+                       n, N, ntiles, c->part);
+  };
+  auto width = [&](auto vect) {
+    switch ((N + 15) / 16) {
+      case 1: go(std::integral_constant<int, 1>{}, vect); break;
+      case 2: go(std::integral_constant<int, 2>{}, vect); break;
+      case 3: go(std::integral_constant<int, 3>{}, vect); break;
+      case 4: go(std::integral_constant<int, 4>{}, vect); break;
+      case 5: go(std::integral_constant<int, 5>{}, vect); break;
+      case 6: go(std::integral_constant<int, 6>{}, vect); break;
+      case 7: go(std::integral_constant<int, 7>{}, vect); break;
+      default: go(std::integral_constant<int, 8>{}, vect); break;
+    }
+  };
+  if (aligned) width(std::true_type{});
+  else width(std::false_type{});
+  if (gx < 1) return hipErrorInvalidValue;
+  *nparts = gx;
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gram(ope_ctx* c, const double* A, int64_t lda, int na, const double* B, int64_t ldb, int nb,
@@ -1335,4 +1655,12 @@ hipError_t launch_rowmm_f32(ope_ctx* c, int kind, const float* X0, const float* 
   if (kind == MK_BF16)
     return rowmm_t<float, MK_BF16>(c, X0, M0, X1, M1, Cm, cbeta, ascale, Out, want_colsq, predicated, nparts);
   return rowmm_t<float, MK_F32>(c, X0, M0, X1, M1, Cm, cbeta, ascale, Out, want_colsq, predicated, nparts);
+}
+
+hipError_t launch_start(ope_ctx* c, const void* U, void* Y, void* R0, int64_t* nparts) {
+  if (c->prec == OPE_FP64)
+    return start_t<double, MK_F64>(c, (const double*)U, (const double*)c->HU, c->Lam, c->Linv, (double*)Y, (double*)R0,
+                                   nparts);
+  return start_t<float, MK_F32>(c, (const float*)U, (const float*)c->HU, c->Lam32, c->Linv32, (float*)Y, (float*)R0,
+                                nparts);
 }

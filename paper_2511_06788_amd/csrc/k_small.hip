@@ -1111,8 +1111,8 @@ hipError_t launch_convert(ope_ctx* c, const void* src, void* dst, int64_t count,
   return hipGetLastError();
 }
 
-hipError_t launch_cg_setup(ope_ctx* c, const double* rho0) {
-  hipLaunchKernelGGL(k_cg_setup, dim3(1), dim3(SW), 0, c->stream, c->rcol, rho0, c->cnorm2, c->eta_rel, c->eta_floor,
+hipError_t launch_cg_setup(ope_ctx* c, const double* rho0, const double* rcol) {
+  hipLaunchKernelGGL(k_cg_setup, dim3(1), dim3(SW), 0, c->stream, rcol, rho0, c->cnorm2, c->eta_rel, c->eta_floor,
                      (uint32_t)c->N, c->rho, c->target, c->alpha, c->beta, c->active, c->sc);
   return hipGetLastError();
 }

@@ -166,40 +166,52 @@ hipError_t apply_mass(ope_ctx* c, const void* X, void* Y) {
   return e;
 }
 
-// HU, Grams C and Lam, the small prep kernel (energy, drift, Lam^{-1}) and the
-// residual R = HU - U Lam written over HU with its column norms in c->rcol.
+// HU, Grams C and Lam, and the small prep kernel (energy, drift, Lam^{-1}).
 // FP64: everything in FP64.  Mixed: FP32 stencil, C and Lam accumulated in
-// FP64 on the matrix cores (energy and drift stay FP64), R in FP32.
+// FP64 on the matrix cores (energy and drift stay FP64).
+ope_status phase_matrices(ope_ctx* c, const void* Uv) {
+  const int N = (int)c->N;
+  HIPCHK(launch_apply_h(c, Uv, c->HU));
+  if (c->prec == OPE_FP64) {
+    const double* U = (const double*)Uv;
+    HIPCHK(launch_gram(c, U, N, N, U, N, N, c->n, c->C));
+    HIPCHK(launch_gram_sym(c, U, N, (const double*)c->HU, N, N, c->n, c->Lam));     // H is symmetric
+  } else {
+    const float* U = (const float*)Uv;
+    HIPCHK(launch_gram_f32(c, MK_F64, U, N, N, U, N, N, c->n, c->C));
+    HIPCHK(launch_gram_f32(c, MK_F64, U, N, N, (const float*)c->HU, N, N, c->n, c->Lam));
+  }
+  HIPCHK(launch_prep_small(c));
+  return OPE_OK;
+}
+
+// phase_matrices, then the residual R = HU - U Lam (mixed: in FP32) written over
+// HU with its column norms in c->rcol.
 ope_status phase_residual(ope_ctx* c, const void* Uv) {
   const int N = (int)c->N;
   int64_t np = 0;
-  HIPCHK(launch_apply_h(c, Uv, c->HU));
   if (c->prec == OPE_FP64 && c->has_mass) {
     // generalized problem: C = U^T M U, Lam = U^T H U, R = HU - MU Lam, and the
     // Step-1 right-hand sides M u_j set the CG tolerances (their norms)
     const double* U = (const double*)Uv;
     double* HU = (double*)c->HU;
     double* MU = (double*)c->Rb[1];
+    HIPCHK(launch_apply_h(c, Uv, c->HU));
     HIPCHK(apply_mass(c, U, MU));
     HIPCHK(launch_gram(c, U, N, N, MU, N, N, c->n, c->C));
     HIPCHK(launch_gram(c, U, N, N, HU, N, N, c->n, c->Lam));
     HIPCHK(launch_prep_small(c));
     HIPCHK(launch_colsq(c, MU, N, N, c->cnorm2));
     HIPCHK(launch_rowmm(c, MU, c->Lam, nullptr, nullptr, HU, 1.0, -1.0, HU, 1, 0, &np));
-  } else if (c->prec == OPE_FP64) {
-    const double* U = (const double*)Uv;
-    double* HU = (double*)c->HU;
-    HIPCHK(launch_gram(c, U, N, N, U, N, N, c->n, c->C));
-    HIPCHK(launch_gram_sym(c, U, N, HU, N, N, c->n, c->Lam));     // H is symmetric
-    HIPCHK(launch_prep_small(c));
-    HIPCHK(launch_rowmm(c, U, c->Lam, nullptr, nullptr, HU, 1.0, -1.0, HU, 1, 0, &np));
   } else {
-    const float* U = (const float*)Uv;
-    float* HU = (float*)c->HU;
-    HIPCHK(launch_gram_f32(c, MK_F64, U, N, N, U, N, N, c->n, c->C));
-    HIPCHK(launch_gram_f32(c, MK_F64, U, N, N, HU, N, N, c->n, c->Lam));
-    HIPCHK(launch_prep_small(c));
-    HIPCHK(launch_rowmm_f32(c, MK_F32, U, c->Lam32, nullptr, nullptr, HU, 1.0, -1.0, HU, 1, 0, &np));
+    const ope_status st = phase_matrices(c, Uv);
+    if (st != OPE_OK) return st;
+    if (c->prec == OPE_FP64)
+      HIPCHK(launch_rowmm(c, (const double*)Uv, c->Lam, nullptr, nullptr, (const double*)c->HU, 1.0, -1.0,
+                          (double*)c->HU, 1, 0, &np));
+    else
+      HIPCHK(launch_rowmm_f32(c, MK_F32, (const float*)Uv, c->Lam32, nullptr, nullptr, (const float*)c->HU, 1.0, -1.0,
+                              (float*)c->HU, 1, 0, &np));
   }
   HIPCHK(launch_reduce_cols(c, c->part, np, N, c->rcol, RED_PLAIN));
   return OPE_OK;
@@ -470,7 +482,27 @@ ope_status phase_warm_start(ope_ctx* c, const void* Uv) {
                             (float*)c->Rb[0], 1, 0, &np));
   }
   HIPCHK(launch_reduce_cols(c, c->part, np, N, c->rho0, RED_PLAIN));
-  HIPCHK(launch_cg_setup(c, c->rho0));
+  HIPCHK(launch_cg_setup(c, c->rho0, c->rcol));
+  if (c->mg_on) HIPCHK(pcg_begin(c));
+  return OPE_OK;
+}
+
+// phase_residual and phase_warm_start of one iterate.  Where nothing else needs R
+// and both N x N matrices fit beside a wave's rows (N <= 128), one launch forms Y,
+// r and both residuals' column norms; R itself is not kept.
+ope_status phase_start(ope_ctx* c, const void* Uv) {
+  if (c->N > OPE_MAX_N_ONE_WG || (c->prec == OPE_FP64 && (c->has_mass || c->recycle))) {
+    const ope_status st = phase_residual(c, Uv);
+    return st != OPE_OK ? st : phase_warm_start(c, Uv);
+  }
+  const int N = (int)c->N;
+  int64_t np = 0;
+  c->cg_on_d = 0;
+  const ope_status st = phase_matrices(c, Uv);
+  if (st != OPE_OK) return st;
+  HIPCHK(launch_start(c, Uv, c->Y, c->Rb[0], &np));
+  HIPCHK(launch_reduce_cols(c, c->part, np, 2 * N, c->rho0, RED_PLAIN));
+  HIPCHK(launch_cg_setup(c, c->rho0, c->rho0 + N));
   if (c->mg_on) HIPCHK(pcg_begin(c));
   return OPE_OK;
 }
@@ -583,9 +615,7 @@ ope_status run_step(ope_ctx* c, void* U, double tau, ope_step_info* info, double
   if (converged) *converged = false;
   ope_status st = mixed_renormalize(c, U);
   if (st != OPE_OK) return st;
-  st = phase_residual(c, U);
-  if (st != OPE_OK) return st;
-  st = phase_warm_start(c, U);
+  st = phase_start(c, U);
   if (st != OPE_OK) return st;
   if (res_tol >= 0.0) {
     st = sync_and_read_scalars(c);
@@ -641,7 +671,7 @@ ope_status learned_core(ope_ctx* c, void* Uv, double tau, bool* accepted, ope_st
   HIPCHK(hipMemcpyAsync(c->hsc2, c->sc, sizeof(OpeScalars), hipMemcpyDeviceToHost, c->stream));
   st = phase_residual(c, U);
   if (st != OPE_OK) return st;
-  HIPCHK(launch_cg_setup(c, c->rcol));   // the residual scalar from the column norms
+  HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));   // the residual scalar from the column norms
   st = sync_and_read_scalars(c);
   if (st != OPE_OK) return st;
   const OpeScalars& s = *c->hsc;
@@ -691,7 +721,7 @@ ope_status solve_learned(ope_ctx* c, void* U, double tau, double res_tol, int32_
     if (!ready) {
       st = phase_residual(c, U);
       if (st != OPE_OK) return st;
-      HIPCHK(launch_cg_setup(c, c->rcol));
+      HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));
       st = sync_and_read_scalars(c);
       if (st != OPE_OK) return st;
       if (c->hsc->err != 0) return (ope_status)c->hsc->err;
@@ -924,8 +954,7 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
     HIPCHK(hipStreamWaitEvent(c->stream, b->start, 0));
     ope_status st = ensure_ws(c);
     if (st == OPE_OK) st = mixed_renormalize(c, U[i]);
-    if (st == OPE_OK) st = phase_residual(c, U[i]);
-    if (st == OPE_OK) st = phase_warm_start(c, U[i]);
+    if (st == OPE_OK) st = phase_start(c, U[i]);
     if (st == OPE_OK && hipMemcpyAsync(c->hsc, c->sc, sizeof(OpeScalars), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
       st = OPE_EHIP;
     if (st != OPE_OK) {
@@ -1528,7 +1557,7 @@ ope_status ope_residual(ope_ctx* c, const void* U, double* residual, double* rit
   const int N = (int)c->N;
   ope_status st = phase_residual(c, U);
   if (st != OPE_OK) return st;
-  HIPCHK(launch_cg_setup(c, c->rcol));   // computes the residual scalar from the column norms
+  HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));   // computes the residual scalar from the column norms
   if (ritz) {
     HIPCHK(launch_sym_eig(c, c->Lam, c->rho0));
     HIPCHK(hipMemcpyAsync(c->hbuf, c->rho0, sizeof(double) * N, hipMemcpyDeviceToHost, c->stream));
@@ -1749,9 +1778,7 @@ ope_status ope_solve(ope_ctx* c, void* U, double tau, double res_tol, int32_t ma
 
 // Residual phase and Step-1 warm start of the current iterate, scalars on the host.
 static ope_status prepare_iterate(ope_ctx* c, void* U) {
-  ope_status st = phase_residual(c, U);
-  if (st != OPE_OK) return st;
-  st = phase_warm_start(c, U);
+  ope_status st = phase_start(c, U);
   if (st != OPE_OK) return st;
   st = sync_and_read_scalars(c);
   if (st != OPE_OK) return st;
@@ -1808,8 +1835,7 @@ static ope_status solve_adaptive(ope_ctx* c, void* U, const ope_solve_opts* o, o
       st = phase_update(c, U, tau);
       if (st != OPE_OK) return st;
       HIPCHK(hipMemcpyAsync(c->hsc2, c->sc, sizeof(OpeScalars), hipMemcpyDeviceToHost, c->stream));
-      st = phase_residual(c, U);
-      if (st == OPE_OK) st = phase_warm_start(c, U);
+      st = phase_start(c, U);
       if (st == OPE_OK) st = sync_and_read_scalars(c);
       if (st != OPE_OK) return st;
       if (c->hsc2->err != 0) return (ope_status)c->hsc2->err;    // the step failed; U is unchanged
@@ -1883,7 +1909,7 @@ ope_status ope_step_learned(ope_ctx* c, void* U, double tau, ope_step_info* info
   if (accepted) *accepted = 0;
   st = phase_residual(c, U);
   if (st != OPE_OK) return st;
-  HIPCHK(launch_cg_setup(c, c->rcol));
+  HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));
   st = sync_and_read_scalars(c);
   if (st != OPE_OK) return st;
   if (c->hsc->err != 0) {
@@ -2149,8 +2175,7 @@ ope_status ope_batch_capture(ope_batch* b, void* const* U, double tau, int32_t c
     for (int i = 0; i < P; ++i) {
       ope_ctx* c = b->ctx[i];
       HIPCHK(hipStreamWaitEvent(c->stream, b->cap_fork, 0));
-      ope_status st = phase_residual(c, U[i]);
-      if (st == OPE_OK) st = phase_warm_start(c, U[i]);
+      ope_status st = phase_start(c, U[i]);
       if (st != OPE_OK) return st;
       if (shared[i]) {
         HIPCHK(hipEventRecord(b->done[i], c->stream));
@@ -2463,7 +2488,7 @@ ope_status ope_residual_d(ope_ctx* c, const void* U, double* d_residual, double*
   WSCHK(c);
   ope_status st = phase_residual(c, U);
   if (st != OPE_OK) return st;
-  HIPCHK(launch_cg_setup(c, c->rcol));   // computes the residual scalar from the column norms
+  HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));   // computes the residual scalar from the column norms
   if (d_residual) HIPCHK(launch_scalar_copy(c, 1, d_residual));
   if (d_drift) HIPCHK(launch_scalar_copy(c, 2, d_drift));
   return OPE_OK;

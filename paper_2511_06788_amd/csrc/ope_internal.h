@@ -299,6 +299,7 @@ hipError_t launch_resid0(ope_ctx* c, const double* U, const double* HY, double* 
 // mixed precision: FP32 blocks, kind MK_F64 / MK_F32 / MK_BF16
 hipError_t launch_gram_f32(ope_ctx* c, int kind, const float* A, int64_t lda, int na, const float* B,
                            int64_t ldb, int nb, int64_t rows, double* out);
+hipError_t launch_start(ope_ctx* c, const void* U, void* Y, void* R0, int64_t* nparts);
 hipError_t launch_rowmm_f32(ope_ctx* c, int kind, const float* X0, const float* M0, const float* X1,
                             const float* M1, const float* Cm, double cbeta, double ascale, float* Out,
                             int want_colsq, int predicated, int64_t* nparts);
@@ -307,7 +308,7 @@ hipError_t launch_convert(ope_ctx* c, const void* src, void* dst, int64_t count,
 
 // one-work-group FP64 kernels
 hipError_t launch_prep_small(ope_ctx* c);
-hipError_t launch_cg_setup(ope_ctx* c, const double* rho0);
+hipError_t launch_cg_setup(ope_ctx* c, const double* rho0, const double* rcol);
 hipError_t launch_small_solve(ope_ctx* c, const double* Sb, const double* T, double tau,
                               double* Z, double* A, double* B);
 // mixed: M = I + tau/2 (S_a - S_b) + tau^2/4 (P^T P - S_b^T (C-I) S_b), B = M^{-1}; Z32 = [-2(I-B) ; tau B]

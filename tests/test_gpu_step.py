@@ -259,3 +259,38 @@ def test_full_size_step_building_blocks_match_oracle(full_size):
     bound = 4 * N * np.finfo(np.float64).eps * (np.abs(U[rows]) @ np.abs(Z[:N]) + np.abs(Y[rows]) @ np.abs(Z[N:]))
     assert np.all(np.abs(Un[rows] - ref) <= bound + 1e-300)
 
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("m,N", [((43, 3), 1), ((127, 1), 8), ((16, 8), 15), ((43, 3), 16), ((43, 3), 17),
+                                 ((37, 29), 32), ((37, 29), 33), ((43, 3), 48), ((43, 3), 49), ((37, 29), 64),
+                                 ((37, 29), 80), ((37, 29), 81), ((43, 3), 96), ((37, 29), 112), ((37, 29), 113),
+                                 ((37, 29), 127), ((16, 9), 128), ((37, 29), 128)])
+def test_start_of_a_step_matches_the_separate_products(m, N, precision):
+    """The fused start of a step against the separate residual product of
+    ope_residual, and Y with its residual against the dense solve: with no
+    iteration allowed to stop early, U after the step is right only if r is
+    U - H Y.  Rows and widths around the tiles.  Residuals agree to the rounding
+    of two summation orders, 8 N eps of |H| sqrt(N) relative to |Lam|."""
+    import torch
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    op = O.Operator(g.m, g.h, np.zeros(g.n))
+    U0 = W.initial_block(g.n, N, 7)
+    dt = torch.float32 if precision else torch.float64
+    eps = 2.0 ** -23 if precision else 2.0 ** -52
+    Ud = torch.from_numpy(U0).to("cuda").to(dt)
+    U = Ud.double().cpu().numpy()
+    HU = O.apply_H(op, U)
+    lam = np.linalg.norm(U.T @ HU)
+    tau = 1.0
+    ref = O.steps_1_to_4(U, O.GSolver(op), tau)["U"]
+    say(f"start of a step m={m} N={N} precision={precision}")
+    with ope.Context(g, np.zeros(g.n), N, precision=precision) as ctx:
+        ope.ope_set_inner(ctx.handle, 0.0, 1e-6 if precision else 1e-13, 20000)
+        res, _, _ = ope.ope_residual(ctx.handle, Ud, N, want_ritz=False)
+        info = ope.ope_step(ctx.handle, Ud, tau, allow_maxit=False)
+        Un = Ud.double().cpu().numpy()
+    hmax = 4.0 * np.sum(1.0 / np.asarray(g.h) ** 2)
+    assert abs(info.residual - res) * lam <= 8 * N * eps * hmax * np.sqrt(N)
+    step = np.max(np.abs(ref - U))
+    assert np.max(np.abs(Un - ref)) <= (1e-2 * step + 4 * eps if precision else 1e-11)
