@@ -413,23 +413,30 @@ struct TShape {
 constexpr uint32_t MG_TWG = 1024;                 // threads of a tiled work-group (at most)
 constexpr uint32_t MG_TLDS_BYTES = 36864;         // LDS of one plane's tile and ring
 
-// Slices of a row: as many as keep a slice at least 8 vector groups wide (a
-// 128-byte run of FP64 pairs), dividing NV.
+// Slices of a row: halved as long as that keeps a slice at least 8 vector groups
+// wide (a 128-byte run of FP64 pairs) and divides NV.  Where that leaves more than
+// MG_SLICE of a row of more than two such, slices of equal width and a shorter last
+// one: a whole row of an odd NV leaves a tile of so few columns that its ring is
+// several times as large (V-cycles of one step at 64^3, FP64: N = 250, NV = 125,
+// 12.6 -> 3.5 ms, N = 130 4.3 -> 2.4, N = 200 3.7 -> 3.2; 45x38x51, N = 45 0.75 ->
+// 0.69; but NV = 25 in two slices, N = 50 at 48^3, 0.56 -> 0.60).
+constexpr uint32_t MG_SLICE = 16;
 uint32_t tslices(uint32_t NV) {
   uint32_t ns = 1;
   while (NV % (2 * ns) == 0 && NV / (2 * ns) >= 8) ns *= 2;
+  if (NV > 2 * MG_SLICE && NV / ns > MG_SLICE) ns = (NV + MG_SLICE - 1) / MG_SLICE;
   return ns;
 }
 
 TShape tshape(uint32_t m0, uint32_t m1, uint32_t m2, uint32_t NV, uint32_t N, uint32_t esz) {
   TShape s;
   s.NS = tslices(NV);
-  s.NVS = NV / s.NS;
+  s.NVS = (NV + s.NS - 1) / s.NS;
   // columns per work-group: as many as MG_TWG threads hold (measured at 64^3,
   // N = 128: 1024 threads on 16 x 8 tiles beat 512 on 8 x 8 and 256 on 8 x 4,
   // whose rings cost more than the extra work-groups per compute unit gain)
   const uint32_t P = std::max(1u, MG_TWG / s.NVS);
-  const uint64_t rowb = (uint64_t)(N / s.NS) * esz;      // LDS bytes of one column's slice
+  const uint64_t rowb = (uint64_t)s.NVS * (N / NV) * esz;      // LDS bytes of one column's slice
   uint32_t tx = 1;
   while ((tx * 2) * (tx * 2) <= P) tx *= 2;       // a square tile of powers of two, x side first
   if (tx * tx * 2 <= P) tx *= 2;
@@ -476,12 +483,12 @@ struct TPos {
 
 __device__ __forceinline__ TPos tpos(const TShape& ts, uint32_t L) {
   TPos q;
-  q.xt = L % ts.nxt;
-  uint32_t r = L / ts.nxt;
+  q.sl = L % ts.NS;                               // first: neighbouring slices share 128-byte lines
+  uint32_t r = L / ts.NS;
+  q.xt = r % ts.nxt;
+  r /= ts.nxt;
   q.yt = r % ts.nyt;
-  r /= ts.nyt;
-  q.zc = r % ts.nzc;
-  q.sl = r / ts.nzc;
+  q.zc = r / ts.nyt;
   q.row = (q.zc * ts.nyt + q.yt) * ts.nxt + q.xt;
   return q;
 }
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tstencil(const T* __restrict__ b,
   const uint32_t x0 = wp.xt * ts.TX, y0 = wp.yt * ts.TY;
   const uint32_t x = x0 + tx, y = y0 + ty;
   const bool inb = x < g.m0 && y < g.m1;
-  const bool act = vec_active<VW>(active, v);
+  const bool act = v < N / VW && vec_active<VW>(active, v);    // (the last slice may be short)
   if (!__syncthreads_or(act ? 1 : 0)) return;     // every column of the slice has stopped
   const bool own = inb && act;
   const uint32_t z0 = wp.zc * ts.ZC, z1 = z0 + ts.ZC < g.m2 ? z0 + ts.ZC : g.m2;
@@ -742,11 +749,11 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
   const uint32_t x0 = wp.xt * ts.TX, y0 = wp.yt * ts.TY;
   const uint32_t x = x0 + tx, y = y0 + ty;
   const bool inb = x < g.m0 && y < g.m1;
-  const bool act = vec_active<VW>(active, v);
+  const bool act = v < N / VW && vec_active<VW>(active, v);    // (the last slice may be short)
   if (!__syncthreads_or(act ? 1 : 0)) {          // every column of the slice has stopped
     if constexpr (DOTS) {
       const uint32_t SC = ts.NVS * VW, c0 = wp.sl * SC;
-      for (uint32_t c = t; c < SC; c += blockDim.x) {
+      for (uint32_t c = t; c < SC && c0 + c < N; c += blockDim.x) {
         part[(uint64_t)wp.row * 2 * N + c0 + c] = 0.0;
         part[(uint64_t)wp.row * 2 * N + N + c0 + c] = 0.0;
       }
@@ -912,7 +919,7 @@ __global__ __launch_bounds__(MG_TWG) void k_mg_tpost(const T* __restrict__ b, co
 #pragma unroll
       for (int k = 0; k < VW; ++k) red[t * VW + k] = q == 0 ? srz[k] : srr[k];
       __syncthreads();
-      for (uint32_t c = t; c < SC; c += blockDim.x) {
+      for (uint32_t c = t; c < SC && c0 + c < N; c += blockDim.x) {
         const uint32_t cv = c / VW, ck = c % VW;
         double a = 0.0;
         for (uint32_t l = 0; l < P; ++l) a += red[(l * NVS + cv) * VW + ck];

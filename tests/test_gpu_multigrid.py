@@ -356,6 +356,28 @@ def test_vcycle_at_the_edges_of_the_fused_coarse_end(m, N):
     assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(ref))
 
 
+@pytest.mark.parametrize("N", [33, 45, 66, 72, 99, 130, 250])
+def test_vcycle_and_its_dot_products_with_a_short_last_slice(N):
+    """Widths whose vector groups do not divide into slices: the V-cycle, and one
+    and three PCG iterations from the dot products of its last sweep."""
+    from paper_2511_06788_amd import ope
+    p = W.wells_3d(m=13, N=N, seed=11)
+    op = _op(p)
+    R = np.random.default_rng(N).standard_normal((p.grid.n, N))
+    ref = O.Hierarchy(op).vcycle(R)
+    U = W.initial_block(p.grid.n, N, 5)
+    say(f"mg short slice N={N}")
+    with _ctx(p) as c:
+        Z = empty_dev(p.grid.n, N)
+        ope.ope_mg_vcycle(c.handle, to_dev(R), Z)
+        assert np.max(np.abs(to_host(Z) - ref)) <= 1e-12 * np.max(np.abs(ref))
+        for k in (1, 3):
+            Yd = empty_dev(p.grid.n, N)
+            ope.ope_source_solve(c.handle, to_dev(U), Yd, None, 1e-15, k, allow_maxit=True)
+            Y_ref = O.pcg_source(op, U, None, tol=1e-15, max_iter=k)
+            assert np.max(np.abs(to_host(Yd) - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
+
+
 def test_vcycle_on_a_plane_of_more_than_4_gib():
     """A 2D block of 2^29 FP64 values and more takes 64-bit offsets: the same
     columns in a block half as wide, below the line, give the same V-cycle."""
