@@ -874,9 +874,19 @@ void march_shape(ope_ctx* c, int q_max, int mc_override, int order, int nt, int 
   // N = 128 in FP64, 512-byte chunks sweep 1.17x faster than 128-byte ones);
   // else 8 vector columns, one 128-byte line of FP64 or FP32 per grid point
   // and work-group (at N = 512, 96^3, 32-vector chunks were 5% slower).
+  // Rows that are no whole number of 128-byte lines: equal chunks of at most 128
+  // vector columns, the whole row where it fits, since a chunk shares the lines at
+  // its ends with its neighbours (sweeps A and B of one step in FP64, 8-vector
+  // chunks / at most 32 / 64 / 128: 45x38x51 N = 45 0.62 / 0.42 / 0.37 / 0.37 ms,
+  // 64^3 N = 130 3.86 / 2.50 / 2.09 / 1.96, 250 7.54 / 3.97 / 3.68 / 3.79, 48^3
+  // N = 300 2.97 / 1.95 / 2.02 / 1.81, mixed 127 1.56 / 0.74 / 0.56 / 0.45).
   // `narrow` asks for 8 vector columns at any row width.
   if (narrow) ms.ncv = NV < 8u ? NV : 8u;
   else if (NV <= 32u) ms.ncv = NV;
+  else if (c->N * (c->prec == OPE_FP64 ? 8 : 4) % 128 != 0) {
+    const uint32_t k = (NV + 127u) / 128u;
+    ms.ncv = (NV + k - 1) / k;
+  }
   else if (NV <= 64u) ms.ncv = NV % 32u == 0 ? 32u : (NV % 16u == 0 ? 16u : 8u);
   else ms.ncv = 8u;
   ms.pp = OPE_WG / ms.ncv;

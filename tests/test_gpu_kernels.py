@@ -330,6 +330,29 @@ def test_capped_cg_equals_textbook_iterates(k, graphs):
     assert np.max(np.abs(Y - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
 
 
+@pytest.mark.parametrize("m", [(131, 127), (27, 25, 26)])
+@pytest.mark.parametrize("N", [33, 35, 45, 66, 72, 99, 130, 258, 300])
+def test_sweeps_of_rows_that_end_inside_a_line(m, N):
+    """Grids past the one-launch CG, rows of no whole number of 128-byte lines (and
+    one of 33, 258 and 300 values: one chunk, two of unequal width): H X and
+    one and three plain CG iterations against the oracle's."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    V = np.random.default_rng(N).uniform(0.0, 50.0, g.n)
+    op = O.Operator(g.m, g.h, V)
+    U = W.initial_block(g.n, N, 4)
+    say(f"sweeps m={m} N={N}")
+    with ope.Context(g, V, N) as ctx:
+        Ud, Yd = to_dev(U), empty_dev(g.n, N)
+        ope.ope_apply_h(ctx.handle, Ud, Yd)
+        assert np.max(np.abs(to_host(Yd) - O.apply_H(op, U))) <= stencil_bound(op, U)
+        for k in (1, 3):
+            its = ope.ope_source_solve(ctx.handle, Ud, Yd, None, 1e-14, k, allow_maxit=True)
+            Y_ref = O.cg_source(op, U, None, tol=1e-14, max_iter=k)
+            assert its == k
+            assert np.max(np.abs(to_host(Yd) - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
+
+
 def test_energy_residual_ritz_match_oracle():
     from paper_2511_06788_amd import ope
     p = W.wells_3d(m=14, N=24, seed=2)
