@@ -1019,7 +1019,8 @@ def step_rate(ope, torch, p, args, multigrid):
             if kname == "gram":
                 rec["TFLOP/s_fp64"] = 2.0 * n * N * N / (rec["avg_ms"] * 1e-3) / 1e12
             if kname == "rowmm":
-                rec["TFLOP/s_fp64_N_by_N"] = 2.0 * n * N * N / (rec["avg_ms"] * 1e-3) / 1e12
+                # five products of a step (residual, Y, its residual, Step 4's two) in two or four launches
+                rec["TFLOP/s_fp64_N_by_N"] = 5 * 2.0 * n * N * N / (rec["ms_per_step"] * 1e-3) / 1e12
             kernels[kname] = rec
         res["kernels"] = kernels
         # window-independent cost: an inner iteration (both sweeps, the column
