@@ -274,9 +274,12 @@ hipError_t cg_iteration(ope_ctx* c, int it) {
 }
 
 // Preconditioned CG start, after the CG set-up (targets and flags from |r0|^2):
-// z0 = B r0 and rho = r0^T z0.
+// z0 = B r0 and rho = r0^T z0, for every column, also those already below their
+// target: the sweeps run over whole rows and multiply a stopped column's z by
+// alpha = 0, so it has to be finite, and later V-cycles skip stopped columns and
+// leave what this one wrote (never what an earlier call or the allocation left).
 hipError_t pcg_begin(ope_ctx* c) {
-  const hipError_t e = mg_vcycle(c, c->Rb[0], c->mg_Z, c->active, true);
+  const hipError_t e = mg_vcycle(c, c->Rb[0], c->mg_Z, nullptr, true);
   return e != hipSuccess ? e : launch_pcg_start(c);
 }
 

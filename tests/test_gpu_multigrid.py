@@ -400,3 +400,35 @@ def test_vcycle_on_a_plane_of_more_than_4_gib():
     scale = float(out[0].abs().max())
     assert float((out[1][:, :64] - out[0]).abs().max()) <= 1e-13 * scale
     assert float((out[1][:, 64:].flip(1) - out[0]).abs().max()) <= 1e-13 * scale
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("m,N", [((13, 13, 13), 2), ((26, 27, 25), 4)])
+def test_step_ignores_what_an_earlier_vcycle_left_in_stopped_columns(m, N, precision):
+    """A column below its target before the first iteration (an exact eigenvector
+    beside rough ones) is skipped by the V-cycles' coarse levels; a V-cycle of a
+    block of NaN before the step must not reach it.  The step equals a fresh
+    context's bit for bit."""
+    import torch
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    mode = np.array([[1.0]])
+    for k in g.m[::-1]:
+        mode = np.kron(mode, np.sqrt(2.0 / (k + 1)) * np.sin(np.pi * np.arange(1, k + 1) / (k + 1))[:, None])
+    rest = np.random.default_rng(N).standard_normal((g.n, N - 1))
+    rest -= mode @ (mode.T @ rest)
+    U0 = np.concatenate([mode, np.linalg.qr(rest)[0]], axis=1)
+    dt = torch.float32 if precision else torch.float64
+    out = []
+    for poison in (False, True):
+        say(f"stopped column after a NaN V-cycle m={m} N={N} precision={precision} poison={poison}")
+        with ope.Context(g, np.zeros(g.n), N, precision=precision) as c:
+            ope.ope_set_multigrid(c.handle, True)
+            if poison:
+                R = torch.full((g.n, N), float("nan"), dtype=dt, device="cuda")
+                ope.ope_mg_vcycle(c.handle, R, torch.empty_like(R))
+            U = torch.from_numpy(U0).to("cuda").to(dt).contiguous()
+            info = ope.ope_step(c.handle, U, 1.0)
+            out.append((U.cpu().numpy(), info.energy, info.residual, info.inner_iterations))
+    assert np.all(np.isfinite(out[1][0])) and out[1][3] > 0
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
