@@ -518,12 +518,14 @@ __global__ void k_to_f64(const float* __restrict__ src, double* __restrict__ dst
 // ---------------------------------------------------------------------------
 
 // Householder vector of x (entries k + 1 .. N - 1): v = x with the entry k + 1
-// replaced by v0, beta = 2 / v^T v; e is the off-diagonal it leaves.  beta = 0
-// when x is already (x_{k+1}, 0, ..., 0).
+// replaced by v0, beta = 2 / v^T v; e is the off-diagonal it leaves.  sigma: the
+// sum of squares past the entry k + 1.  Up to tiny (house_tiny) those entries
+// count as zero and x as already reduced (beta = 0): the squares of smaller ones
+// lose their digits to the exponent range, and beta its finiteness.
 struct House {
   double v0, beta, e;
-  __device__ House(double alpha, double sigma) {
-    if (sigma == 0.0) {
+  __device__ House(double alpha, double sigma, double tiny) {
+    if (sigma <= tiny) {
       v0 = 0.0;
       beta = 0.0;
       e = alpha;
@@ -536,6 +538,11 @@ struct House {
   }
 };
 
+// The line for a matrix A of Frobenius norm fro: what is dropped of a column moves
+// the eigenvalues by at most 1e-22 |A|, far below a backward-stable method's
+// eps |A| (or by 1e-145, where |A|^2 itself is that small).
+__device__ __forceinline__ double house_tiny(double fro) { return fmax(1e-44 * fro * fro, 1e-290); }
+
 // N <= 128, the matrix in the registers of four waves (thread t: column t % 128,
 // rows t / 128 + 2 r; one wave per SIMD, since what every wave repeats below
 // grows with their number: 16 waves of 16 rows took 462 us at N = 128).  Every
@@ -546,7 +553,7 @@ constexpr int TW = 256;       // threads
 constexpr int TR = 64;        // rows per thread
 constexpr int TB = 8;         // rows skipped together once they are reduced
 
-__global__ __launch_bounds__(TW) void k_tridiag_reg(const double* __restrict__ Asrc, uint32_t N,
+__global__ __launch_bounds__(TW) void k_tridiag_reg(const double* __restrict__ Asrc, uint32_t N, const double* __restrict__ fro,
                                                     double* __restrict__ dg, double* __restrict__ od) {
   __shared__ double x[2][128];
   __shared__ double part[2][128];
@@ -555,6 +562,7 @@ __global__ __launch_bounds__(TW) void k_tridiag_reg(const double* __restrict__ A
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t q = wave >> 1;                   // row group
   const bool upper = (wave & 1u) != 0;            // the wave's columns: 64 + lane
+  const double tiny = house_tiny(*fro);
   double w[TR];
 #pragma unroll
   for (int r = 0; r < TR; ++r) {
@@ -576,7 +584,7 @@ __global__ __launch_bounds__(TW) void k_tridiag_reg(const double* __restrict__ A
     const double alpha = xk[k + 1u];
     if (threadIdx.x == 0) ds[k] = xk[k];
     const double sigma = wave_sum((lane > k + 1u ? va * va : 0.0) + (lane + 64u > k + 1u ? vb * vb : 0.0));
-    const House h(alpha, sigma);
+    const House h(alpha, sigma, tiny);
     if (threadIdx.x == 0) es[k] = h.e;
     if (h.beta == 0.0) continue;                  // uniform: every wave formed the same sums
     if (lane <= k + 1u) va = lane == k + 1u ? h.v0 : 0.0;
@@ -624,13 +632,15 @@ __global__ __launch_bounds__(TW) void k_tridiag_reg(const double* __restrict__ A
 // 128 < N <= 512, the matrix in global memory W: thread t owns the rows
 // gi, gi + G, ... of column j (G groups of NC = N rounded up to 64 threads).
 __global__ __launch_bounds__(SW) void k_tridiag(const double* __restrict__ Asrc, double* __restrict__ W, uint32_t N,
-                                                double* __restrict__ dg, double* __restrict__ od) {
+                                                const double* __restrict__ fro, double* __restrict__ dg,
+                                                double* __restrict__ od) {
   __shared__ double x[2][512], ws[512], part[SW];
   __shared__ double ds[512], es[512];             // written out at the end
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t NC = (N + 63u) & ~63u, G = SW / NC;
   const uint32_t j = threadIdx.x % NC, gi = threadIdx.x / NC;
   const bool own = gi < G && j < N;
+  const double tiny = house_tiny(*fro);
   if (own)
     for (uint32_t i = gi; i < N; i += G)
       W[(uint64_t)i * N + j] = 0.5 * (Asrc[(uint64_t)i * N + j] + Asrc[(uint64_t)j * N + i]);
@@ -643,7 +653,7 @@ __global__ __launch_bounds__(SW) void k_tridiag(const double* __restrict__ Asrc,
     double sg = 0.0;
     for (uint32_t i = lane; i < N; i += 64u) sg += i > k + 1u ? xk[i] * xk[i] : 0.0;
     const double sigma = wave_sum(sg);
-    const House h(xk[k + 1u], sigma);
+    const House h(xk[k + 1u], sigma, tiny);
     if (threadIdx.x == 0) {
       ds[k] = xk[k];
       es[k] = h.e;
@@ -1134,13 +1144,13 @@ hipError_t launch_small_solve(ope_ctx* c, const double* Sb, const double* T, dou
   return hipGetLastError();
 }
 
-hipError_t launch_sym_eig(ope_ctx* c, const double* Asym, double* evals) {
+hipError_t launch_lam_eig(ope_ctx* c, double* evals) {
   const uint32_t N = (uint32_t)c->N;
   double *dg = c->B, *od = c->B + N;               // scratch between steps; 2 N - 1 values (N = 1: one)
   if (N <= OPE_MAX_N_ONE_WG)
-    hipLaunchKernelGGL(k_tridiag_reg, dim3(1), dim3(TW), 0, c->stream, Asym, N, dg, od);
+    hipLaunchKernelGGL(k_tridiag_reg, dim3(1), dim3(TW), 0, c->stream, c->Lam, N, &c->sc->lam_fro, dg, od);
   else
-    hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(SW), 0, c->stream, Asym, c->Wsm, N, dg, od);
+    hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(SW), 0, c->stream, c->Lam, c->Wsm, N, &c->sc->lam_fro, dg, od);
   hipLaunchKernelGGL(k_bisect, dim3(N), dim3(64), 0, c->stream, dg, od, N, evals);
   return hipGetLastError();
 }

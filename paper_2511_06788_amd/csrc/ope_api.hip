@@ -1562,7 +1562,7 @@ ope_status ope_residual(ope_ctx* c, const void* U, double* residual, double* rit
   if (st != OPE_OK) return st;
   HIPCHK(launch_cg_setup(c, c->rcol, c->rcol));   // computes the residual scalar from the column norms
   if (ritz) {
-    HIPCHK(launch_sym_eig(c, c->Lam, c->rho0));
+    HIPCHK(launch_lam_eig(c, c->rho0));
     HIPCHK(hipMemcpyAsync(c->hbuf, c->rho0, sizeof(double) * N, hipMemcpyDeviceToHost, c->stream));
   }
   st = sync_and_read_scalars(c);

@@ -315,7 +315,8 @@ hipError_t launch_small_solve(ope_ctx* c, const double* Sb, const double* T, dou
 hipError_t launch_small_solve_delta(ope_ctx* c, const double* Sb, const double* Tperp, double tau);
 // FP32 copy of an N x N matrix
 hipError_t launch_small_to_f32(ope_ctx* c, const double* src, float* dst, int64_t count);
-hipError_t launch_sym_eig(ope_ctx* c, const double* Asym, double* evals);
+// eigenvalues of sym(Lam), ascending, after launch_prep_small (|Lam|_F in the scalars)
+hipError_t launch_lam_eig(ope_ctx* c, double* evals);
 // D = alpha op(A) op(B) + beta C + gamma I for N x N FP64 matrices (FP64 matrix
 // cores); *skip != 0 makes it a no-op; res (nullable) receives per-work-group
 // sums of (delta_ij - D_ij)^2, ((N + 63) / 64)^2 values

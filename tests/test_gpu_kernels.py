@@ -397,6 +397,33 @@ def test_ritz_values_at_the_edges_of_the_reduction(N, start):
     assert np.max(np.abs(ritz - ref)) <= 1e-12 * ref[-1]
 
 
+@pytest.mark.parametrize("N", [3, 128, 130])
+@pytest.mark.parametrize("scale", [1e-160, 1e-130, 1e-30])
+def test_ritz_values_of_orbitals_that_hardly_overlap(N, scale):
+    """Unit vectors on grid points apart from each other, each with a value of
+    `scale` on the first one's point: Lam is diagonal but for entries whose
+    squares underflow, are tiny, or are below the rounding of the diagonal.
+    Within 1e-14 of the largest value: bisection and the Gram round on the
+    diagonal alone."""
+    from paper_2511_06788_amd import ope
+    m = 11
+    g = W.unit_box_grid((m, m, m))
+    V = np.random.default_rng(N).uniform(0.0, 500.0, g.n)
+    even = np.arange(0, m, 2)
+    pts = (even[None, None, :] + m * (even[None, :, None] + m * even[:, None, None])).ravel()[:N]
+    U = np.zeros((g.n, N))
+    U[pts, np.arange(N)] = 1.0
+    U[pts[0], 1:] = scale
+    op = O.Operator(g.m, g.h, V)
+    Lam = U.T @ O.apply_H(op, U)
+    assert np.any(Lam[0, 1:] != 0.0)
+    ref = np.linalg.eigvalsh(0.5 * (Lam + Lam.T))
+    say(f"ritz of hardly overlapping orbitals N={N} scale={scale}")
+    with ope.Context(g, V, N) as ctx:
+        _, ritz, _ = ope.ope_residual(ctx.handle, to_dev(U), N)
+    assert np.max(np.abs(ritz - ref)) <= 1e-14 * ref[-1]
+
+
 def test_autotune_single_context_keeps_results():
     """ope_autotune picks the fastest sweep shape by timing; H X and the CG
     solution then still match the oracle (a shape changes only the summation
