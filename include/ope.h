@@ -483,7 +483,7 @@ ope_status ope_batch_solve(ope_batch* batch, void* const* U, double tau, double 
 /* shared = 1: Step 1's CG sweeps and column reductions of all
  * problems whose column sums fit one work-group (at most 128 columns and
  * 2^15 partial values), except those on grids of at most 16384 points (their
- * CG is one launch each in any mode), run as one launch per phase and class of problems
+ * CG is one launch each in any mode, see ope_set_graphs), run as one launch per phase and class of problems
  * (storage type, vector width, passes per plane, split x lines, line tiles)
  * on a batch stream, each launch's work-groups spread over (problem, tile)
  * work items of every problem's own sweep shape, each problem over all XCDs; same kernels and summation order as the per-problem launches,
@@ -534,7 +534,8 @@ ope_status ope_batch_autotune(ope_batch* batch, int32_t* tuned);
 ope_status ope_autotune(ope_ctx* ctx);
 
 /* On grids of at most 16384 points the unpreconditioned CG is one launch (one
- * work-group per column), with no host check and no graph; elsewhere
+ * work-group per column), with no host check and no graph, as long as it is
+ * capped at 65536 iterations or fewer; elsewhere
  * Step 1's CG runs in chunks of 4 iterations between host convergence checks
  * (preconditioned: 1, or 2 with graphs on);
  * with graphs on each chunk is one replay of a HIP graph captured once per

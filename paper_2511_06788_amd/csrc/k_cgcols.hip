@@ -186,13 +186,18 @@ void pick(ope_ctx* c, void* y, int32_t max_iter, const T* diag) {
 
 }  // namespace
 
-// The grid fits one work-group (16 points per thread, p in at most 128 KiB of
-// LDS) and the CG runs without the preconditioner.  While a kernel of the CG
-// sweeps is being timed the sweeps run, so that there is something to time.
-bool cg_cols_fits(const ope_ctx* c) {
+// The grid fits one work-group (pick: at most 512 threads of 32 points, p in at
+// most 128 KiB of LDS), the CG runs without the preconditioner, and the launch is
+// bounded: nothing on the host can stop it before max_iter iterations of 8 to 20 us
+// each, about a second at CGC_MAX_ITER; a caller who allows more gets the sweeps,
+// whose launches end after an iteration.  While a kernel of the CG sweeps is being
+// timed the sweeps run, so that there is something to time.
+constexpr int32_t CGC_MAX_ITER = 1 << 16;
+
+bool cg_cols_fits(const ope_ctx* c, int32_t max_iter) {
   const bool timed = c->prof_kernel == OPE_KERNEL_CG_SWEEP_A || c->prof_kernel == OPE_KERNEL_CG_SWEEP_B ||
                      c->prof_kernel == OPE_KERNEL_CG_SWEEP_B_Y || c->prof_kernel == OPE_KERNEL_CG_REDUCE;
-  return !c->mg_on && !timed && c->n <= 16384;
+  return !c->mg_on && !timed && c->n <= 16384 && max_iter <= CGC_MAX_ITER;
 }
 
 hipError_t launch_cg_cols(ope_ctx* c, void* y, int32_t max_iter) {

@@ -414,7 +414,7 @@ bool cg_converged(const ope_ctx* c, bool all_done) { return c->cg_in_flight ? cg
 // checked here, and *all_done stays open until the caller has synchronised the
 // stream (cg_converged).
 ope_status run_cg(ope_ctx* c, int32_t max_iter, int32_t* iters, bool* all_done) {
-  if (cg_cols_fits(c)) {
+  if (cg_cols_fits(c, max_iter)) {
     HIPCHK(cg_cols(c, max_iter));
     *iters = 0;
     *all_done = false;
@@ -770,7 +770,9 @@ struct BatchState {
 // already (a small grid) and its column sums fit one work-group's reduction (the same fixed-order sum its own steps use, so that
 // its shared-launch iterates equal those of its own launches bit for bit); its
 // work items are the tiles of its own sweep shape.
-bool shared_fits(const ope_ctx* c) { return !c->mg_on && reduce_few_fits(c) && !cg_cols_fits(c); }
+bool shared_fits(const ope_ctx* c, int32_t max_iter) {
+  return !c->mg_on && reduce_few_fits(c) && !cg_cols_fits(c, max_iter);
+}
 
 // The shared CG launches of a set of problems: classes of problems that one
 // kernel instance can sweep (storage type, vector width, passes per plane,
@@ -991,8 +993,8 @@ ope_status batch_round(ope_batch* b, void* const* U, double tau, double res_tol,
   for (int i = 0; i < P; ++i) {
     ope_ctx* c = b->ctx[i];
     c->cg_in_flight = 0;
-    shared[i] = go[i] && b->shared && shared_fits(c);
-    if (go[i] && cg_cols_fits(c)) {      // a small grid: the whole CG in one launch, its flags read at the end
+    shared[i] = go[i] && b->shared && shared_fits(c, c->max_iter);
+    if (go[i] && cg_cols_fits(c, c->max_iter)) {      // a small grid: the whole CG in one launch, its flags read at the end
       pending[i] = 0;
       if (cg_cols(c, c->max_iter) != hipSuccess) {
         bs.st[i] = OPE_EHIP;
@@ -2138,11 +2140,13 @@ ope_status ope_batch_capture(ope_batch* b, void* const* U, double tau, int32_t c
       return OPE_ENOMEM;
   }
   // problems in the shared launches (the batch's launch mode), the others run
-  // their CG on their own streams; flags of both kinds land in h_gflags
+  // their CG on their own streams; flags of both kinds land in h_gflags.  The route
+  // of a problem's CG is that of its eager steps (the larger of both caps)
+  auto cap = [&](const ope_ctx* c) { return std::max(c->max_iter, cg_iterations); };
   std::vector<int> members;
   std::vector<char> shared(P, 0);
   for (int i = 0; i < P; ++i)
-    if (b->shared && shared_fits(b->ctx[i])) {
+    if (b->shared && shared_fits(b->ctx[i], cap(b->ctx[i]))) {
       shared[i] = 1;
       members.push_back(i);
     }
@@ -2186,7 +2190,7 @@ ope_status ope_batch_capture(ope_batch* b, void* const* U, double tau, int32_t c
         continue;
       }
       // own launches, the whole step on the problem's stream
-      if (cg_cols_fits(c)) {
+      if (cg_cols_fits(c, cap(c))) {
         HIPCHK(launch_cg_cols(c, cg_y(c), cg_iterations));
       } else {
         for (int32_t it = 0; it < cg_iterations; ++it) HIPCHK(cg_iteration(c, it));

@@ -258,7 +258,7 @@ hipError_t launch_add_block(ope_ctx* c, double* y, const double* x);
 hipError_t launch_cg_setup_reduce(ope_ctx* c, int mode);
 // small grids (k_cgcols.hip): the whole CG, one work-group per column, from the
 // state in rho/target/active and r in Rb[0]; y is updated in place
-bool cg_cols_fits(const ope_ctx* c);
+bool cg_cols_fits(const ope_ctx* c, int32_t max_iter);
 hipError_t launch_cg_cols(ope_ctx* c, void* y, int32_t max_iter);
 
 // multigrid preconditioner (k_mg.hip)

@@ -529,3 +529,28 @@ def test_small_grid_cg_equals_textbook_cg(m, N, k):
     Y_ref = O.cg_source(op, U, Y0, tol=1e-14, max_iter=k, stats=st)
     assert its == st["iterations"]
     assert np.max(np.abs(Y - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
+
+
+@pytest.mark.parametrize("m,N", [((9, 7, 5), 3), ((128, 128), 5)])
+def test_small_grid_cg_runs_the_sweeps_past_its_iteration_cap(m, N):
+    """A CG that may run for more than 65536 iterations is not one launch: its
+    solution is that of the sweeps bit for bit (which run while one of them is
+    timed), and one that may not is the single launch's, whose dot products are
+    summed in another order."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    V = np.random.default_rng(N).uniform(0.0, 50.0, g.n)
+    U = to_dev(W.initial_block(g.n, N, 4))
+    out = {}
+    for cap, timed in ((65537, False), (65537, True), (65536, False)):
+        say(f"small-grid CG cap={cap} timed={timed}")
+        with ope.Context(g, V, N) as ctx:
+            if timed:
+                ope.ope_profile_begin(ctx.handle, ope.OPE_KERNEL_CG_SWEEP_A)
+            Yd = empty_dev(g.n, N)
+            ope.ope_source_solve(ctx.handle, U, Yd, None, 1e-9, cap)
+            if timed:
+                assert ope.ope_profile_end(ctx.handle)[0] > 0
+            out[cap, timed] = to_host(Yd)
+    assert np.array_equal(out[65537, False], out[65537, True])
+    assert not np.array_equal(out[65536, False], out[65537, True])
