@@ -480,17 +480,19 @@ ope_status ope_batch_step(ope_batch* batch, void* const* U, double tau, ope_step
  * test and no learned steps).  info: count entries, nullable. */
 ope_status ope_batch_solve(ope_batch* batch, void* const* U, double tau, double res_tol, int32_t max_steps,
                            ope_solve_info* info);
-/* shared = 1: Step 1's CG sweeps and column reductions of all
- * problems whose column sums fit one work-group (at most 128 columns and
- * 2^15 partial values), except those on grids of at most 16384 points (their
- * CG is one launch each in any mode, see ope_set_graphs), run as one launch per phase and class of problems
- * (storage type, vector width, passes per plane, split x lines, line tiles)
- * on a batch stream, each launch's work-groups spread over (problem, tile)
- * work items of every problem's own sweep shape, each problem over all XCDs; same kernels and summation order as the per-problem launches,
- * so the results are identical.  shared = 0 (default): every problem's CG
- * runs on its own stream.  Measured: on the 64-problem workload (grid edges
- * 24..48, N 16..128) per-problem launches are 4-8% faster, on a batch of large
- * problems alone slightly faster. */
+/* shared = 1: Step 1's CG sweeps and column reductions of all problems of at most
+ * 128 columns whose partial column sums fit one work-group (2^15 values), or whose
+ * rows are swept in the wide chunks of rows that are no whole 128-byte lines (see
+ * ope_set_sweep_shape; their sums then take two launches for all problems
+ * together), except those on grids of at most 16384 points (their CG is one launch
+ * each in any mode, see ope_set_graphs), run as one launch per phase and class of
+ * problems (storage type, vector width, passes per plane, split x lines, line
+ * tiles) on a batch stream, each launch's work-groups spread over (problem, tile)
+ * work items of every problem's own sweep shape, each problem over all XCDs; same
+ * kernels and summation order as the per-problem launches, so the results are
+ * identical.  shared = 0 (default): every problem's CG runs on its own stream.
+ * Measured: on the 64-problem workload (grid edges 24..48, N 16..128) per-problem
+ * launches are 4-8% faster, on a batch of large problems alone slightly faster. */
 ope_status ope_batch_set_shared(ope_batch* batch, int32_t shared);
 /* Graph-captured batched step: one HIP graph holding a whole step of every
  * problem (residual and warm start on the problems' streams, then exactly
@@ -559,9 +561,11 @@ ope_status ope_set_graphs(ope_ctx* ctx, int32_t enable);
  * chunk of every side line) instead of those of one side line;
  * OPE_SWEEP_NONTEMPORAL writes the swept outputs with non-temporal stores;
  * OPE_SWEEP_NARROW gives every work-group an 8-vector column chunk (by
- * default a work-group takes rows of at most 32 vector columns whole, rows
- * of up to 64 in chunks of the widest of 32, 16 and 8 vectors that divides
- * them, and wider rows in chunks of 8);
+ * default a work-group takes rows of at most 32 vector columns whole; wider
+ * rows that are no whole number of 128-byte lines whole up to 128 vectors, else
+ * in equal chunks of at most 128; of the others rows of up to 64 vectors in
+ * chunks of the widest of 32, 16 and 8 that divides them, and wider ones in
+ * chunks of 8);
  * OPE_SWEEP_LINES (3D grids) gives a work-group two adjacent side lines, one
  * per pass over an x segment of 256/c points (q is then 2), OPE_SWEEP_LINES4
  * four, two per pass over segments of half that, OPE_SWEEP_LINES8 eight, four

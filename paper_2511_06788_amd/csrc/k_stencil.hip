@@ -665,21 +665,43 @@ __device__ __forceinline__ void cg_finalise(uint32_t col, double tot, double* __
 }
 
 // First stage of the column sums of a [nrows][ncols] partial array: work-group
-// (column group x, y) sums rows [y rps, (y + 1) rps) of its 64 columns into
+// (column group cg, y) sums rows [y rps, (y + 1) rps) of its 64 columns into
 // stage[y][col], in a fixed order.
-__global__ __launch_bounds__(OPE_WG) void k_reduce_stage(const double* __restrict__ part, uint32_t nrows,
-                                                         uint32_t ncols, uint32_t rps, double* __restrict__ stage) {
-  __shared__ double red[OPE_WG];
+__device__ __forceinline__ void stage_sum(const double* __restrict__ part, uint32_t nrows, uint32_t ncols,
+                                          uint32_t rps, double* __restrict__ stage, uint32_t cg, uint32_t y,
+                                          double* red) {
   const uint32_t lc = threadIdx.x & 63u, grp = threadIdx.x >> 6;
-  const uint32_t col = blockIdx.x * 64u + lc;
-  const uint32_t w0 = blockIdx.y * rps, w1 = min(nrows, w0 + rps);
+  const uint32_t col = cg * 64u + lc;
+  const uint32_t w0 = y * rps, w1 = min(nrows, w0 + rps);
   double acc = 0.0;
   if (col < ncols)
     for (uint32_t w = w0 + grp; w < w1; w += 4) acc += part[(uint64_t)w * ncols + col];
   red[threadIdx.x] = acc;
   __syncthreads();
   if (grp == 0 && col < ncols)
-    stage[(uint64_t)blockIdx.y * ncols + col] = red[lc] + red[64 + lc] + red[128 + lc] + red[192 + lc];
+    stage[(uint64_t)y * ncols + col] = red[lc] + red[64 + lc] + red[128 + lc] + red[192 + lc];
+}
+
+__global__ __launch_bounds__(OPE_WG) void k_reduce_stage(const double* __restrict__ part, uint32_t nrows,
+                                                         uint32_t ncols, uint32_t rps, double* __restrict__ stage) {
+  __shared__ double red[OPE_WG];
+  stage_sum(part, nrows, ncols, rps, stage, blockIdx.x, blockIdx.y, red);
+}
+
+// The first stages of the problems that have one, as one launch: problem j owns
+// work-groups [stage_begin, next stage_begin), an empty range without a stage.
+__global__ __launch_bounds__(OPE_WG) void k_reduce_stage_batched(const ReduceJob* __restrict__ jobs, uint32_t njobs) {
+  __shared__ double red[OPE_WG];
+  const uint32_t b = blockIdx.x;
+  uint32_t lo = 0, hi = njobs;                 // the last problem that begins at or before b
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (jobs[mid].stage_begin <= b) lo = mid;
+    else hi = mid;
+  }
+  const ReduceJob& jb = jobs[lo];
+  const uint32_t ncg = (jb.ncols + 63u) / 64u, t = b - jb.stage_begin;
+  stage_sum(jb.part, jb.nrows, jb.ncols, jb.rps, jb.stage, t % ncg, t / ncg, red);
 }
 
 // Column sums of a [nrows][ncols] partial array in a fixed order (one
@@ -771,7 +793,9 @@ __global__ __launch_bounds__(RED_WG) void k_reduce_few(const double* __restrict_
   else cg_finalise<MODE>(col, tot, alpha, beta, rho, target, active, sc);
 }
 
-// Batched one-work-group column reductions: work-group j reduces problem j.
+// Batched column reductions, after k_reduce_stage_batched where a problem has a
+// first stage: work-group j reduces problem j in the order of k_reduce_few or, with
+// a first stage, of k_reduce_cols over the stage rows (256 threads to 64 columns).
 // par: the CG iteration's parity, which selects the half of the problem's
 // alpha array (2 ncols entries) the alpha reduction writes.
 template <int MODE>
@@ -780,7 +804,20 @@ __global__ __launch_bounds__(RED_WG) void k_reduce_batched(const ReduceJob* __re
   const ReduceJob& jb = jobs[blockIdx.x];
   uint32_t col;
   bool lead;
-  const double tot = few_cols_sum(jb.part, jb.nrows, jb.ncols, red, col, lead);
+  double tot = 0.0;
+  if (jb.stage_rows == 0) {
+    tot = few_cols_sum(jb.part, jb.nrows, jb.ncols, red, col, lead);
+  } else {
+    const uint32_t base = threadIdx.x & ~255u, lc = threadIdx.x & 63u, grp = (threadIdx.x >> 6) & 3u;
+    col = base / 4u + lc;
+    lead = grp == 0 && col < jb.ncols;
+    double acc = 0.0;
+    if (col < jb.ncols)
+      for (uint32_t w = grp; w < jb.stage_rows; w += 4) acc += jb.stage[(uint64_t)w * jb.ncols + col];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    if (lead) tot = red[base + lc] + red[base + 64 + lc] + red[base + 128 + lc] + red[base + 192 + lc];
+  }
   if (!lead) return;
   cg_finalise<MODE>(col, tot, jb.alpha + (uint64_t)par * jb.ncols, jb.beta, jb.rho, jb.target, jb.active, jb.sc);
 }
@@ -880,6 +917,11 @@ void march_shape(ope_ctx* c, int q_max, int mc_override, int order, int nt, int 
   // chunks / at most 32 / 64 / 128: 45x38x51 N = 45 0.62 / 0.42 / 0.37 / 0.37 ms,
   // 64^3 N = 130 3.86 / 2.50 / 2.09 / 1.96, 250 7.54 / 3.97 / 3.68 / 3.79, 48^3
   // N = 300 2.97 / 1.95 / 2.02 / 1.81, mixed 127 1.56 / 0.74 / 0.56 / 0.45).
+  // A wide chunk leaves a work-group few points, so the column sums have up to 16
+  // times the partial rows, often too many for the one-launch reduction; with it
+  // counted, a whole CG iteration in chunks of 8 / the widest the one launch still
+  // sums / up to 128: 48^3 N = 45 156 / 104 / 98 us, 99 358 / 250 / 225, 127 496 /
+  // 288 / 242, mixed 127 - / 234 / 131.
   // `narrow` asks for 8 vector columns at any row width.
   if (narrow) ms.ncv = NV < 8u ? NV : 8u;
   else if (NV <= 32u) ms.ncv = NV;
@@ -987,10 +1029,25 @@ hipError_t launch_y_flush(ope_ctx* c, hipStream_t s, void* y, const void* p, con
   return hipGetLastError();
 }
 
+uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps) {
+  *rps = 0;
+  if (ncols <= 128 && nrows * ncols <= FEW_MAX) return 0;
+  // about 32 rows per work-group, at most 64 work-groups per column group (enough
+  // work-groups to keep HBM busy), within the stage buffer
+  uint32_t S = (uint32_t)((nrows + 31) / 32);
+  if (S > 64) S = 64;
+  if ((int64_t)S * ncols > c->stage_cap) S = (uint32_t)(c->stage_cap / ncols);
+  if (S <= 1) return 1;
+  *rps = (uint32_t)((nrows + S - 1) / S);
+  return (uint32_t)((nrows + *rps - 1) / *rps);
+}
+
 hipError_t launch_reduce_cols(ope_ctx* c, const double* part, int64_t nrows, int64_t ncols, double* out, int mode,
                               double* alpha) {
   if (!alpha) alpha = c->alpha;
-  if (ncols <= 128 && nrows * ncols <= FEW_MAX) {
+  uint32_t rps = 0;
+  const uint32_t S = reduce_stage_rows(c, nrows, ncols, &rps);
+  if (S == 0) {
     const uint32_t nr = (uint32_t)nrows, nc = (uint32_t)ncols;
     switch (mode) {
       case RED_PLAIN:
@@ -1009,14 +1066,7 @@ hipError_t launch_reduce_cols(ope_ctx* c, const double* part, int64_t nrows, int
     return hipGetLastError();
   }
   const uint32_t ncg = (uint32_t)((ncols + 63) / 64);
-  // first stage: about 32 rows per work-group, at most 64 work-groups per
-  // column group (enough work-groups to keep HBM busy), within the stage buffer
-  uint32_t S = (uint32_t)((nrows + 31) / 32);
-  if (S > 64) S = 64;
-  if ((int64_t)S * ncols > c->stage_cap) S = (uint32_t)(c->stage_cap / ncols);
-  if (S > 1) {
-    const uint32_t rps = (uint32_t)((nrows + S - 1) / S);
-    S = (uint32_t)((nrows + rps - 1) / rps);
+  if (rps > 0) {
     hipLaunchKernelGGL(k_reduce_stage, dim3(ncg, S), dim3(OPE_WG), 0, c->stream, part, (uint32_t)nrows,
                        (uint32_t)ncols, rps, c->stage);
     part = c->stage;
@@ -1051,8 +1101,10 @@ hipError_t launch_resid0(ope_ctx* c, const double* U, const double* HY, double* 
   return hipGetLastError();
 }
 
-bool reduce_few_fits(const ope_ctx* c) {
-  return c->N <= 128 && march_rows(c) * c->N <= FEW_MAX;
+bool reduce_shared_fits(const ope_ctx* c) {
+  if (c->N > 128) return false;
+  const bool wide_chunks = c->N / c->vw > 32 && c->N * (c->prec == OPE_FP64 ? 8 : 4) % 128 != 0;
+  return wide_chunks || march_rows(c) * c->N <= FEW_MAX;
 }
 
 template <typename T, int VW, int Q, int MODE, bool FIRST, bool LN>
@@ -1106,8 +1158,11 @@ hipError_t launch_march_batched(hipStream_t s, int prec, int vw, int q, int halo
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_batched(hipStream_t s, int mode, int par, const ReduceJob* jobs, uint32_t njobs) {
+hipError_t launch_reduce_batched(hipStream_t s, int mode, int par, const ReduceJob* jobs, uint32_t njobs,
+                                 uint32_t stage_wgs) {
   if (njobs == 0) return hipSuccess;
+  if (stage_wgs > 0)
+    hipLaunchKernelGGL(k_reduce_stage_batched, dim3(stage_wgs), dim3(OPE_WG), 0, s, jobs, njobs);
   if (mode == RED_CG_ALPHA)
     hipLaunchKernelGGL((k_reduce_batched<RED_CG_ALPHA>), dim3(njobs), dim3(RED_WG), 0, s, jobs, (uint32_t)par);
   else

@@ -767,11 +767,11 @@ struct BatchState {
 };
 
 // A problem takes part in the shared launches when its CG is not one launch
-// already (a small grid) and its column sums fit one work-group's reduction (the same fixed-order sum its own steps use, so that
-// its shared-launch iterates equal those of its own launches bit for bit); its
-// work items are the tiles of its own sweep shape.
+// already (a small grid) and reduce_shared_fits (its column sums have the same fixed
+// order as in its own steps, so that its shared-launch iterates equal those of its
+// own launches bit for bit); its work items are the tiles of its own sweep shape.
 bool shared_fits(const ope_ctx* c, int32_t max_iter) {
-  return !c->mg_on && reduce_few_fits(c) && !cg_cols_fits(c, max_iter);
+  return !c->mg_on && reduce_shared_fits(c) && !cg_cols_fits(c, max_iter);
 }
 
 // The shared CG launches of a set of problems: classes of problems that one
@@ -788,6 +788,7 @@ struct CgPlan {
   uint32_t M = 0;       // problems (reduce jobs)
   uint32_t jobs = 0;    // march jobs
   uint32_t flags = 0;   // convergence flags gathered
+  uint32_t stage_wgs = 0;   // work-groups of the first stages of the column sums
 };
 
 void plan_cg(ope_batch* b, const std::vector<int>& members, int32_t* d_flags, CgPlan& pl) {
@@ -850,8 +851,12 @@ void plan_cg(ope_batch* b, const std::vector<int>& members, int32_t* d_flags, Cg
     ope_ctx* c = b->ctx[members[m]];
     ReduceJob& rj = b->h_rjobs[m];
     rj.part = c->part;
+    rj.stage = c->stage;
     rj.nrows = (uint32_t)march_rows(c);
     rj.ncols = (uint32_t)c->N;
+    rj.stage_rows = reduce_stage_rows(c, rj.nrows, rj.ncols, &rj.rps);
+    rj.stage_begin = pl.stage_wgs;
+    pl.stage_wgs += rj.stage_rows * ((rj.ncols + 63u) / 64u);
     rj.alpha = c->alpha;
     rj.beta = c->beta;
     rj.rho = c->rho;
@@ -906,9 +911,9 @@ hipError_t enqueue_cg(ope_batch* b, const CgPlan& pl, const MarchJob* mjobs, con
   for (int32_t k = 0, it = it0; k < count; ++k, ++it) {
     const int par = it & 1, first = it == 0;
     if ((e = sweep(BATCH_SW_PAP, par, first)) != hipSuccess) return e;
-    if ((e = launch_reduce_batched(s, RED_CG_ALPHA, par, rjobs, pl.M)) != hipSuccess) return e;
+    if ((e = launch_reduce_batched(s, RED_CG_ALPHA, par, rjobs, pl.M, pl.stage_wgs)) != hipSuccess) return e;
     if ((e = sweep(BATCH_SW_UPDATE, par, first)) != hipSuccess) return e;
-    if ((e = launch_reduce_batched(s, RED_CG_BETA, par, rjobs, pl.M)) != hipSuccess) return e;
+    if ((e = launch_reduce_batched(s, RED_CG_BETA, par, rjobs, pl.M, pl.stage_wgs)) != hipSuccess) return e;
   }
   return hipSuccess;
 }

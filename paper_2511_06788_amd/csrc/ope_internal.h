@@ -353,11 +353,14 @@ struct MarchJob {
   OpeScalars* sc;
   uint32_t wg_begin, wg_count;
 };
-// Batched column reductions (one work-group per problem; ncols <= 128) and the
-// gather of every problem's convergence flags into one array.
+// Batched column reductions (ncols <= 128; one work-group per problem, after a
+// first stage into `stage` where reduce_stage_rows asks for one: stage_rows > 0) and
+// the gather of every problem's convergence flags into one array.
 struct ReduceJob {
   const double* part;
+  double* stage;
   uint32_t nrows, ncols;
+  uint32_t stage_rows, rps, stage_begin;   // rows per stage row; the problem's first stage work-group
   double *alpha, *beta, *rho;   // alpha: 2 ncols (one half per iteration parity)
   const double* target;
   int32_t* active;
@@ -370,10 +373,18 @@ enum { BATCH_SW_PAP = 1, BATCH_SW_UPDATE = 2, BATCH_SW_UPDATE_Y = 3 };
 // ln: its work-groups take two side lines, one per pass (ly = 2)
 hipError_t launch_march_batched(hipStream_t s, int prec, int vw, int q, int halo, int ln, int mode, int first,
                                 const MarchJob* jobs, uint32_t njobs, uint32_t total_wgs);
-hipError_t launch_reduce_batched(hipStream_t s, int mode, int par, const ReduceJob* jobs, uint32_t njobs);
+hipError_t launch_reduce_batched(hipStream_t s, int mode, int par, const ReduceJob* jobs, uint32_t njobs,
+                                 uint32_t stage_wgs);
 hipError_t launch_gather_flags(hipStream_t s, const ReduceJob* jobs, uint32_t njobs);
-// whether a context's CG column sums fit the one-work-group reduction
-bool reduce_few_fits(const ope_ctx* c);
+// Stage rows of the column sums of a [nrows][ncols] partial array: 0 when one
+// work-group sums them all, else the rows of the stage array, each the sum of *rps
+// partial rows (*rps = 0: the few rows of more than 128 columns need no stage).
+uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps);
+// Whether a context's CG column sums are taken by the shared launches: N <= 128 and
+// either one work-group's sums or those of wide column chunks (march_shape), whose
+// partial rows are many because their work-groups cover few points, not because the
+// problem is large.
+bool reduce_shared_fits(const ope_ctx* c);
 
 // set-up kernels (k_check.hip): Lanczos extreme eigenvalues of H (FP64, one
 // vector, temporary device buffers), the Cholesky-based R^{-1} of an N x N SPD

@@ -171,3 +171,41 @@ def test_shared_launches_of_several_problems_past_the_one_launch_grids(prec, mon
     probs = [W.wells_3d(m=26, N=5, seed=1), W.wells_3d(m=27, N=16, seed=2), W.harmonic_2d_32(m=130)]
     monkeypatch.setattr("tests.test_gpu_batch._ragged", lambda: probs)
     test_batch_steps_equal_single_steps(prec, True)
+
+
+def _odd_rows(prec):
+    """Grids past the one-launch CG whose rows are no whole 128-byte lines: the wide
+    column chunks, whose column sums one work-group takes (the first) or does not
+    (the others), beside a row of whole lines."""
+    return [W.wells_3d(m=26, N=35 if prec else 45, seed=1), W.wells_3d(m=27, N=45, seed=2),
+            W.wells_3d(m=28, N=127, seed=3), W.wells_3d(m=26, N=99, seed=4), W.wells_3d(m=27, N=16, seed=5),
+            W.wells_3d(m=30, N=65, seed=6)]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_shared_launches_take_rows_swept_in_wide_chunks(prec):
+    """With shared launches on, none of these problems launches a sweep of its own,
+    and three steps equal the single steps bit for bit."""
+    from paper_2511_06788_amd import ope
+    probs = _odd_rows(prec)
+    tau = 0.5
+    say(f"shared launches of wide chunks prec={prec}")
+    with ope.Batch(probs, precision=prec) as b:
+        b.set_shared(True)
+        Ub = [_dev(p.U0, prec) for p in probs]
+        for i in range(len(probs)):
+            ope.ope_profile_begin(b.context(i), ope.OPE_KERNEL_CG_SWEEP_A)
+        infos = [b.step(Ub, tau) for _ in range(3)]
+        own = [ope.ope_profile_end(b.context(i))[0] for i in range(len(probs))]
+        Ub = [to_host(U) for U in Ub]
+    assert own == [0] * len(probs)
+    for i, p in enumerate(probs):
+        with ope.Context(p.grid, p.V, p.N, precision=prec) as ctx:
+            U = _dev(p.U0, prec)
+            ref = [ope.ope_step(ctx.handle, U, tau) for _ in range(3)]
+            assert np.array_equal(to_host(U), Ub[i]), i
+        for k in range(3):
+            a, c = ref[k], infos[k][i]
+            assert a.inner_iterations > 0
+            assert (a.energy, a.residual, a.drift, a.inner_iterations) == (c.energy, c.residual, c.drift,
+                                                                            c.inner_iterations), (i, k)

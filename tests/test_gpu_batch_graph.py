@@ -99,3 +99,35 @@ def test_capture_refusals():
         with pytest.raises(ope.OpeError) as ei:
             b.capture([_dev(p.U0, 0) for p in wide], 0.5, 8)
         assert ei.value.status == ope.OPE_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("shared", [True, False])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_replays_equal_eager_steps_past_the_one_launch_grids(prec, shared):
+    """Several problems of more than 16384 points, of one class and of others, among
+    them rows swept in wide chunks (two-launch column sums) and a 2D grid: with
+    shared launches the sweeps of all of them are the graph's."""
+    import torch
+    from paper_2511_06788_amd import ope
+    probs = [W.wells_3d(m=26, N=45, seed=1), W.wells_3d(m=27, N=16, seed=2), W.wells_3d(m=28, N=127, seed=3),
+             W.wells_3d(m=26, N=16, seed=4), W.harmonic_2d_32(m=130), W.wells_3d(m=27, N=99, seed=5)]
+    tau = 0.5
+    say(f"graph replays of larger grids prec={prec} shared={shared}")
+    with ope.Batch(probs, precision=prec) as b:
+        b.set_shared(shared)
+        Ug = [_dev(p.U0, prec) for p in probs]
+        Ue = [_dev(p.U0, prec) for p in probs]
+        Uo = [_dev(p.U0, prec) for p in probs]
+        b.capture(Ug, tau, 300)
+        for k in range(3):
+            ig = b.replay()
+            ie = b.step(Ue, tau)
+            for i in range(len(probs)):
+                a, c = ig[i], ie[i]
+                assert a.status == c.status == ope.OPE_OK, (k, i, a.status, c.status)
+                assert a.inner_iterations > 0
+                assert (a.energy, a.residual, a.drift, a.inner_iterations) == (
+                    c.energy, c.residual, c.drift, c.inner_iterations), (k, i)
+                assert torch.equal(Ug[i], Ue[i]), (k, i)
+            b.step(Uo, 2.0 * tau)
+            torch.cuda.synchronize()
