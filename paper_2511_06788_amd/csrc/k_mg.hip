@@ -992,7 +992,7 @@ __global__ __launch_bounds__(MG_WG) void k_mg_zrestrict(const T* __restrict__ R1
   }
 }
 
-// The PCG's scalars from the partial rows of r^T z and r^T r, in one
+// The PCG's scalars from the (partial or stage) rows of r^T z and r^T r, in one
 // work-group: column sums in a fixed order (thread t: column t % 2N, rows
 // t / 2N, t / 2N + G, ...; 8 running sums, then the G groups in order), then
 //   START: rho = r^T z (the CG set-up has already set the targets and the
@@ -1001,9 +1001,16 @@ __global__ __launch_bounds__(MG_WG) void k_mg_zrestrict(const T* __restrict__ R1
 //          running while |r|^2 > target (a non-positive r^T z, which an SPD
 //          preconditioner cannot give, stops it); flags (nullable, pinned host
 //          memory) receives a copy of the flags.
-// One launch instead of three (two reduction stages and the scalars): the rows
-// are few (a tile's slices share one), 2 us of reads even at 2N = 1024.
+// One launch instead of three (two reduction stages and the scalars) while the
+// partial values are few, as in 3D (a tile's slices share a row); more than PS_MAX of
+// them (2D, where the rows are the tiles of the whole plane) go through a first stage
+// over the chip.  One launch / with the stage, us: 64^3 N = 17 (240 x 34 values) 6.3
+// / 9.7, N = 128 FP32 (64 x 256) 7.6 / 10.0, 300^2 N = 16 (722 x 32) 8.9 / 9.4, 100^3
+// N = 64 (182 x 128) 11.4 / 10.7, 48^3 N = 250 (144 x 500) 19.6 / 11.6, 200^2 N = 65
+// (575 x 130) 16.1 / 10.1, 500^2 N = 128 (2016 x 256) 94 / 14.5, 1000^2 N = 128 (7875
+// x 256) 374 / 23.
 constexpr uint32_t PS_WG = 1024;
+constexpr int64_t PS_MAX = (int64_t)1 << 15;
 
 template <bool START>
 __global__ __launch_bounds__(PS_WG) void k_pcg_scalars(const double* __restrict__ part, uint32_t nrows, uint32_t N,
@@ -1404,15 +1411,22 @@ hipError_t mg_vcycle(ope_ctx* c, const void* r, void* z, const int32_t* active, 
   }
 }
 
-hipError_t launch_pcg_start(ope_ctx* c) {
-  hipLaunchKernelGGL(k_pcg_scalars<true>, dim3(1), dim3(PS_WG), 0, c->stream, c->mg_part, (uint32_t)c->mg_rows_used,
-                     (uint32_t)c->N, c->rho, c->beta, c->target, c->active, c->sc, (int32_t*)nullptr);
+template <bool START>
+static hipError_t launch_pcg_scalars(ope_ctx* c, int32_t* flags) {
+  const double* part = c->mg_part;
+  int64_t rows = c->mg_rows_used;
+  if (rows * 2 * c->N > PS_MAX) {
+    const hipError_t e = launch_reduce_stage(c, &part, &rows, 2 * c->N);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_pcg_scalars<START>, dim3(1), dim3(PS_WG), 0, c->stream, part, (uint32_t)rows, (uint32_t)c->N,
+                     c->rho, c->beta, c->target, c->active, c->sc, flags);
   return hipGetLastError();
 }
 
+hipError_t launch_pcg_start(ope_ctx* c) { return launch_pcg_scalars<true>(c, nullptr); }
+
 hipError_t launch_pcg_beta(ope_ctx* c, int32_t* flags) {
   ProfScope ps(c, OPE_KERNEL_CG_REDUCE);
-  hipLaunchKernelGGL(k_pcg_scalars<false>, dim3(1), dim3(PS_WG), 0, c->stream, c->mg_part, (uint32_t)c->mg_rows_used,
-                     (uint32_t)c->N, c->rho, c->beta, c->target, c->active, c->sc, flags);
-  return hipGetLastError();
+  return launch_pcg_scalars<false>(c, flags);
 }

@@ -1029,9 +1029,9 @@ hipError_t launch_y_flush(ope_ctx* c, hipStream_t s, void* y, const void* p, con
   return hipGetLastError();
 }
 
-uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps) {
+// Stage rows of a first stage, each the sum of *rps partial rows; *rps = 0: none.
+static uint32_t stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps) {
   *rps = 0;
-  if (ncols <= 128 && nrows * ncols <= FEW_MAX) return 0;
   // about 32 rows per work-group, at most 64 work-groups per column group (enough
   // work-groups to keep HBM busy), within the stage buffer
   uint32_t S = (uint32_t)((nrows + 31) / 32);
@@ -1042,12 +1042,27 @@ uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint3
   return (uint32_t)((nrows + *rps - 1) / *rps);
 }
 
+uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps) {
+  *rps = 0;
+  return ncols <= 128 && nrows * ncols <= FEW_MAX ? 0 : stage_rows(c, nrows, ncols, rps);
+}
+
+hipError_t launch_reduce_stage(ope_ctx* c, const double** part, int64_t* nrows, int64_t ncols) {
+  uint32_t rps = 0;
+  const uint32_t S = stage_rows(c, *nrows, ncols, &rps);
+  if (rps == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_reduce_stage, dim3((uint32_t)((ncols + 63) / 64), S), dim3(OPE_WG), 0, c->stream, *part,
+                     (uint32_t)*nrows, (uint32_t)ncols, rps, c->stage);
+  *part = c->stage;
+  *nrows = S;
+  return hipGetLastError();
+}
+
 hipError_t launch_reduce_cols(ope_ctx* c, const double* part, int64_t nrows, int64_t ncols, double* out, int mode,
                               double* alpha) {
   if (!alpha) alpha = c->alpha;
   uint32_t rps = 0;
-  const uint32_t S = reduce_stage_rows(c, nrows, ncols, &rps);
-  if (S == 0) {
+  if (reduce_stage_rows(c, nrows, ncols, &rps) == 0) {
     const uint32_t nr = (uint32_t)nrows, nc = (uint32_t)ncols;
     switch (mode) {
       case RED_PLAIN:
@@ -1066,12 +1081,8 @@ hipError_t launch_reduce_cols(ope_ctx* c, const double* part, int64_t nrows, int
     return hipGetLastError();
   }
   const uint32_t ncg = (uint32_t)((ncols + 63) / 64);
-  if (rps > 0) {
-    hipLaunchKernelGGL(k_reduce_stage, dim3(ncg, S), dim3(OPE_WG), 0, c->stream, part, (uint32_t)nrows,
-                       (uint32_t)ncols, rps, c->stage);
-    part = c->stage;
-    nrows = S;
-  }
+  const hipError_t e = launch_reduce_stage(c, &part, &nrows, ncols);
+  if (e != hipSuccess) return e;
   const dim3 grid(ncg), blk(OPE_WG);
   switch (mode) {
     case RED_PLAIN:

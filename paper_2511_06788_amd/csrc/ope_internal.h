@@ -380,6 +380,9 @@ hipError_t launch_gather_flags(hipStream_t s, const ReduceJob* jobs, uint32_t nj
 // work-group sums them all, else the rows of the stage array, each the sum of *rps
 // partial rows (*rps = 0: the few rows of more than 128 columns need no stage).
 uint32_t reduce_stage_rows(const ope_ctx* c, int64_t nrows, int64_t ncols, uint32_t* rps);
+// a first stage of [*nrows][ncols] partials into c->stage, where there are rows
+// enough for one; *part and *nrows become what is left to sum
+hipError_t launch_reduce_stage(ope_ctx* c, const double** part, int64_t* nrows, int64_t ncols);
 // Whether a context's CG column sums are taken by the shared launches: N <= 128 and
 // either one work-group's sums or those of wide column chunks (march_shape), whose
 // partial rows are many because their work-groups cover few points, not because the

@@ -432,3 +432,46 @@ def test_step_ignores_what_an_earlier_vcycle_left_in_stopped_columns(m, N, preci
             out.append((U.cpu().numpy(), info.energy, info.residual, info.inner_iterations))
     assert np.all(np.isfinite(out[1][0])) and out[1][3] > 0
     assert np.array_equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
+
+
+@pytest.mark.parametrize("m,N", [((97, 90), 128), ((200, 200), 65), ((500, 130), 40)])
+def test_pcg_scalars_of_many_partial_rows(m, N):
+    """Planes whose tiles give more partial sums than one work-group takes (the
+    last two; the first is just below): one and three PCG iterations against the
+    oracle's."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid(m)
+    V = np.random.default_rng(N).uniform(0.0, 40.0, g.n)
+    op = O.Operator(g.m, g.h, V)
+    U = W.initial_block(g.n, N, 5)
+    say(f"pcg scalars m={m} N={N}")
+    with ope.Context(g, V, N) as c:
+        ope.ope_set_multigrid(c.handle, True)
+        for k in (1, 3):
+            Yd = empty_dev(g.n, N)
+            its = ope.ope_source_solve(c.handle, to_dev(U), Yd, None, 1e-15, k, allow_maxit=True)
+            Y_ref = O.pcg_source(op, U, None, tol=1e-15, max_iter=k)
+            assert its == k
+            assert np.max(np.abs(to_host(Yd) - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
+
+
+def test_pcg_scalars_of_a_large_plane_are_not_one_work_groups():
+    """At 500^2, N = 128 the dot products' 4 MB of partial sums take about 15 us
+    over the chip and 93 us through one compute unit; a third of that is the line."""
+    import torch
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid((500, 500))
+    N = 128
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    U = torch.linalg.qr(torch.randn(g.n, N, dtype=torch.float64, device="cuda", generator=gen))[0].contiguous()
+    say("pcg scalars of a large plane")
+    with ope.Context(g, np.zeros(g.n), N) as c:
+        ope.ope_set_multigrid(c.handle, True)
+        Y = torch.empty_like(U)
+        ope.ope_source_solve(c.handle, U, Y, None, 1e-30, 2, allow_maxit=True)
+        ope.ope_profile_begin(c.handle, ope.OPE_KERNEL_CG_REDUCE)
+        ope.ope_source_solve(c.handle, U, Y, None, 1e-30, 12, allow_maxit=True)
+        _, _, tags, ms = ope.ope_profile_end_launches(c.handle, 64)
+    tags, ms = np.asarray(tags), np.asarray(ms)
+    beta = [ms[tags == k][-1] for k in range(12)]
+    assert min(beta) <= 0.031, beta
