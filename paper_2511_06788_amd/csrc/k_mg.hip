@@ -450,15 +450,21 @@ TShape tshape(uint32_t m0, uint32_t m1, uint32_t m2, uint32_t NV, uint32_t N, ui
   }
   s.nxt = (m0 + s.TX - 1) / s.TX;
   s.nyt = (m1 + s.TY - 1) / s.TY;
-  // z ranges: one work-group of this size fits a compute unit (256 of them), so a
-  // launch runs in rounds of 256, each as long as a range and about two planes of
-  // set-up; the count with the shortest total (64^3, N = 17, 80 tiles: 480
-  // work-groups of 11 planes in 2 rounds, against 560 of 10 in 3)
+  // z ranges: one work-group of this size fits a compute unit, two of at most half
+  // of it (256 or 512 places), so a launch runs in rounds of as many, each as long as
+  // a range and about two planes of set-up; the count with the shortest total (64^3,
+  // N = 17, 80 tiles: 480 work-groups of 11 planes in 2 rounds, against 560 of 10 in
+  // 3).  A few tiles of a long thin grid fill one round with more than 64 ranges
+  // each (V-cycle, us, at least 512 work-groups in all / 64 ranges at most in rounds
+  // of 256 / this rule: 16 x 16 x 1000, N = 4 86 / 99 / 76, 8 x 8 x 4000, N = 8 158 /
+  // 225 / 105, 4 x 4 x 8000, N = 16 205 / 333 / 114).
   const uint64_t tiles = (uint64_t)s.nxt * s.nyt * s.NS;
+  const uint64_t places = s.TX * s.TY * s.NVS > MG_TWG / 2 ? 256 : 512;
+  const uint64_t most = std::min<uint64_t>(m2, std::max<uint64_t>(64, places / tiles));
   uint64_t best = UINT64_MAX;
-  for (uint32_t nzc = 1; nzc <= m2 && nzc <= 64; ++nzc) {
+  for (uint32_t nzc = 1; nzc <= most; ++nzc) {
     const uint32_t ZC = (m2 + nzc - 1) / nzc, nr = (m2 + ZC - 1) / ZC;
-    const uint64_t cost = ((tiles * nr + 255) / 256) * (ZC + 2);
+    const uint64_t cost = ((tiles * nr + places - 1) / places) * (ZC + 2);
     if (cost < best) {
       best = cost;
       s.ZC = ZC;
