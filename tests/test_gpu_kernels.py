@@ -554,3 +554,60 @@ def test_small_grid_cg_runs_the_sweeps_past_its_iteration_cap(m, N):
             out[cap, timed] = to_host(Yd)
     assert np.array_equal(out[65537, False], out[65537, True])
     assert not np.array_equal(out[65536, False], out[65537, True])
+
+
+@pytest.fixture
+def solve_by_sweeps(monkeypatch):
+    """ope_source_solve with a CG sweep being timed, so that small grids run the
+    marching sweeps instead of their one-launch CG; asserts that they ran."""
+    from paper_2511_06788_amd import ope
+    real = ope.ope_source_solve
+
+    def solve(ctx, *args, **kw):
+        ope.ope_profile_begin(ctx, ope.OPE_KERNEL_CG_SWEEP_B)
+        its = real(ctx, *args, **kw)
+        assert ope.ope_profile_end(ctx)[0] >= its
+        return its
+
+    monkeypatch.setattr(ope, "ope_source_solve", solve)
+
+
+@pytest.mark.parametrize("q_max,chunks,flags", [(1, 1, 0), (2, 3, 1), (4, 0, 2), (4, 5, 3), (1, 0, 3),
+                                                 (2, 0, 9), (2, 3, 8), (1, 2, 11), (2, 0, 13),
+                                                 (2, 0, 17), (2, 2, 19), (2, 0, 21),
+                                                 (2, 0, 33), (2, 0, 36), (2, 2, 39), (2, 0, 37)])
+def test_sweep_shapes_agree_by_sweeps(solve_by_sweeps, q_max, chunks, flags):
+    """Every launch shape with the CG by the marching sweeps themselves."""
+    test_sweep_shapes_agree(q_max, chunks, flags)
+
+
+@pytest.mark.parametrize("N", [80, 96, 128])
+@pytest.mark.parametrize("narrow", [False, True])
+def test_wide_row_chunks_agree_by_sweeps(solve_by_sweeps, N, narrow):
+    """The column chunks of wide rows with the CG by the marching sweeps."""
+    test_wide_row_chunks_agree(N, narrow)
+
+
+def test_autotuned_context_by_sweeps(solve_by_sweeps):
+    """The tuned shape with the CG by the marching sweeps."""
+    test_autotune_single_context_keeps_results()
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 6])
+def test_capped_cg_equals_textbook_iterates_past_the_one_launch_grids(k, graphs):
+    """The paired y updates and the captured 4-iteration chunks (k = 5, 6: one chunk
+    and eager iterations) on a grid of more than 16384 points."""
+    from paper_2511_06788_amd import ope
+    p = W.wells_3d(m=26, N=6, seed=11)
+    op = _op(p)
+    U = W.initial_block(p.grid.n, p.N, 5)
+    say(f"capped CG 26^3 k={k} graphs={graphs}")
+    with _ctx(p) as ctx:
+        ope.ope_set_graphs(ctx.handle, graphs)
+        Yd = empty_dev(p.grid.n, p.N)
+        its = ope.ope_source_solve(ctx.handle, to_dev(U), Yd, None, 1e-14, k, allow_maxit=True)
+        Y = to_host(Yd)
+    Y_ref = O.cg_source(op, U, None, tol=1e-14, max_iter=k)
+    assert its == k
+    assert np.max(np.abs(Y - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))

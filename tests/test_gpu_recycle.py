@@ -99,3 +99,12 @@ def test_recycle_refusals():
         ope.ope_set_recycle(c.handle, False)
         Ud = to_dev(p.U0)
         ope.ope_step(c.handle, Ud, 10.0)                     # plain warm start again
+
+
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_capped_recycled_steps_by_sweeps_equal_oracle(k, monkeypatch):
+    """The capped plain-CG steps on a grid of more than 16384 points, whose CG runs
+    the marching sweeps."""
+    real = W.wells_3d
+    monkeypatch.setattr(W, "wells_3d", lambda m, N, seed: real(m=26, N=N, seed=seed))
+    test_capped_recycled_steps_equal_oracle(k, False)
