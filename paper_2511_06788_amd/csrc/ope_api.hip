@@ -1310,8 +1310,12 @@ ope_status ope_create(ope_ctx** out, const ope_op_desc* op, int64_t N, int32_t p
   }
 
   const int64_t blk = n * N;
+  // partial sums: those of the sweeps, the flat kernels and the row products, and a
+  // Gram's, at most as many splits as give about 1024 work-groups of 64 x 64 tiles or
+  // 512 of 128 x 128 (gram_splits takes what fits; a wider product of ope_gram is
+  // refused where not even one split does)
   const int64_t gtiles = ((N + 63) / 64) * ((N + 63) / 64);
-  const int64_t ltiles = ((N + 127) / 128) * ((N + 127) / 128);   // 128 x 128 tiles of the LDS Gram
+  const int64_t ltiles = ((N + 127) / 128) * ((N + 127) / 128);
   int64_t gram_parts = ((1024 + gtiles - 1) / gtiles) * N * N;
   if (((512 + ltiles - 1) / ltiles) * N * N > gram_parts) gram_parts = ((512 + ltiles - 1) / ltiles) * N * N;
   const int64_t row_parts = ((n + 63) / 64) * N;
@@ -1320,7 +1324,7 @@ ope_status ope_create(ope_ctx** out, const ope_op_desc* op, int64_t N, int32_t p
   if (gram_parts > pc) pc = gram_parts;
   if (row_parts > pc) pc = row_parts;
   c->part_cap = pc;
-  c->stage_cap = 64 * (N * N > 2 * N ? N * N : 2 * N);
+  c->stage_cap = 64 * 2 * N;     // at most 64 stage rows of at most 2N columns
 
   std::vector<double> hd((size_t)n);
   const double dsum = 2.0 * (g.cx + g.cy + g.cz);
@@ -1509,8 +1513,8 @@ ope_status ope_gram_noalloc(const double* A, int64_t lda, int64_t na, const doub
   const ope_status st = scratch_address(&part);
   if (st != OPE_OK) return st;
   // a context-free view for the shared launchers: the partial sums live in the
-  // scratch array, there is no stage buffer (the column sums then run in one
-  // pass), no timing and no per-step scalars
+  // scratch array, there is no stage buffer (k_gram_sum needs none), no timing and
+  // no per-step scalars
   ope_ctx v{};
   v.stream = (hipStream_t)stream;
   v.part = part;

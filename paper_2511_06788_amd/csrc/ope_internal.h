@@ -133,7 +133,7 @@ struct ope_ctx {
   // reductions
   double* part;                 // partial sums, part_cap doubles
   int64_t part_cap;
-  double* stage;                // second-stage partial sums
+  double* stage;                // first-stage column sums of long partial arrays
   int64_t stage_cap;
   // scalars
   OpeScalars* sc;               // device

@@ -139,3 +139,20 @@ def test_mixed_96_cubed_n512_steps():
     # the device drift check after every update keeps the block below the 1e-6 target
     assert i1.drift <= 1e-6 and i2.drift <= 1e-6 and drift <= 1e-6
     assert np.isfinite(res)
+
+
+def test_context_memory_at_the_largest_width():
+    """The N x N state of a context of 512 columns, its Newton-Schulz matrices and the
+    Gram's partial sums take about 100 MiB; a stage buffer of 64 N x N matrices, which
+    no reduction fills, took 128 MiB more."""
+    import torch
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid((9, 9, 9))
+    with ope.Context(g, np.zeros(g.n), 4):
+        pass                                     # whatever the first context loads
+    torch.cuda.synchronize()
+    say("context memory N=512")
+    before = torch.cuda.mem_get_info()[0]
+    with ope.Context(g, np.zeros(g.n), 512):
+        used = before - torch.cuda.mem_get_info()[0]
+    assert used <= 160 << 20, used
