@@ -898,39 +898,12 @@ static hipError_t launch_march(ope_ctx* c, const void* F0, const void* F1, void*
   return hipGetLastError();
 }
 
-void march_shape(ope_ctx* c, int q_max, int mc_override, int order, int nt, int narrow, int lines) {
+// What follows from the column chunk ncv: passes, line tile, march chunks.
+static void march_fit(ope_ctx* c, int q_max, int mc_override, int lines, uint32_t ncv) {
   MarchShape& ms = c->ms;
-  ms.order = order ? 1u : 0u;
-  ms.nt = nt ? 1u : 0u;
   const OpeGrid& g = c->g;
   const uint32_t NV = (uint32_t)(c->N / c->vw);
-  // Column chunk of a work-group: whole rows when they have at most 32 vector
-  // columns (one contiguous run of pp rows per pass, no partly idle chunk);
-  // rows of up to 64 the widest of 32, 16 and 8 vector columns that divides
-  // them (no idle lanes; a wide chunk streams long runs per grid point: at
-  // N = 128 in FP64, 512-byte chunks sweep 1.17x faster than 128-byte ones);
-  // else 8 vector columns, one 128-byte line of FP64 or FP32 per grid point
-  // and work-group (at N = 512, 96^3, 32-vector chunks were 5% slower).
-  // Rows that are no whole number of 128-byte lines: equal chunks of at most 128
-  // vector columns, the whole row where it fits, since a chunk shares the lines at
-  // its ends with its neighbours (sweeps A and B of one step in FP64, 8-vector
-  // chunks / at most 32 / 64 / 128: 45x38x51 N = 45 0.62 / 0.42 / 0.37 / 0.37 ms,
-  // 64^3 N = 130 3.86 / 2.50 / 2.09 / 1.96, 250 7.54 / 3.97 / 3.68 / 3.79, 48^3
-  // N = 300 2.97 / 1.95 / 2.02 / 1.81, mixed 127 1.56 / 0.74 / 0.56 / 0.45).
-  // A wide chunk leaves a work-group few points, so the column sums have up to 16
-  // times the partial rows, often too many for the one-launch reduction; with it
-  // counted, a whole CG iteration in chunks of 8 / the widest the one launch still
-  // sums / up to 128: 48^3 N = 45 156 / 104 / 98 us, 99 358 / 250 / 225, 127 496 /
-  // 288 / 242, mixed 127 - / 234 / 131.
-  // `narrow` asks for 8 vector columns at any row width.
-  if (narrow) ms.ncv = NV < 8u ? NV : 8u;
-  else if (NV <= 32u) ms.ncv = NV;
-  else if (c->N * (c->prec == OPE_FP64 ? 8 : 4) % 128 != 0) {
-    const uint32_t k = (NV + 127u) / 128u;
-    ms.ncv = (NV + k - 1) / k;
-  }
-  else if (NV <= 64u) ms.ncv = NV % 32u == 0 ? 32u : (NV % 16u == 0 ? 16u : 8u);
-  else ms.ncv = 8u;
+  ms.ncv = ncv;
   ms.pp = OPE_WG / ms.ncv;
   // passes per plane (1, 2 or 4, at most q_max, default 2; a larger one only
   // while the smaller does not cover the x line): the one that leaves the
@@ -992,6 +965,48 @@ void march_shape(ope_ctx* c, int q_max, int mc_override, int order, int nt, int 
   if (mc > ms.mlen) mc = ms.mlen;
   ms.mchunk = (ms.mlen + mc - 1) / mc;
   ms.mc = (ms.mlen + ms.mchunk - 1) / ms.mchunk;
+}
+
+void march_shape(ope_ctx* c, int q_max, int mc_override, int order, int nt, int narrow, int lines) {
+  MarchShape& ms = c->ms;
+  ms.order = order ? 1u : 0u;
+  ms.nt = nt ? 1u : 0u;
+  const uint32_t NV = (uint32_t)(c->N / c->vw);
+  // Column chunk of a work-group: whole rows when they have at most 32 vector
+  // columns (one contiguous run of pp rows per pass, no partly idle chunk);
+  // rows of up to 64 the widest of 32, 16 and 8 vector columns that divides
+  // them (no idle lanes; a wide chunk streams long runs per grid point: at
+  // N = 128 in FP64, 512-byte chunks sweep 1.17x faster than 128-byte ones);
+  // else 8 vector columns, one 128-byte line of FP64 or FP32 per grid point
+  // and work-group (at N = 512, 96^3, 32-vector chunks were 5% slower).
+  // Rows that are no whole number of 128-byte lines: equal chunks of at most 128
+  // vector columns, the whole row where it fits, since a chunk shares the lines at
+  // its ends with its neighbours (sweeps A and B of one step in FP64, 8-vector
+  // chunks / at most 32 / 64 / 128: 45x38x51 N = 45 0.62 / 0.42 / 0.37 / 0.37 ms,
+  // 64^3 N = 130 3.86 / 2.50 / 2.09 / 1.96, 250 7.54 / 3.97 / 3.68 / 3.79, 48^3
+  // N = 300 2.97 / 1.95 / 2.02 / 1.81, mixed 127 1.56 / 0.74 / 0.56 / 0.45).
+  // A wide chunk leaves a work-group few points, so the column sums have up to 16
+  // times the partial rows, often too many for the one-launch reduction; with it
+  // counted, a whole CG iteration in chunks of 8 / the widest the one launch still
+  // sums / up to 128: 48^3 N = 45 156 / 104 / 98 us, 99 358 / 250 / 225, 127 496 /
+  // 288 / 242, mixed 127 401 / 234 / 131.
+  // `narrow` asks for 8 vector columns at any row width.
+  uint32_t ncv = 8u;
+  if (narrow) {
+    ncv = NV < 8u ? NV : 8u;
+  } else if (NV <= 32u) {
+    ncv = NV;
+  } else if (c->N * (c->prec == OPE_FP64 ? 8 : 4) % 128 != 0) {
+    // where a caller's march chunks make more partial rows of that than the context
+    // has room for, the widest chunk that fits
+    for (uint32_t k = (NV + 127u) / 128u; (NV + k - 1) / k > 8u; ++k) {
+      march_fit(c, q_max, mc_override, lines, (NV + k - 1) / k);
+      if (c->part_cap == 0 || march_rows(c) * c->N <= c->part_cap) return;
+    }
+  } else if (NV <= 64u) {
+    ncv = NV % 32u == 0 ? 32u : (NV % 16u == 0 ? 16u : 8u);
+  }
+  march_fit(c, q_max, mc_override, lines, ncv);
 }
 
 int64_t march_rows(const ope_ctx* c) {

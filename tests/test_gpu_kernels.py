@@ -611,3 +611,27 @@ def test_capped_cg_equals_textbook_iterates_past_the_one_launch_grids(k, graphs)
     Y_ref = O.cg_source(op, U, None, tol=1e-14, max_iter=k)
     assert its == k
     assert np.max(np.abs(Y - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
+
+
+@pytest.mark.parametrize("N", [65, 127])
+def test_many_march_chunks_of_wide_rows_are_accepted(N):
+    """One plane per march chunk with rows swept in wide chunks: the partial rows of
+    the widest chunk exceed the context's partial buffer, so a narrower one is taken
+    instead of refusing the shape; H X and one and three CG iterations."""
+    from paper_2511_06788_amd import ope
+    g = W.unit_box_grid((64, 64, 64))
+    V = np.random.default_rng(N).uniform(0.0, 50.0, g.n)
+    op = O.Operator(g.m, g.h, V)
+    U = W.initial_block(g.n, N, 4)
+    say(f"many march chunks N={N}")
+    with ope.Context(g, V, N) as ctx:
+        ope.ope_set_sweep_shape(ctx.handle, 2, 64, ope.OPE_SWEEP_CHUNK_MAJOR | ope.OPE_SWEEP_LINES8)
+        assert ope.ope_get_sweep_shape(ctx.handle)[1] == 64
+        Ud, Yd = to_dev(U), empty_dev(g.n, N)
+        ope.ope_apply_h(ctx.handle, Ud, Yd)
+        assert np.max(np.abs(to_host(Yd) - O.apply_H(op, U))) <= stencil_bound(op, U)
+        for k in (1, 3):
+            its = ope.ope_source_solve(ctx.handle, Ud, Yd, None, 1e-14, k, allow_maxit=True)
+            Y_ref = O.cg_source(op, U, None, tol=1e-14, max_iter=k)
+            assert its == k
+            assert np.max(np.abs(to_host(Yd) - Y_ref)) <= 1e-12 * np.max(np.abs(Y_ref))
