@@ -531,7 +531,8 @@ ope_status ope_batch_replay(ope_batch* batch, ope_step_info* info);
  * Synchronises; uses a temporary n x N block per tuned bucket. */
 ope_status ope_batch_autotune(ope_batch* batch, int32_t* tuned);
 /* The same search for one context.  The shape changes only the summation
- * order of the CG dot products.  Synchronises; an FP64 context uses a
+ * order of the CG dot products.  It serves ope_apply_h and the sweeps; a small
+ * grid's unpreconditioned CG (one launch, see ope_set_graphs) runs none.  Synchronises; an FP64 context uses a
  * temporary n x N block (an FP32 one its own CG buffers). */
 ope_status ope_autotune(ope_ctx* ctx);
 

@@ -18,15 +18,16 @@
 // Kernels, per level: k_mg_tstencil (r1, one stencil over x0 formed on the
 // fly from b), k_mg_zrestrict (R r1), k_mg_tpost (x1 = x0 + P e and z, one
 // stencil over x1; on level 0 also the per-column partial sums of r^T z and
-// r^T r that the PCG needs); from the first level of at most 4096 nodes down,
-// all levels in one launch (k_mg_coarse).  The
+// r^T r that the PCG needs); from the first level of at most MC_MAX nodes down
+// (as many levels as MC_LEVELS and MC_LDS hold), all in one launch (k_mg_coarse).  The
 // stencil and transfer kernels march along z (see zmarch_shape, tshape); the
 // smoother's factors omega / d are precomputed per level.
 // Layout: every block is n x N row-major (a grid point's N values
 // contiguous), x fastest, as everywhere in the library; a thread owns one
 // 16-byte chunk (VW elements) or one element of a point's row, FP64, or
 // FP32 for mixed-precision contexts (dot products accumulated in FP64).  Columns
-// whose CG has converged are skipped.
+// whose CG has converged are skipped, and keep what the last V-cycle that ran them
+// left, which the first one of every CG has for all columns (pcg_begin).
 #include <algorithm>
 #include <cmath>
 #include <cstring>

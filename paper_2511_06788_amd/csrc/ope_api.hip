@@ -405,11 +405,12 @@ hipError_t cg_cols(ope_ctx* c, int32_t max_iter) {
 bool cg_converged(const ope_ctx* c, bool all_done) { return c->cg_in_flight ? cg_all_done(c, 0) : all_done; }
 
 // CG iterations on H Y = U from the state prepared in rho/target/active, with
-// r in c->Rb[0]; returns the enqueued iteration count in *iters.  The next
-// chunk is enqueued before the flags of the previous one are read, so the GPU
-// does not wait for the host; a chunk enqueued after convergence finds every
-// column inactive and its kernels do nothing (the sweeps exit, the
-// reductions leave inactive columns at alpha = beta = 0).
+// r in c->Rb[0]; returns the enqueued iteration count in *iters.  Work is enqueued
+// behind the flags being read, so the GPU does not wait for the host: the next
+// chunk, or of the eager preconditioned CG (split_chunks) the next iteration's
+// sweeps; past convergence it finds every column inactive and its kernels do
+// nothing (the sweeps exit, the reductions leave inactive columns at alpha =
+// beta = 0).
 // On a small grid the whole CG is one launch (launch_cg_cols): nothing is
 // checked here, and *all_done stays open until the caller has synchronised the
 // stream (cg_converged).
