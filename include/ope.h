@@ -491,8 +491,10 @@ ope_status ope_batch_solve(ope_batch* batch, void* const* U, double tau, double 
  * work items of every problem's own sweep shape, each problem over all XCDs; same
  * kernels and summation order as the per-problem launches, so the results are
  * identical.  shared = 0 (default): every problem's CG runs on its own stream.
- * Measured: on the 64-problem workload (grid edges 24..48, N 16..128) per-problem
- * launches are 4-8% faster, on a batch of large problems alone slightly faster. */
+ * Measured: on the 64-problem workload (grid edges 24..48, N 16..128) 549
+ * problem-steps/s with per-problem launches and 552 with shared ones (538 and 516
+ * after ope_batch_autotune); on a batch of large problems alone per-problem
+ * launches are slightly faster. */
 ope_status ope_batch_set_shared(ope_batch* batch, int32_t shared);
 /* Graph-captured batched step: one HIP graph holding a whole step of every
  * problem (residual and warm start on the problems' streams, then exactly
